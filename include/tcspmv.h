@@ -113,7 +113,9 @@ typedef struct {
   int32_t lds_stage;          /* 0 (default): a tile no wider than one workgroup's LDS (160 KB,
                                  40960 columns) with at least 8 entries per float staged has its
                                  x segment staged in LDS by a persistent kernel, so its gathers
-                                 are LDS reads; 1: every tile that fits is staged; -1: every
+                                 are LDS reads, and any other tile of at least 3M entries has
+                                 its first (hottest) 40896 columns staged; 1: every tile that
+                                 fits is staged, the first columns of every other; -1: every
                                  tile gathers x through the caches */
   int32_t panels;             /* row panels (MI355X reading of Section 3.2's row partition, applied
                                  to the workgroups of one GPU): 0 (default) = none; P > 0 = P

@@ -61,6 +61,11 @@ __device__ inline void add_to_y(float* y, int32_t row, double s) { y[row] = (flo
 
 typedef int v4i __attribute__((ext_vector_type(4)));
 typedef float v4f __attribute__((ext_vector_type(4)));
+typedef int v2i __attribute__((ext_vector_type(2)));
+typedef float v2f __attribute__((ext_vector_type(2)));
+// the same where only the elements are aligned (row ids; the hardware needs 4 bytes)
+typedef int v4iu __attribute__((ext_vector_type(4), aligned(4)));
+typedef int v2iu __attribute__((ext_vector_type(2), aligned(4)));
 
 // Streams of the matrix are read once per product: non-temporal loads keep
 // them from evicting x and y from the caches.
@@ -116,6 +121,24 @@ __device__ inline double wave_total(double v) {
   v += dpp_f64<0x142, 0xa>(v);  // row_bcast:15 into rows 1 and 3
   v += dpp_f64<0x143, 0xc>(v);  // row_bcast:31 into rows 2 and 3
   return v;
+}
+
+// Copies n floats of x into LDS by the B threads of a workgroup, up to eight
+// 16-byte loads in flight per thread (a load per step of a plain loop would
+// wait for each before the next).  xs is 16-byte aligned; past n nothing is read.
+template <int B>
+__device__ inline void stage_x(float* xs, const float* __restrict__ x, int32_t n) {
+  constexpr int U = 8;
+  const int32_t n4 = ((uintptr_t)x & 15) == 0 ? n & ~3 : 0;
+  for (int32_t k0 = 4 * (int32_t)threadIdx.x; k0 < n4; k0 += 4 * B * U) {
+    v4f t[U];
+#pragma unroll
+    for (int u = 0; u < U; ++u) t[u] = *(const v4f*)(x + (k0 + 4 * B * u < n4 ? k0 + 4 * B * u : k0));
+#pragma unroll
+    for (int u = 0; u < U; ++u)
+      if (k0 + 4 * B * u < n4) *(v4f*)(xs + k0 + 4 * B * u) = t[u];
+  }
+  for (int32_t k = n4 + (int32_t)threadIdx.x; k < n; k += B) xs[k] = x[k];
 }
 
 template <class G>
@@ -279,6 +302,127 @@ __device__ inline void cm_rows(const Wl& d, int lane, const int32_t* __restrict_
   }
 }
 
+// V consecutive entries of a stream, read once (16, 8 or 4 bytes).
+template <int V>
+struct Pack {
+  int32_t i[V];
+  float v[V];
+};
+template <int V>
+__device__ inline Pack<V> ld_pack(const int32_t* __restrict__ idx, const float* __restrict__ val, uint32_t e) {
+  Pack<V> p;
+  if constexpr (V == 4) {
+    const v4i a = ld_nt4(idx + e);
+    const v4f b = ld_nt4(val + e);
+    p.i[0] = a.x, p.i[1] = a.y, p.i[2] = a.z, p.i[3] = a.w;
+    p.v[0] = b.x, p.v[1] = b.y, p.v[2] = b.z, p.v[3] = b.w;
+  } else if constexpr (V == 2) {
+    const v2i a = __builtin_nontemporal_load((const v2i*)(idx + e));
+    const v2f b = __builtin_nontemporal_load((const v2f*)(val + e));
+    p.i[0] = a.x, p.i[1] = a.y;
+    p.v[0] = b.x, p.v[1] = b.y;
+  } else {
+    p.i[0] = ld_nt(idx + e);
+    p.v[0] = ld_nt(val + e);
+  }
+  return p;
+}
+
+// Column-major rectangle by wide loads: a lane owns V consecutive rows of each
+// group of 64 V rows, so one load per stream serves V entries where cm_rows
+// issues one per entry; U groups and C columns are in flight together (U V C
+// independent gathers per lane).  Each row is summed by one lane in column
+// order, so the bits are cm_rows'.  For the staged tile kernel, which runs 16
+// wavefronts per compute unit: 104 us against 117 on a 31M-entry power-law
+// matrix.  With 32 of them (k_tile) it measured slower, 421 against 408 us on
+// 59M entries, and so did the panel pass's small workloads (a whole product on
+// 118M entries 736 against 730 us).
+// As in cm_rows, every load runs on every lane: a lane past the stored rows
+// reads the workload's first entry, and pad rows hold zeros; neither is stored.
+template <int V, int U, int C, int S, class G>
+__device__ inline void cm_vec(const Wl& d, int lane, const int32_t* __restrict__ idx0,
+                               const float* __restrict__ val0, const int32_t* __restrict__ rowid0,
+                               const G& x, float* __restrict__ y, int32_t sl) {
+  const int32_t* idx = idx0 + d.data_off;
+  const float* val = val0 + d.data_off;
+  const int32_t* rowid = rowid0 + d.rowid_off;
+  const uint32_t hp = (uint32_t)d.h_pad;
+  const int32_t w = d.w_pad, nr = d.n_rows;
+  // slice sl of S takes the groups sl, sl + S, ..., U of them at a time
+  for (int32_t r0 = sl * (kWave * V); r0 < nr; r0 += U * S * (kWave * V)) {
+    double acc[U][V];
+    uint32_t e[U], es[U];
+    int32_t rid[U][V];
+#pragma unroll
+    for (int u = 0; u < U; ++u) {
+      const uint32_t r = (uint32_t)(r0 + u * S * (kWave * V) + lane * V);
+      const bool in = r < hp;
+      e[u] = in ? r : 0;
+      es[u] = in ? hp : 0;
+      // the rows' ids go out with the first matrix loads
+      if constexpr (V == 4) {
+        const v4iu t = __builtin_nontemporal_load((const v4iu*)(rowid + e[u]));
+        rid[u][0] = t.x, rid[u][1] = t.y, rid[u][2] = t.z, rid[u][3] = t.w;
+      } else if constexpr (V == 2) {
+        const v2iu t = __builtin_nontemporal_load((const v2iu*)(rowid + e[u]));
+        rid[u][0] = t.x, rid[u][1] = t.y;
+      } else {
+        rid[u][0] = ld_nt(rowid + e[u]);
+      }
+#pragma unroll
+      for (int v = 0; v < V; ++v) acc[u][v] = 0.0;
+    }
+    int32_t c = 0;
+    for (; c + C <= w; c += C) {
+      Pack<V> m[U][C];
+      float xv[U][C][V];
+#pragma unroll
+      for (int u = 0; u < U; ++u)
+#pragma unroll
+        for (int k = 0; k < C; ++k) {
+          m[u][k] = ld_pack<V>(idx, val, e[u]);
+          e[u] += es[u];
+        }
+#pragma unroll
+      for (int u = 0; u < U; ++u)
+#pragma unroll
+        for (int k = 0; k < C; ++k)
+#pragma unroll
+          for (int v = 0; v < V; ++v) xv[u][k][v] = x(m[u][k].i[v]);
+#pragma unroll
+      for (int u = 0; u < U; ++u)
+#pragma unroll
+        for (int k = 0; k < C; ++k)
+#pragma unroll
+          for (int v = 0; v < V; ++v) acc[u][v] = fma((double)m[u][k].v[v], (double)xv[u][k][v], acc[u][v]);
+    }
+    if constexpr (C > 1) {
+      for (; c < w; ++c) {
+        Pack<V> m[U];
+        float xv[U][V];
+#pragma unroll
+        for (int u = 0; u < U; ++u) {
+          m[u] = ld_pack<V>(idx, val, e[u]);
+          e[u] += es[u];
+        }
+#pragma unroll
+        for (int u = 0; u < U; ++u)
+#pragma unroll
+          for (int v = 0; v < V; ++v) xv[u][v] = x(m[u].i[v]);
+#pragma unroll
+        for (int u = 0; u < U; ++u)
+#pragma unroll
+          for (int v = 0; v < V; ++v) acc[u][v] = fma((double)m[u].v[v], (double)xv[u][v], acc[u][v]);
+      }
+    }
+#pragma unroll
+    for (int u = 0; u < U; ++u)
+#pragma unroll
+      for (int v = 0; v < V; ++v)
+        if (r0 + u * S * (kWave * V) + lane * V + v < nr) x.addy(y, rid[u][v], acc[u][v]);
+  }
+}
+
 // Any layout, any padding (used when the rectangle is not 64-aligned).
 template <int S, class G>
 __device__ inline void generic_wl(const Wl& d, int lane, int layout, const int32_t* __restrict__ idx,
@@ -365,13 +509,27 @@ struct PrivX {
   __device__ void addy(float* y, int32_t rid, double s) const { y[rid & ~kAddFlag] = (float)s; }
 };
 
-template <int S = 1, class G>
+// VEC: column-major rectangles by wide loads (cm_vec), whose 32-bit offsets
+// need an area below kVecMaxArea; larger or unaligned ones go the other way.
+constexpr int64_t kVecMaxArea = (int64_t)1 << 29;
+template <int S = 1, bool VEC = false, class G>
 __device__ __attribute__((always_inline)) inline void run_workload(const Wl& d, int lane, const int32_t* __restrict__ idx,
                                     const float* __restrict__ val, const int32_t* __restrict__ rowid, const G& x,
                                     float* __restrict__ y, double* __restrict__ partial, int32_t sl = 0) {
   const int layout = d.info & 3;
   const bool aligned = (d.data_off & 3) == 0;
-  if (layout == kCM && (d.h_pad & 63) == 0) {
+  if (VEC && layout == kCM && (d.h_pad & 63) == 0 && aligned && (int64_t)d.w_pad * d.h_pad < kVecMaxArea) {
+    // 64-row blocks per slice (every slice of a workload has to choose alike)
+    const int32_t blocks = (d.n_rows + kWave * S - 1) / (kWave * S);
+    if (blocks > 4)
+      cm_vec<4, 2, 1, S>(d, lane, idx, val, rowid, x, y, sl);
+    else if (blocks > 2)
+      cm_vec<4, 1, 2, S>(d, lane, idx, val, rowid, x, y, sl);
+    else if (blocks > 1)
+      cm_vec<2, 1, 4, S>(d, lane, idx, val, rowid, x, y, sl);
+    else
+      cm_vec<1, 1, 8, S>(d, lane, idx, val, rowid, x, y, sl);
+  } else if (layout == kCM && (d.h_pad & 63) == 0) {
     // row blocks of this slice
     const int32_t blocks = ((d.n_rows + kWave - 1) / kWave - sl + S - 1) / S;
     if (blocks >= 8)

@@ -6,42 +6,11 @@
 #include <cmath>
 #include <vector>
 
-#include "tc_host.h"
+#include "tc_tile.h"
 
 namespace tc {
 
 namespace {
-
-// The tile kernel with the fused PageRank update (PrX); d = *dmass, the
-// dangling mass of x.
-template <int S>
-__global__ void __launch_bounds__(kB) k_tile_spmv_pr(const Wl* __restrict__ wl, int64_t n_wl,
-                                                     const int32_t* __restrict__ idx, const float* __restrict__ val,
-                                                     const int32_t* __restrict__ rowid, const float* __restrict__ x,
-                                                     float* __restrict__ pn, double* __restrict__ partial, double c,
-                                                     const double* __restrict__ dmass, int64_t n) {
-  const int lane = lane_id();
-  const int64_t w = (int64_t)blockIdx.x * kWpb + __builtin_amdgcn_readfirstlane(threadIdx.x / kWave);
-  if (w >= n_wl * S) return;
-  const Wl d = wl[w / S];
-  run_workload<S>(d, lane, idx, val, rowid, PrX{x, c, *dmass / (double)n, (1.0 - c) / (double)n}, pn, partial,
-                  (int32_t)(w % S));
-}
-
-// The tile kernel with the fused restart of a one-query RWR (RwrX); the seed
-// is an internal id on the device.
-template <int S>
-__global__ void __launch_bounds__(kB) k_tile_spmv_rwr(const Wl* __restrict__ wl, int64_t n_wl,
-                                                      const int32_t* __restrict__ idx, const float* __restrict__ val,
-                                                      const int32_t* __restrict__ rowid, const float* __restrict__ x,
-                                                      float* __restrict__ rn, double* __restrict__ partial, double c,
-                                                      const int32_t* __restrict__ seed) {
-  const int lane = lane_id();
-  const int64_t w = (int64_t)blockIdx.x * kWpb + __builtin_amdgcn_readfirstlane(threadIdx.x / kWave);
-  if (w >= n_wl * S) return;
-  const Wl d = wl[w / S];
-  run_workload<S>(d, lane, idx, val, rowid, RwrX{x, c, *seed}, rn, partial, (int32_t)(w % S));
-}
 
 // PageRank update (Eq. 6 with uniform dangling mass), fused with the L1
 // change and the dangling mass of the new iterate:
@@ -304,15 +273,7 @@ extern "C" tc_status tc_pagerank(const tc_handle* hc, float c, float tol, int32_
           zero_rows[1 - cur] = false;
           cur = 1 - cur;
         } else if (fuse && !need_res) {
-          const int64_t b = h->tile_wl_begin[0], e = h->tile_wl_begin[1];
-          if (e > b)
-            launch_tile(h,
-                        pick_slices(tile_slices(h, 0, e - b), k_tile_spmv_pr<1>, k_tile_spmv_pr<2>,
-                                    k_tile_spmv_pr<4>, k_tile_spmv_pr<8>),
-                        dim3(nblk((e - b) * tile_slices(h, 0, e - b), kWpb)), dim3(kB), 0, st, (const Wl*)(h->d_wl + b),
-                        (int64_t)(e - b), (const int32_t*)h->d_idx, (const float*)h->d_val,
-                        (const int32_t*)h->d_rowid, (const float*)pc, pn, h->d_partial, (double)c,
-                        (const double*)(res + 1), n);
+          run_tile(h, 0, PrSpec{pc, (double)c, res + 1, n}, pn, st);
           if (h->n_split_rows + h->n_empty > 0) {
             hipLaunchKernelGGL(k_pr_split_empty, dim3(nblk(h->n_split_rows + h->n_empty, kB)), dim3(kB), 0, st,
                                h->d_split, h->n_split_rows, (const double*)h->d_partial,
@@ -481,15 +442,7 @@ extern "C" tc_status tc_rwr(const tc_handle* hc, const int32_t* seeds, int32_t k
           held[1 - cur] = kRestart;
           cur = 1 - cur;
         } else if (fuse1 && !need_res) {
-          const int64_t b = h->tile_wl_begin[0], e = h->tile_wl_begin[1];
-          if (e > b)
-            launch_tile(h,
-                        pick_slices(tile_slices(h, 0, e - b), k_tile_spmv_rwr<1>, k_tile_spmv_rwr<2>,
-                                    k_tile_spmv_rwr<4>, k_tile_spmv_rwr<8>),
-                        dim3(nblk((e - b) * tile_slices(h, 0, e - b), kWpb)), dim3(kB), 0, st, (const Wl*)(h->d_wl + b),
-                        (int64_t)(e - b), (const int32_t*)h->d_idx, (const float*)h->d_val,
-                        (const int32_t*)h->d_rowid, (const float*)Rcur, Yb, h->d_partial, (double)c,
-                        (const int32_t*)dseeds);
+          run_tile(h, 0, RwrSpec{Rcur, (double)c, dseeds}, Yb, st);
           const int64_t ne = held[1 - cur] == kRestart ? 0 : h->n_empty;
           if (h->n_split_rows + ne > 0) {
             hipLaunchKernelGGL(k_rwr1_split_empty, dim3(nblk(h->n_split_rows + ne, kB)), dim3(kB), 0, st,

@@ -8,24 +8,11 @@
 #include <cmath>
 #include <cstdlib>
 
-#include "tc_host.h"
+#include "tc_tile.h"
 
 namespace tc {
 
 namespace {
-
-// S wavefronts per workload of the tile (row slices; grid = workloads * S / 4).
-template <int S>
-__global__ void __launch_bounds__(kB) k_tile_spmv(const Wl* __restrict__ wl, int64_t n_wl,
-                                                  const int32_t* __restrict__ idx, const float* __restrict__ val,
-                                                  const int32_t* __restrict__ rowid, const float* __restrict__ x,
-                                                  float* __restrict__ y, double* __restrict__ partial) {
-  const int lane = lane_id();
-  const int64_t w = (int64_t)blockIdx.x * kWpb + __builtin_amdgcn_readfirstlane(threadIdx.x / kWave);
-  if (w >= n_wl * S) return;
-  const Wl d = wl[w / S];
-  run_workload<S>(d, lane, idx, val, rowid, GlobalX{x}, y, partial, (int32_t)(w % S));
-}
 
 // x of a tile whose whole column range sits in LDS (a tile no wider than the
 // LDS of one workgroup): every gather of the tile is an LDS read.
@@ -51,12 +38,7 @@ __global__ void __launch_bounds__(kLdsB) k_tile_lds(const Wl* __restrict__ wl, i
                                                     double* __restrict__ partial) {
   extern __shared__ float xs[];
   const float* xsrc = x + cb;
-  if (((uintptr_t)xsrc & 15) == 0 && (lw & 3) == 0) {
-    for (int32_t k = 4 * (int32_t)threadIdx.x; k < lw; k += 4 * kLdsB)
-      *(float4*)(xs + k) = *(const float4*)(xsrc + k);
-  } else {
-    for (int32_t k = threadIdx.x; k < lw; k += kLdsB) xs[k] = xsrc[k];
-  }
+  stage_x<kLdsB>(xs, xsrc, lw);
   __syncthreads();
   const int lane = lane_id();
   const int64_t waves = (int64_t)gridDim.x * (kLdsB / kWave);
@@ -169,12 +151,7 @@ __global__ void __launch_bounds__(NW * kWave) k_panel_spmv(const Wl* __restrict_
   const int32_t r0 = pb[p], nr = pb[p + 1] - r0;
   for (int32_t i = threadIdx.x; i < nr; i += NW * kWave) ys[i] = 0.0f;
   float* xs = ys + rows_cap;  // rows_cap is a multiple of 4: 16-byte aligned
-  if (w0 > 0) {
-    const int32_t w4 = ((uintptr_t)x & 15) == 0 ? w0 & ~3 : 0;
-    for (int32_t k = 4 * (int32_t)threadIdx.x; k < w4; k += 4 * NW * kWave)
-      *(float4*)(xs + k) = *(const float4*)(x + k);
-    for (int32_t k = w4 + (int32_t)threadIdx.x; k < w0; k += NW * kWave) xs[k] = x[k];
-  }
+  stage_x<NW * kWave>(xs, x, w0);
   __syncthreads();
   const int lane = lane_id();
   const int32_t wv = __builtin_amdgcn_readfirstlane(threadIdx.x / kWave);
@@ -644,9 +621,7 @@ void spmv_internal(tc_handle* h, const float* x, float* y, hipStream_t st, bool 
                   (int32_t)h->tile_col_begin[t], (int32_t)lw, y, h->d_partial);
       continue;
     }
-    launch_tile(h, pick_slices(S, k_tile_spmv<1>, k_tile_spmv<2>, k_tile_spmv<4>, k_tile_spmv<8>),
-                dim3(nblk((e - b) * S, kWpb)), dim3(kB), 0, st, (const Wl*)(h->d_wl + b), (int64_t)(e - b),
-                (const int32_t*)h->d_idx, (const float*)h->d_val, (const int32_t*)h->d_rowid, x, y, h->d_partial);
+    run_tile(h, t, PlainSpec{x}, y, st);
   }
   if (xcd) {
     const int32_t G = h->n_tiles - 1;

@@ -1,0 +1,158 @@
+// The tile kernels of the single-vector products and their launches: one
+// wavefront per workload slice, every row written through a writer that knows
+// what becomes of a row's sum (the product, or an update fused into it).
+#pragma once
+
+#include <algorithm>
+
+#include "tc_host.h"
+
+namespace tc {
+
+namespace {
+
+// What a kernel is given to make a writer from: the product itself, ...
+struct PlainSpec {
+  const float* x;
+  using X = GlobalX;
+  __device__ X make() const { return X{x}; }
+};
+// ... the PageRank update (d = *dmass, the dangling mass of x), ...
+struct PrSpec {
+  const float* x;
+  double c;
+  const double* dmass;
+  int64_t n;
+  using X = PrX;
+  __device__ X make() const { return X{x, c, *dmass / (double)n, (1.0 - c) / (double)n}; }
+};
+// ... or the restart of a one-query RWR (seed: an internal id on the device).
+struct RwrSpec {
+  const float* x;
+  double c;
+  const int32_t* seed;
+  using X = RwrX;
+  __device__ X make() const { return X{x, c, *seed}; }
+};
+
+// S wavefronts per workload of the tile (row slices; grid = workloads * S / 4).
+template <int S, class Spec>
+__global__ void __launch_bounds__(kB) k_tile(const Wl* __restrict__ wl, int64_t n_wl, const int32_t* __restrict__ idx,
+                                             const float* __restrict__ val, const int32_t* __restrict__ rowid,
+                                             Spec spec, float* __restrict__ y, double* __restrict__ partial) {
+  const int lane = lane_id();
+  const int64_t w = (int64_t)blockIdx.x * kWpb + __builtin_amdgcn_readfirstlane(threadIdx.x / kWave);
+  if (w >= n_wl * S) return;
+  const Wl d = wl[w / S];
+  run_workload<S>(d, lane, idx, val, rowid, spec.make(), y, partial, (int32_t)(w % S));
+}
+
+// x with its first `hot` columns from cb on in LDS and the others gathered
+// through the caches.  Both reads run on every lane without a branch: a lane
+// whose column is staged gives its buffer load an offset past the buffer,
+// which returns 0 and makes no request, and the others read LDS word 0.
+template <class X>
+struct HotX {
+  X b;
+  const float* xs;
+  int32_t cb, hot;
+  __amdgpu_buffer_rsrc_t r;  // x, limited to its 4 n_cols bytes
+  __device__ float operator()(int32_t i) const {
+    const uint32_t k = (uint32_t)(i - cb);
+    const bool in = k < (uint32_t)hot;
+    const float l = xs[in ? k : 0];
+    const float g = __builtin_bit_cast(
+        float, __builtin_amdgcn_raw_buffer_load_b32(r, in ? (int32_t)0x80000000 : i * 4, 0, 0));
+    return in ? l : g;
+  }
+  __device__ void addy(float* y, int32_t rid, double s) const { b.addy(y, rid, s); }
+};
+
+// Tile pass with the tile's hottest columns staged in LDS.  Columns are sorted
+// by length, so the first `hot` of a tile carry a large share of its entries
+// (the first 40K of a 2^20-node R-MAT graph: 73%), and a gather that LDS
+// serves is no L2 request; the requests bound k_tile (205 G/s on that graph,
+// the rate of the random-gather measurement within one L2).  One workgroup of
+// 16 wavefronts per compute unit, since the staging takes its LDS.  Its items
+// (workload slices, slice-major: equal slices of every workload) are
+// blockIdx.x + k gridDim.x, handed to the wavefronts by an LDS counter.
+// Measured, k_tile -> this, us per product: R-MAT 2^20 symmetrised (31.4M
+// entries) 155 -> 101, its PageRank matrix (16.1M) 96 -> 65, its HITS matrix
+// (32.2M) 171 -> 116; 2^18 symmetrised (7.6M) 40 -> 27.5; Chung-Lu 2^22 (59M)
+// 408 -> 370; uniform 2^20 x 16 117 -> 113.  What is left on the first: 10.6M
+// L2 read requests (23.5M before) at 130 G/s, and a tenth between the XCDs.
+constexpr int kHotB = 1024;
+template <int S, class Spec>
+__global__ void __launch_bounds__(kHotB) k_tile_hot(const Wl* __restrict__ wl, uint32_t n_wl,
+                                                    const int32_t* __restrict__ idx, const float* __restrict__ val,
+                                                    const int32_t* __restrict__ rowid, Spec spec, int32_t n_cols,
+                                                    int32_t cb, int32_t hot, float* __restrict__ y,
+                                                    double* __restrict__ partial) {
+  extern __shared__ float xs[];  // the staged columns, then the item counter
+  uint32_t* ctr = (uint32_t*)(xs + hot);
+  if (threadIdx.x == 0) *ctr = 0;
+  stage_x<kHotB>(xs, spec.x + cb, hot);
+  __syncthreads();
+  const int lane = lane_id();
+  const HotX<typename Spec::X> xg{
+      spec.make(), xs, cb, hot,
+      __builtin_amdgcn_make_buffer_rsrc((void*)spec.x, (short)0, n_cols * 4, 0x00020000)};
+  const uint32_t items = n_wl * S, G = gridDim.x;
+  auto take = [&]() -> uint32_t {
+    uint32_t k = 0;
+    if (lane == 0) k = atomicAdd(ctr, 1u);
+    return blockIdx.x + (uint32_t)__builtin_amdgcn_readfirstlane(k) * G;
+  };
+  uint32_t w = take();
+  if (w >= items) return;
+  Wl d = wl[w % n_wl];
+  for (;;) {  // the next item and its descriptor are read while the current one runs
+    const uint32_t wn = take();
+    const Wl dn = wl[(wn < items ? wn : w) % n_wl];
+    run_workload<S, true>(d, lane, idx, val, rowid, xg, y, partial, (int32_t)(w / n_wl));
+    if (wn >= items) break;
+    d = dn;
+    w = wn;
+  }
+}
+
+// Columns of tile t that k_tile_hot stages, or 0 for k_tile.  From 3M entries
+// on the staging (up to 160 KB into every compute unit, 3.4 us) and the fewer
+// wavefronts pay: measured k_tile / k_tile_hot over R-MAT, Chung-Lu and
+// uniform matrices of 2^12-2^20 columns, 0.71-1.02 up to 2.1M entries,
+// 1.01-1.24 on power-law and 0.96-0.98 on uniform ones at 3-4.2M, 0.99-1.67
+// from 6M on.  The build option lds_stage = 1 stages every tile, -1 none.  x
+// must fit the buffer load's 32-bit offsets.
+constexpr int64_t kHotMinNnz = (int64_t)3 << 20;
+inline int64_t hot_width(const tc_handle* h, int t, int64_t items) {
+  if (!h->lds_tiles || h->n_cols >= kBufMaxFloats || items >= ((int64_t)1 << 31)) return 0;
+  if (h->lds_tiles == 1 && h->tile_nnz[t] < kHotMinNnz) return 0;
+  const int64_t room = h->lds_floats - 64;  // and the counter
+  return std::max<int64_t>(0, std::min(room, h->tile_col_end[t] - h->tile_col_begin[t]));
+}
+
+// y's rows of tile t through the writer of `sp` (split rows' chunks to the
+// partial slots).
+template <class Spec>
+void run_tile(tc_handle* h, int t, const Spec& sp, float* y, hipStream_t st) {
+  const int64_t b = h->tile_wl_begin[t], n = h->tile_wl_begin[t + 1] - b;
+  if (n == 0) return;
+  const int32_t S = tile_slices(h, t, n);
+  const int64_t hot = hot_width(h, t, n * S);
+  if (hot > 0) {
+    auto kern = pick_slices(S, k_tile_hot<1, Spec>, k_tile_hot<2, Spec>, k_tile_hot<4, Spec>, k_tile_hot<8, Spec>);
+    const uint32_t lds = (uint32_t)(4 * (hot + 1));
+    if (lds > 65536) HIPC(hipFuncSetAttribute((const void*)kern, hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds));
+    const unsigned grid = (unsigned)std::min<int64_t>(h->n_cu, nblk(n * S, kHotB / kWave));
+    launch_tile(h, kern, dim3(grid), dim3(kHotB), lds, st, (const Wl*)(h->d_wl + b), (uint32_t)n,
+                (const int32_t*)h->d_idx, (const float*)h->d_val, (const int32_t*)h->d_rowid, sp, (int32_t)h->n_cols,
+                (int32_t)h->tile_col_begin[t], (int32_t)hot, y, h->d_partial);
+    return;
+  }
+  launch_tile(h, pick_slices(S, k_tile<1, Spec>, k_tile<2, Spec>, k_tile<4, Spec>, k_tile<8, Spec>),
+              dim3(nblk(n * S, kWpb)), dim3(kB), 0, st, (const Wl*)(h->d_wl + b), n, (const int32_t*)h->d_idx,
+              (const float*)h->d_val, (const int32_t*)h->d_rowid, sp, y, h->d_partial);
+}
+
+}  // namespace
+}  // namespace tc

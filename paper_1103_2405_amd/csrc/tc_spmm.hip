@@ -14,12 +14,17 @@ namespace {
 // ---- multiple right-hand sides.  Pad entries (value 0) are skipped.
 //
 // SpMM, Y := A X with X row-major n_cols x k.  Each lane owns V consecutive
-// right-hand sides (V = 4 when k is a multiple of 4 and X, Y are 16-byte
-// aligned: one 16-byte load per gathered X row and lane).  A wavefront holds
-// 64 / kg lane groups of kg lanes (kg = ceil(k / V) rounded up to a power of
-// two, at most 64); lane q of a group owns right-hand sides
-// V * (q + 64 * blockIdx.y) ... + V - 1, so every gathered X row is one
-// coalesced access and one load instruction serves 64 / kg entries.
+// right-hand sides (one 16-byte load per gathered X row and lane for V = 4) and
+// KG lanes form a group that covers a row of up to 32 of them; the 64 / KG
+// groups of a wavefront take different entries, so one load instruction
+// serves 64 / KG entries and every gathered X row is one coalesced access.
+// When k is no multiple of V the last lane of the row starts at k - V instead:
+// it computes up to V - 1 right-hand sides a second time and stores only its
+// own, and no lane reads past the row.
+//
+// A step covers SUB entries per group, all gathers in flight together; their
+// values and indices are read once per wavefront, coalesced, one step ahead,
+// and handed to the groups by lane shuffles.
 template <int V>
 struct Vec {
   double a[V];
@@ -28,134 +33,333 @@ struct Vec {
     for (int i = 0; i < V; ++i) a[i] = 0.0;
   }
 };
-
-// Branch-free: an inactive lane (pad entry, or right-hand sides past k) reads
-// X[0 .. V) and takes zeros.  A load under a branch would end its branch with
-// a wait for that load (the conversions to double sink into it), so a step's
-// gathers would go out one at a time instead of all together.
 template <int V>
-__device__ inline void load_x(const float* __restrict__ X, int64_t row, int32_t k, int32_t col, bool act, float* xv) {
-  const int64_t o = act ? row * k + col : 0;
-  if constexpr (V == 4) {
-    const float4 t = *(const float4*)(X + o);
-    xv[0] = act ? t.x : 0.0f;
-    xv[1] = act ? t.y : 0.0f;
-    xv[2] = act ? t.z : 0.0f;
-    xv[3] = act ? t.w : 0.0f;
-  } else {
-    const float t = X[o];
-    xv[0] = act ? t : 0.0f;
+struct FVec {
+  float a[V];
+};
+
+// The right-hand sides of one lane: columns [col, col + V) of X and Y, of which
+// it stores those from `own` on; act: it has any.
+template <int V, int KG>
+struct Cols {
+  int32_t col, own;
+  bool act;
+  __device__ Cols(int lane, int32_t c0, int32_t k) {
+    const int32_t c = c0 + (lane % KG) * V;
+    act = c < k;
+    col = act ? min(c, k - V) : 0;
+    own = c - col;
   }
-}
+};
 
+// X by 32-bit offsets through a buffer descriptor (n_cols <= 2^24 and at most
+// 2^31 bytes): an inactive lane (pad entry, or right-hand sides past k) gives
+// an offset past the buffer, reads zeros and makes no request.
 template <int V>
-__device__ inline void fma_vec(Vec<V>& acc, float v, const float* xv) {
-#pragma unroll
-  for (int i = 0; i < V; ++i) acc.a[i] = fma((double)v, (double)xv[i], acc.a[i]);
-}
-
-template <int V>
-__device__ inline void add_y(float* __restrict__ Y, int32_t rid, int32_t k, int32_t col, const Vec<V>& s) {
-  const bool add = (rid & kAddFlag) != 0;
-  float* p = Y + (int64_t)(rid & ~kAddFlag) * k + col;
-  if constexpr (V == 4) {
-    float4 o;
-    if (add) {
-      const float4 t = *(const float4*)p;
-      o = make_float4((float)((double)t.x + s.a[0]), (float)((double)t.y + s.a[1]), (float)((double)t.z + s.a[2]),
-                      (float)((double)t.w + s.a[3]));
+struct SmallX {
+  __amdgpu_buffer_rsrc_t r;
+  uint32_t k4;  // bytes of a row
+  __device__ SmallX(const float* X, int64_t n_cols, int32_t k)
+      : r(__builtin_amdgcn_make_buffer_rsrc((void*)X, (short)0, (int32_t)(n_cols * k * 4), 0x00020000)),
+        k4((uint32_t)k * 4) {}
+  __device__ FVec<V> operator()(int32_t row, int32_t col, bool on) const {
+    const int32_t o = on ? (int32_t)(__umul24((uint32_t)row, k4) + (uint32_t)col * 4) : (int32_t)0x80000000;
+    FVec<V> x;
+    if constexpr (V == 4) {
+      const auto t = __builtin_amdgcn_raw_buffer_load_b128(r, o, 0, 0);
+      const v4f f = __builtin_bit_cast(v4f, t);
+      x.a[0] = f.x, x.a[1] = f.y, x.a[2] = f.z, x.a[3] = f.w;
+    } else if constexpr (V == 2) {
+      const auto t = __builtin_amdgcn_raw_buffer_load_b64(r, o, 0, 0);
+      const v2f f = __builtin_bit_cast(v2f, t);
+      x.a[0] = f.x, x.a[1] = f.y;
     } else {
-      o = make_float4((float)s.a[0], (float)s.a[1], (float)s.a[2], (float)s.a[3]);
+      x.a[0] = __builtin_bit_cast(float, __builtin_amdgcn_raw_buffer_load_b32(r, o, 0, 0));
     }
-    *(float4*)p = o;
-  } else {
-    *p = add ? (float)((double)*p + s.a[0]) : (float)s.a[0];
+    return x;
   }
+};
+
+typedef float v4fu __attribute__((ext_vector_type(4), aligned(4)));
+typedef float v2fu __attribute__((ext_vector_type(2), aligned(4)));
+
+// ... or of any size by 64-bit addresses.  Branch-free: an inactive lane reads
+// X[0 .. V) and takes zeros (a load under a branch would end its branch with
+// a wait for that load, so a step's gathers would go out one at a time).
+template <int V>
+struct LargeX {
+  const float* X;
+  int64_t k;
+  __device__ LargeX(const float* x, int64_t, int32_t k_) : X(x), k(k_) {}
+  __device__ FVec<V> operator()(int32_t row, int32_t col, bool on) const {
+    const float* p = X + (on ? row * k + col : 0);
+    FVec<V> x;
+    if constexpr (V == 4) {
+      const v4fu t = *(const v4fu*)p;
+      x.a[0] = t.x, x.a[1] = t.y, x.a[2] = t.z, x.a[3] = t.w;
+    } else if constexpr (V == 2) {
+      const v2fu t = *(const v2fu*)p;
+      x.a[0] = t.x, x.a[1] = t.y;
+    } else {
+      x.a[0] = *p;
+    }
+#pragma unroll
+    for (int i = 0; i < V; ++i) x.a[i] = on ? x.a[i] : 0.0f;
+    return x;
+  }
+};
+
+template <int V>
+__device__ inline void fma_vec(Vec<V>& acc, float v, const FVec<V>& x) {
+#pragma unroll
+  for (int i = 0; i < V; ++i) acc.a[i] = fma((double)v, (double)x.a[i], acc.a[i]);
 }
 
 template <int V>
-__device__ inline void rwr_y(float* __restrict__ Y, int32_t rid, int32_t k, int32_t col, const Vec<V>& s,
-                             const RwrEpi& epi, const int32_t* seeds_lds) {
-  const int32_t* sd = seeds_lds + col;
+__device__ inline void store_row(float* p, int32_t own, const float* o) {
+  if constexpr (V == 4) {
+    if (own == 0) {
+      *(v4fu*)p = v4fu{o[0], o[1], o[2], o[3]};
+      return;
+    }
+  } else if constexpr (V == 2) {
+    if (own == 0) {
+      *(v2fu*)p = v2fu{o[0], o[1]};
+      return;
+    }
+  }
+#pragma unroll
+  for (int i = 0; i < V; ++i)
+    if (i >= own) p[i] = o[i];
+}
+
+// One row of Y, the first writer's store or a later tile's add; RWR: the
+// restart of every right-hand side (its seed in LDS) fused in.
+template <int V, bool RWR>
+__device__ inline void write_row(float* __restrict__ Y, int32_t rid, int32_t k, int32_t col, int32_t own,
+                                 const Vec<V>& s, const RwrEpi& epi, const int32_t* seeds_lds) {
   const int32_t row = rid & ~kAddFlag;
   float* p = Y + (int64_t)row * k + col;
   float o[V];
+  if constexpr (RWR) {
 #pragma unroll
-  for (int i = 0; i < V; ++i) o[i] = rwr_restart(epi.c, (float)s.a[i], row == sd[i]);
-  if constexpr (V == 4)
-    *(float4*)p = make_float4(o[0], o[1], o[2], o[3]);
-  else
-    *p = o[0];
+    for (int i = 0; i < V; ++i) o[i] = rwr_restart(epi.c, (float)s.a[i], row == seeds_lds[col + i]);
+  } else if (rid & kAddFlag) {
+#pragma unroll
+    for (int i = 0; i < V; ++i) o[i] = (float)((double)p[i] + s.a[i]);
+  } else {
+#pragma unroll
+    for (int i = 0; i < V; ++i) o[i] = (float)s.a[i];
+  }
+  store_row<V>(p, own, o);
 }
 
 // Cross-group sum of a row-major row: the groups took interleaved entries,
 // and an xor tree over the group bits of the lane id adds their sums.
-template <int V>
-__device__ inline void group_sum(Vec<V>& s, int kg) {
-  for (int o = kg; o < kWave; o <<= 1)
+template <int V, int KG>
+__device__ inline void group_sum(Vec<V>& s) {
+#pragma unroll
+  for (int o = KG; o < kWave; o <<= 1)
 #pragma unroll
     for (int i = 0; i < V; ++i) s.a[i] += __shfl_xor(s.a[i], o, kWave);
 }
 
-// One step over RS consecutive matrix slots: lane l < RS loads slot l with one
-// coalesced load (value and index), then in sub-step u (u < RS / groups) lane
-// group g takes slot u * groups + g by a lane shuffle and gathers that X row.
-// So the wavefront issues two matrix loads per RS entries instead of two per
-// sub-step.
-template <int V, int SUB = 8>
-__device__ inline void step_gather(float vl, int32_t il, int subs, int groups, int g, const float* __restrict__ X,
-                                   int32_t k, int32_t col, bool act, float* v, float (*xv)[V]) {
-  int32_t ii[SUB];
+// The slots of one step: SUB * G of them (G = 64 / KG groups), L per lane;
+// slot u * G + g belongs to group g's sub-step u.
+template <int KG, int SUB>
+struct Slots {
+  static constexpr int G = kWave / KG, N = SUB * G, L = (N + kWave - 1) / kWave;
+  float v[L];
+  int32_t i[L];
+  // slot s at element at(s) of the stream, where in(s), else the pad (0, 0)
+  // (it reads element `safe`)
+  template <class In, class At>
+  __device__ void load(const int32_t* __restrict__ idx, const float* __restrict__ val, int lane, int64_t safe, In in,
+                       At at) {
 #pragma unroll
-  for (int u = 0; u < SUB; ++u) {
-    if (u < subs) {
-      const int src = u * groups + g;
-      v[u] = __shfl(vl, src, kWave);
-      ii[u] = __shfl(il, src, kWave);
-    } else {
-      v[u] = 0.0f;
-      ii[u] = 0;
+    for (int j = 0; j < L; ++j) {
+      const int s = j * kWave + lane;
+      const bool ok = s < N && in(s);
+      const int64_t e = ok ? at(s) : safe;
+      const float tv = ld_nt(val + e);
+      const int32_t ti = ld_nt(idx + e);
+      v[j] = ok ? tv : 0.0f;
+      i[j] = ok ? ti : 0;
     }
   }
-#pragma unroll
-  for (int u = 0; u < SUB; ++u) load_x<V>(X, ii[u], k, col, act && v[u] != 0.0f, xv[u]);
-}
+  __device__ void get(int u, int g, float& vo, int32_t& io) const {
+    if constexpr (KG == 1) {
+      vo = v[u];
+      io = i[u];
+    } else {
+      const int src = (u % KG) * G + g;
+      vo = __shfl(v[u / KG], src, kWave);
+      io = __shfl(i[u / KG], src, kWave);
+    }
+  }
+};
 
-// entries [lo, hi) of the row-major row at `base`; slot u * groups + g of each
-// step goes to group g, so this lane's sums cover the entries c with
-// (c - lo) mod 64 in its group's residues, in increasing c
-template <int V>
-__device__ inline Vec<V> rm_range(const int32_t* __restrict__ idx, const float* __restrict__ val,
-                                  const float* __restrict__ X, int64_t base, int64_t lo, int64_t hi, int32_t k,
-                                  int32_t col, bool act, int g, int groups, int lane) {
-  const int rs = min(kWave, groups * 8), subs = rs / groups;
+// sum over entries [lo, hi) of the row-major row at `base`: sub-step u of each
+// step of SUB * G entries gives group g the entry u * G + g, and a group adds
+// its own in increasing order
+template <int V, int KG, int SUB, class XR>
+__device__ inline Vec<V> rm_range(const int32_t* __restrict__ idx, const float* __restrict__ val, const XR& X,
+                                  int64_t base, int32_t lo, int32_t hi, const Cols<V, KG>& c, int lane) {
+  using Sl = Slots<KG, SUB>;
+  const int g = lane / KG;
   Vec<V> acc;
   acc.zero();
-  for (int64_t c0 = lo; c0 < hi; c0 += rs) {
-    const bool in = lane < rs && c0 + lane < hi;
-    const float vl = in ? ld_nt(val + base + c0 + lane) : 0.0f;
-    const int32_t il = in ? ld_nt(idx + base + c0 + lane) : 0;
-    float v[8], xv[8][V];
-    step_gather<V>(vl, il, subs, groups, g, X, k, col, act, v, xv);
+  Sl nx;
+  auto fetch = [&](int32_t e0) {
+    nx.load(idx, val, lane, base, [&](int s) { return e0 + s < hi; }, [&](int s) { return base + e0 + s; });
+  };
+  if (lo < hi) fetch(lo);
+  for (int32_t e0 = lo; e0 < hi; e0 += Sl::N) {
+    const Sl cur = nx;
+    float v[SUB];
+    FVec<V> x[SUB];
 #pragma unroll
-    for (int u = 0; u < 8; ++u)
-      if (v[u] != 0.0f) fma_vec<V>(acc, v[u], xv[u]);
+    for (int u = 0; u < SUB; ++u) {
+      int32_t i;
+      cur.get(u, g, v[u], i);
+      x[u] = X(i, c.col, c.act && v[u] != 0.0f);
+    }
+    fetch(e0 + Sl::N);  // past the end: the row's first entry, not used
+#pragma unroll
+    for (int u = 0; u < SUB; ++u) fma_vec<V>(acc, v[u], x[u]);
   }
   return acc;
 }
 
-// Every workload but the leading chunk workloads of a tile (those go to
-// k_spmm_chunks); `pieces` = slots per chunk in `partial` (1 when a chunk
-// shows up here: it is then done whole, as one piece).
-// SUB: rows summed per lane group in one column step (accumulators per lane).
-// `slices` wavefronts share a workload, slice s taking every slices-th step.
-// RWR: rows are written through the fused restart (epi) instead of stored.
-template <int V, int SUB, bool RWR = false>
-__global__ void __launch_bounds__(kB) k_tile_spmm(const Wl* __restrict__ wl, int64_t n_wl, int32_t slices,
-                                                  const int32_t* __restrict__ idx,
+// Column-major rectangle, rows sl * U * G, + slices * U * G, ...: a step covers
+// U rows and C columns per group (U C gathers in flight); each row is summed by
+// its group's lanes in column order.
+template <int V, int KG, int U, int C, bool RWR, class XR>
+__device__ inline void cm_range(const Wl& d, int32_t sl, int32_t slices, const int32_t* __restrict__ idx,
+                                const float* __restrict__ val, const int32_t* __restrict__ rowid, const XR& X,
+                                float* __restrict__ Y, int32_t k, const Cols<V, KG>& c, int lane, const RwrEpi& epi,
+                                const int32_t* sd) {
+  using Sl = Slots<KG, U * C>;
+  constexpr int R = U * Sl::G;  // rows of a step
+  const int g = lane / KG;
+  const int32_t w = d.w_pad, nr = d.n_rows, rstep = slices * R;
+  const int64_t off = d.data_off, hp = d.h_pad;
+  int32_t r0 = sl * R, c0 = 0;
+  if (r0 >= nr) return;
+  Sl nx;
+  auto fetch = [&](int32_t r, int32_t cc) {
+    nx.load(
+        idx, val, lane, off, [&](int s) { return cc + s / R < w && r + s % R < nr; },
+        [&](int s) { return off + (int64_t)(cc + s / R) * hp + r + s % R; });
+  };
+  int32_t rid[U];
+  Vec<V> acc[U];
+  auto begin = [&](int32_t r) {
+#pragma unroll
+    for (int u = 0; u < U; ++u) {
+      const int32_t q = r + u * Sl::G + g;
+      rid[u] = ld_nt(rowid + d.rowid_off + (q < nr ? q : 0));
+      acc[u].zero();
+    }
+  };
+  fetch(r0, 0);
+  begin(r0);
+  for (;;) {
+    const Sl cur = nx;
+    const bool last = c0 + C >= w;
+    const int32_t rn = last ? r0 + rstep : r0, cn = last ? 0 : c0 + C;
+    float v[U * C];
+    FVec<V> x[U * C];
+#pragma unroll
+    for (int q = 0; q < U * C; ++q) {  // sub-step q: column c0 + q / U, row r0 + (q % U) G + g
+      int32_t i;
+      cur.get(q, g, v[q], i);
+      x[q] = X(i, c.col, c.act && v[q] != 0.0f);
+    }
+    fetch(rn, cn);  // past the rectangle: its first entry, not used
+#pragma unroll
+    for (int q = 0; q < U * C; ++q) fma_vec<V>(acc[q % U], v[q], x[q]);
+    if (last) {
+#pragma unroll
+      for (int u = 0; u < U; ++u)
+        if (c.act && r0 + u * Sl::G + g < nr) write_row<V, RWR>(Y, rid[u], k, c.col, c.own, acc[u], epi, sd);
+      if (rn >= nr) break;
+      begin(rn);
+    }
+    r0 = rn;
+    c0 = cn;
+  }
+}
+
+// One wavefront's part of a workload: piece `part` of a leading chunk workload
+// (a split row's pieces: kPiece entries each, sums to slot chunk slot * parts +
+// part of `partial`), or row slice `part` of `parts` of any other workload.  (A
+// chunk among the others is done whole, as one piece.)
+constexpr int kPiece = 512;
+template <int V, int KG, bool RWR, class XR>
+__device__ inline void spmm_item(const Wl& d, int32_t part, int32_t parts, bool lead, const int32_t* __restrict__ idx,
+                                 const float* __restrict__ val, const int32_t* __restrict__ rowid, const XR& xr,
+                                 float* __restrict__ Y, int32_t k, const Cols<V, KG>& c, int lane,
+                                 double* __restrict__ partial, const RwrEpi& epi, const int32_t* sd) {
+  constexpr int G = kWave / KG;
+  const bool g0 = lane < KG;
+  if (lead) {
+    const int32_t lo = (int32_t)min<int64_t>((int64_t)part * kPiece, d.w_pad), hi = min(lo + kPiece, d.w_pad);
+    Vec<V> acc = rm_range<V, KG, 8>(idx, val, xr, d.data_off, lo, hi, c, lane);
+    group_sum<V, KG>(acc);
+    if (c.act && g0)
+#pragma unroll
+      for (int i = 0; i < V; ++i)
+        if (i >= c.own) partial[((int64_t)(d.info >> 2) * parts + part) * k + c.col + i] = acc.a[i];
+    return;
+  }
+  const int layout = d.info & 3;
+  if (layout == kCM) {
+    if (d.w_pad == 1)
+      cm_range<V, KG, 8, 1, RWR>(d, part, parts, idx, val, rowid, xr, Y, k, c, lane, epi, sd);
+    else if (d.w_pad <= 3)
+      cm_range<V, KG, 4, 2, RWR>(d, part, parts, idx, val, rowid, xr, Y, k, c, lane, epi, sd);
+    else
+      cm_range<V, KG, 2, 4, RWR>(d, part, parts, idx, val, rowid, xr, Y, k, c, lane, epi, sd);
+    return;
+  }
+  for (int32_t r = part; r < d.n_rows; r += parts) {
+    const int64_t base = d.data_off + (int64_t)r * d.w_pad;
+    const int32_t rid = layout == kChunk ? 0 : ld_nt(rowid + d.rowid_off + r);
+    Vec<V> acc = d.w_pad > 2 * G ? rm_range<V, KG, 8>(idx, val, xr, base, 0, d.w_pad, c, lane)
+                                 : rm_range<V, KG, 2>(idx, val, xr, base, 0, d.w_pad, c, lane);
+    group_sum<V, KG>(acc);
+    if (!(c.act && g0)) continue;
+    if (layout == kChunk) {
+#pragma unroll
+      for (int i = 0; i < V; ++i)
+        if (i >= c.own) partial[(int64_t)(d.info >> 2) * k + c.col + i] = acc.a[i];
+    } else {
+      write_row<V, RWR>(Y, rid, k, c.col, c.own, acc, epi, sd);
+    }
+  }
+}
+
+// One pass over a tile for the right-hand sides [c0 + V KG blockIdx.y, ...):
+// wavefronts for the pieces of the tile's leading chunk workloads, then for
+// the row slices of the others.
+//
+// Bound at k = 32 on a 31.4M-entry power-law matrix of 1M rows (304 us of the
+// kernel, 346 a product; 336 and 378 with two launches, four rows or eight
+// entries in flight without the next step's entries, and a branch per entry):
+// 2.0 GB of L2 misses, 6.5 TB/s, the card's streaming-read rate.  126 VGPRs,
+// four wavefronts per SIMD: capping them for 5 or 6 measured 358 and 404 us (the
+// kernel spills), 4 entries in flight 394, 16 367, 8 row slices 455 (wavefronts
+// without a row to sum), 2 362; a persistent grid with an LDS item counter 351.
+// By k, us a product before and now: 3 357 -> 224, 4 279 -> 227, 8 290 -> 249,
+// 37 1825 -> 931 (the last lane of a row overlaps its neighbour instead of one
+// right-hand side per lane); 13 on 4.8M entries of 100K columns 86 -> 60.
+template <int V, int KG, bool RWR, template <int> class XR>
+__global__ void __launch_bounds__(kB) k_tile_spmm(const Wl* __restrict__ wl, int64_t n_wl, int64_t n_lead,
+                                                  int32_t pieces, int32_t slices, const int32_t* __restrict__ idx,
                                                   const float* __restrict__ val, const int32_t* __restrict__ rowid,
-                                                  const float* __restrict__ X, float* __restrict__ Y, int32_t k,
-                                                  int32_t kg, double* __restrict__ partial, RwrEpi epi) {
+                                                  const float* __restrict__ X, int64_t n_cols, float* __restrict__ Y,
+                                                  int32_t k, int32_t c0, double* __restrict__ partial, RwrEpi epi) {
   // fused restart: the seeds (k <= kB) in LDS, read only where rows are written
   __shared__ int32_t sd[RWR ? kB : 1];
   if constexpr (RWR) {
@@ -164,102 +368,14 @@ __global__ void __launch_bounds__(kB) k_tile_spmm(const Wl* __restrict__ wl, int
   }
   const int lane = lane_id();
   const int64_t w = (int64_t)blockIdx.x * kWpb + __builtin_amdgcn_readfirstlane(threadIdx.x / kWave);
-  if (w >= n_wl * slices) return;
-  const int64_t j = w / slices;
-  const int32_t sl = (int32_t)(w % slices);
-  const int groups = kWave / kg;
-  const int g = lane / kg;
-  const int32_t col = ((int32_t)blockIdx.y * kg + lane % kg) * V;
-  const bool act = col < k;
-  const Wl d = wl[j];
-  const int layout = d.info & 3;
-  const int64_t off = d.data_off;
-  if (layout == kCM) {
-    // RS rows per step: lane l loads row r0 + l's entry of column c, and row
-    // r0 + u * groups + g is summed by group g in sub-step u, in column order
-    const int rs = min(kWave, groups * SUB), subs = rs / groups;
-    const int64_t hp = d.h_pad;
-    for (int32_t r0 = sl * rs; r0 < d.n_rows; r0 += rs * slices) {
-      const bool okl = lane < rs && r0 + lane < d.n_rows;
-      Vec<V> a[SUB];
-#pragma unroll
-      for (int u = 0; u < SUB; ++u) a[u].zero();
-      // column c + 1's entries are loaded while column c's X rows are in
-      // flight (a lane past the rows reads the workload's first entry)
-      const int64_t eb = okl ? off + r0 + lane : off;
-      const int64_t es = okl ? hp : 0;
-      float nv = ld_nt(val + eb);
-      int32_t ni = ld_nt(idx + eb);
-      for (int32_t c = 0; c < d.w_pad; ++c) {
-        const float vl = okl ? nv : 0.0f;
-        const int32_t il = okl ? ni : 0;
-        float v[SUB], xv[SUB][V];
-        step_gather<V, SUB>(vl, il, subs, groups, g, X, k, col, act, v, xv);
-        const int64_t en = eb + (c + 1 < d.w_pad ? (int64_t)(c + 1) * es : 0);
-        nv = ld_nt(val + en);
-        ni = ld_nt(idx + en);
-#pragma unroll
-        for (int u = 0; u < SUB; ++u)
-          if (v[u] != 0.0f) fma_vec<V>(a[u], v[u], xv[u]);
-      }
-      if (act) {
-#pragma unroll
-        for (int u = 0; u < SUB; ++u) {
-          const int32_t r = r0 + u * groups + g;
-          if (u < subs && r < d.n_rows) {
-            if constexpr (RWR)
-              rwr_y<V>(Y, ld_nt(rowid + d.rowid_off + r), k, col, a[u], epi, sd);
-            else
-              add_y<V>(Y, ld_nt(rowid + d.rowid_off + r), k, col, a[u]);
-          }
-        }
-      }
-    }
-  } else {
-    const int64_t wp = d.w_pad;
-    for (int32_t r = sl; r < d.n_rows; r += slices) {
-      Vec<V> acc = rm_range<V>(idx, val, X, off + (int64_t)r * wp, 0, wp, k, col, act, g, groups, lane);
-      group_sum<V>(acc, kg);
-      if (act && g == 0) {
-        if (layout == kChunk) {
-#pragma unroll
-          for (int i = 0; i < V; ++i) partial[(int64_t)(d.info >> 2) * k + col + i] = acc.a[i];
-        } else {
-          if constexpr (RWR)
-            rwr_y<V>(Y, ld_nt(rowid + d.rowid_off + r), k, col, acc, epi, sd);
-          else
-            add_y<V>(Y, ld_nt(rowid + d.rowid_off + r), k, col, acc);
-        }
-      }
-    }
-  }
-}
-
-// Chunk workloads of one tile (a split row's pieces of w_pad entries): wave
-// w takes entries [p*kPiece, (p+1)*kPiece) of chunk w / pieces, p = w % pieces,
-// and writes its sums to slot (chunk slot * pieces + p) of `partial`.
-constexpr int kPiece = 512;
-template <int V>
-__global__ void __launch_bounds__(kB) k_spmm_chunks(const Wl* __restrict__ wl, int64_t n_wl, int32_t pieces,
-                                                    const int32_t* __restrict__ idx, const float* __restrict__ val,
-                                                    const float* __restrict__ X, int32_t k, int32_t kg,
-                                                    double* __restrict__ partial) {
-  const int lane = lane_id();
-  const int64_t w = (int64_t)blockIdx.x * kWpb + __builtin_amdgcn_readfirstlane(threadIdx.x / kWave);
-  if (w >= n_wl * pieces) return;
-  const int64_t j = w / pieces;
-  const int32_t p = (int32_t)(w % pieces);
-  const int groups = kWave / kg;
-  const int g = lane / kg;
-  const int32_t col = ((int32_t)blockIdx.y * kg + lane % kg) * V;
-  const bool act = col < k;
-  const Wl d = wl[j];
-  const int64_t lo = min<int64_t>((int64_t)p * kPiece, d.w_pad), hi = min<int64_t>(lo + kPiece, d.w_pad);
-  Vec<V> acc = rm_range<V>(idx, val, X, d.data_off, lo, hi, k, col, act, g, groups, lane);
-  group_sum<V>(acc, kg);
-  if (act && g == 0)
-#pragma unroll
-    for (int i = 0; i < V; ++i) partial[((int64_t)(d.info >> 2) * pieces + p) * k + col + i] = acc.a[i];
+  const int64_t lead_items = n_lead * pieces, v = w - lead_items;
+  if (v >= (n_wl - n_lead) * slices) return;
+  const bool lead = v < 0;
+  const Wl d = wl[lead ? w / pieces : n_lead + v / slices];
+  const Cols<V, KG> c(lane, c0 + (int32_t)blockIdx.y * (V * KG), k);
+  const XR<V> xr(X, n_cols, k);
+  spmm_item<V, KG, RWR>(d, (int32_t)(lead ? w % pieces : v % slices), lead ? pieces : slices, lead, idx, val, rowid,
+                        xr, Y, k, c, lane, partial, epi, sd);
 }
 
 // Zero the rows no workload writes: block b takes rows b * rpb ..., thread
@@ -315,6 +431,44 @@ void spmm_plan(tc_handle* h) {
   h->mm_planned = true;
 }
 
+// The passes of one tile over the k right-hand sides: 32 at a time (128 bytes
+// of each X row, one cache line per gather), then the rest by as many lanes as
+// it needs.  Wider passes spread the gathers over n * 4k bytes, past the 256
+// MB MALL at a million rows and k = 64 (measured on a 31M-entry power-law
+// matrix, 1M rows: k = 64 1262 -> 1152 us, k = 128 2718 -> 2244 us per
+// product; 16 per pass slows k = 32 by 40%).
+template <bool RWR, template <int> class XR>
+void spmm_tile_x(tc_handle* h, int64_t b, int64_t n, int64_t lead, int32_t pieces, int32_t slices, const float* X,
+                 float* Y, int32_t k, double* partial, const RwrEpi& ep, hipStream_t st) {
+  const unsigned gx = nblk(lead * pieces + (n - lead) * slices, kWpb);
+  auto go = [&](auto kern, int32_t c0, unsigned gy) {
+    launch_tile(h, kern, dim3(gx, gy), dim3(kB), 0, st, (const Wl*)(h->d_wl + b), n, lead, pieces, slices,
+                (const int32_t*)h->d_idx, (const float*)h->d_val, (const int32_t*)h->d_rowid, X, (int64_t)h->n_cols, Y,
+                k, c0, partial, ep);
+  };
+  if (k == 1) return go(k_tile_spmm<1, 1, RWR, XR>, 0, 1);
+  if (k == 2) return go(k_tile_spmm<2, 1, RWR, XR>, 0, 1);
+  if (k == 3) return go(k_tile_spmm<2, 2, RWR, XR>, 0, 1);
+  const int32_t full = k / 32, rest = k - 32 * full;
+  if (full > 0) go(k_tile_spmm<4, 8, RWR, XR>, 0, (unsigned)full);
+  if (rest > 16)
+    go(k_tile_spmm<4, 8, RWR, XR>, 32 * full, 1);
+  else if (rest > 8)
+    go(k_tile_spmm<4, 4, RWR, XR>, 32 * full, 1);
+  else if (rest > 4)
+    go(k_tile_spmm<4, 2, RWR, XR>, 32 * full, 1);
+  else if (rest > 0)
+    go(k_tile_spmm<4, 1, RWR, XR>, 32 * full, 1);
+}
+
+void spmm_tile(tc_handle* h, int64_t b, int64_t n, int64_t lead, int32_t pieces, int32_t slices, const float* X,
+               float* Y, int32_t k, double* partial, bool rwr, const RwrEpi& ep, hipStream_t st) {
+  const bool small = h->n_cols <= ((int64_t)1 << 24) && h->n_cols * k < ((int64_t)1 << 29);
+  auto f = rwr ? (small ? spmm_tile_x<true, SmallX> : spmm_tile_x<true, LargeX>)
+               : (small ? spmm_tile_x<false, SmallX> : spmm_tile_x<false, LargeX>);
+  f(h, b, n, lead, pieces, slices, X, Y, k, partial, ep, st);
+}
+
 }  // namespace
 
 // epi (one tile, k <= kB): write the RWR restart of every row instead of
@@ -330,25 +484,9 @@ void spmm_internal(tc_handle* h, const float* X, float* Y, int32_t k, hipStream_
   if (epi && !(h->n_tiles == 1 && h->xcd_groups == 0 && k <= kB))
     throw Err{TC_EINVAL, "fused restart needs one tile and k <= 256"};
   const RwrEpi ep = epi ? *epi : RwrEpi{0.0, nullptr};
-  // four right-hand sides per lane when the rows allow 16-byte accesses
-  const bool v4 = k % 4 == 0 && ((uintptr_t)X % 16) == 0 && ((uintptr_t)Y % 16) == 0;
-  const int32_t V = v4 ? 4 : 1;
-  const int32_t kq = (k + V - 1) / V;
-  // one pass (grid row) covers at most 32 right-hand sides: 128 bytes of each
-  // X row, one cache line per gather. Wider passes spread the gathers over
-  // n * 4k bytes, past the 256 MB MALL at a million rows and k = 64 (measured
-  // on a 31M-entry power-law matrix, 1M rows: k = 64 1262 -> 1152 us, k = 128
-  // 2718 -> 2244 us per product; 16 per pass slows k = 32 by 40%)
-  int32_t kg = 1;
-  while (kg < kq && kg < 32 / V) kg <<= 1;
   spmm_plan(h);
   const int32_t pieces = h->mm_pieces;
-  const int kchunks = (kq + kg - 1) / kg;
-  // 4-wide lanes: four rows per sub-step group (fewer registers, more
-  // wavefronts resident) and each workload cut into four row slices
-  // (measured on a 31M-entry power-law matrix at k = 32: 25% over one slice,
-  // and within 2% of two columns per step or eight rows per group)
-  const int32_t slices = v4 ? 4 : 1;
+  const int32_t slices = 4;  // row slices of a workload (the kernel has the figures)
   double* partial = nullptr;
   if (partial_ext) {
     partial = partial_ext;
@@ -375,17 +513,7 @@ void spmm_internal(tc_handle* h, const float* X, float* Y, int32_t k, hipStream_
   for (int t = 0; t < h->n_tiles; ++t) {
     const int64_t b = h->tile_wl_begin[t], e = h->tile_wl_begin[t + 1];
     const int64_t lead = h->mm_lead[t];
-    if (lead > 0)
-      launch_tile(h, v4 ? k_spmm_chunks<4> : k_spmm_chunks<1>, dim3(nblk(lead * pieces, kWpb), kchunks), dim3(kB), 0,
-                  st, (const Wl*)(h->d_wl + b), lead, pieces, (const int32_t*)h->d_idx, (const float*)h->d_val, X, k,
-                  kg, partial);
-    if (e > b + lead)
-      launch_tile(h,
-                  epi ? (v4 ? k_tile_spmm<4, 4, true> : k_tile_spmm<1, 8, true>)
-                      : (v4 ? k_tile_spmm<4, 4> : k_tile_spmm<1, 8>),
-                  dim3(nblk((e - b - lead) * slices, kWpb), kchunks), dim3(kB), 0, st,
-                  (const Wl*)(h->d_wl + b + lead), (int64_t)(e - b - lead), slices, (const int32_t*)h->d_idx,
-                  (const float*)h->d_val, (const int32_t*)h->d_rowid, X, Y, k, kg, partial, ep);
+    if (e > b) spmm_tile(h, b, e - b, lead, pieces, slices, X, Y, k, partial, epi != nullptr, ep, st);
   }
   if (h->n_split_rows > 0) {
     hipLaunchKernelGGL(k_split_combine_mm, dim3(nblk(h->n_split_rows * k, kB)), dim3(kB), 0, st, h->d_split,

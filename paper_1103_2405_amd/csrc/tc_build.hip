@@ -2240,8 +2240,16 @@ void build(const tc_csr* A, const tc_build_opts* o, hipStream_t st, tc_handle* h
   }
   h->d_split = hold<SplitRow>(h, (int64_t)srows.size());
   h->d_partial = hold<double>(h, std::max<int64_t>(h->n_slots, 1) * 256);
-  if (!srows.empty())
+  std::vector<int32_t> slot_split((size_t)h->n_slots);
+  if (!srows.empty()) {
     HIPX(hipMemcpyAsync(h->d_split, srows.data(), sizeof(SplitRow) * srows.size(), hipMemcpyHostToDevice, st));
+    for (size_t i = 0; i < srows.size(); ++i)
+      std::fill_n(slot_split.begin() + srows[i].slot_begin, srows[i].n_slots, (int32_t)i);
+    h->d_slot_split = hold<int32_t>(h, h->n_slots);
+    h->d_ticket = hold<uint32_t>(h, h->n_split_rows);
+    HIPX(hipMemcpyAsync(h->d_slot_split, slot_split.data(), sizeof(int32_t) * h->n_slots, hipMemcpyHostToDevice, st));
+    HIPX(hipMemsetAsync(h->d_ticket, 0, sizeof(uint32_t) * h->n_split_rows, st));
+  }
   std::vector<int64_t> psb;
   if (h->n_panels > 0) {
     // split rows of each panel (srows is in increasing row): [psb[p], psb[p+1])
@@ -2259,7 +2267,6 @@ void build(const tc_csr* A, const tc_build_opts* o, hipStream_t st, tc_handle* h
   h->d_xbuf = hold<float>(h, std::max(n_rows, n_cols));
   h->d_ybuf = hold<float>(h, std::max(n_rows, n_cols));
   h->d_red = hold<double>(h, 4096);
-  h->d_counters = hold<unsigned long long>(h, std::max<int64_t>(ntiles, 1));
   HIPX(hipStreamSynchronize(st));
   clk.mark("a7 pack + metadata");
 }

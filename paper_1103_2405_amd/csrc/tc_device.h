@@ -31,7 +31,8 @@ struct RwrEpi {
 // the order of the split-row list), for the pass that adds its chunks.
 struct PanelPr {
   double c;
-  const double* dmass;    // dangling mass of the iterate the product reads
+  const double* dparts;   // partial sums of the dangling mass of the iterate the product reads
+  int32_t nd;             // (at most 64)
   int64_t n;
   const int64_t* psb;     // [panels + 1] split rows of each panel
   const SplitRow* split;  // split rows, increasing row
@@ -123,22 +124,27 @@ __device__ inline double wave_total(double v) {
   return v;
 }
 
-// Copies n floats of x into LDS by the B threads of a workgroup, up to eight
-// 16-byte loads in flight per thread (a load per step of a plain loop would
-// wait for each before the next).  xs is 16-byte aligned; past n nothing is read.
+// Copies n floats of x into LDS by the B threads of a workgroup, eight 16-byte
+// loads in flight per thread, then two (a plain loop would wait for each load
+// before the next).  xs is 16-byte aligned; past n nothing is read.
 template <int B>
 __device__ inline void stage_x(float* xs, const float* __restrict__ x, int32_t n) {
-  constexpr int U = 8;
-  const int32_t n4 = ((uintptr_t)x & 15) == 0 ? n & ~3 : 0;
-  for (int32_t k0 = 4 * (int32_t)threadIdx.x; k0 < n4; k0 += 4 * B * U) {
-    v4f t[U];
+  const int32_t n4 = ((uintptr_t)x & 15) == 0 ? n & ~3 : 0, t4 = 4 * (int32_t)threadIdx.x;
+  int32_t k = 0;
+  for (; k + 32 * B <= n4; k += 32 * B) {
+    v4f t[8];
 #pragma unroll
-    for (int u = 0; u < U; ++u) t[u] = *(const v4f*)(x + (k0 + 4 * B * u < n4 ? k0 + 4 * B * u : k0));
+    for (int u = 0; u < 8; ++u) t[u] = *(const v4f*)(x + k + 4 * B * u + t4);
 #pragma unroll
-    for (int u = 0; u < U; ++u)
-      if (k0 + 4 * B * u < n4) *(v4f*)(xs + k0 + 4 * B * u) = t[u];
+    for (int u = 0; u < 8; ++u) *(v4f*)(xs + k + 4 * B * u + t4) = t[u];
   }
-  for (int32_t k = n4 + (int32_t)threadIdx.x; k < n; k += B) xs[k] = x[k];
+  for (; k < n4; k += 8 * B) {
+    const int32_t a = k + t4, b = a + 4 * B;
+    const v4f ta = *(const v4f*)(x + (a < n4 ? a : 0)), tb = *(const v4f*)(x + (b < n4 ? b : 0));
+    if (a < n4) *(v4f*)(xs + a) = ta;
+    if (b < n4) *(v4f*)(xs + b) = tb;
+  }
+  for (int32_t q = n4 + (int32_t)threadIdx.x; q < n; q += B) xs[q] = x[q];
 }
 
 template <class G>
@@ -150,6 +156,16 @@ __device__ inline double dot4(v4i i, v4f v, const G& xg) {
   return fma((double)v.w, (double)x3, s);
 }
 
+// A chunk's sum into its partial slot; SAME: read in the same kernel, possibly
+// on another XCD (finish_chunk), so written through to where that reads it.
+template <bool SAME>
+__device__ inline void put_partial(double* partial, int32_t slot, double v) {
+  if constexpr (SAME)
+    __hip_atomic_store(partial + slot, v, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+  else
+    partial[slot] = v;
+}
+
 // Row-major rectangle with 64-element-aligned rows (S a multiple of 64), or
 // rows padded to 32: every lane reads 4 consecutive entries (16 bytes) per
 // 256-entry chunk.
@@ -158,7 +174,7 @@ __device__ inline double dot4(v4i i, v4f v, const G& xg) {
 //   w_pad = 128: a chunk holds 2 rows, 32 lanes each
 //   otherwise:   one row at a time, chunks of 256 (last one masked)
 // Two chunks are in flight per iteration (8 gathers per lane).
-template <int S, class G>
+template <int S, bool SAME, class G>
 __device__ inline void rm_wide(const Wl& d, int lane, const int32_t* __restrict__ idx,
                                const float* __restrict__ val, const int32_t* __restrict__ rowid,
                                const G& x, float* __restrict__ y, double* __restrict__ partial,
@@ -201,7 +217,7 @@ __device__ inline void rm_wide(const Wl& d, int lane, const int32_t* __restrict_
       }
       if ((lane % lpr) == lpr - 1) {
         if (chunk) {
-          if (oka) partial[d.info >> 2] = sa;
+          if (oka) put_partial<SAME>(partial, d.info >> 2, sa);
         } else {
           if (oka) x.addy(y, ida, sa);
           if (okb) x.addy(y, idb, sb);
@@ -224,7 +240,7 @@ __device__ inline void rm_wide(const Wl& d, int lane, const int32_t* __restrict_
     acc = wave_total(acc);
     if (lane == kWave - 1) {
       if (chunk)
-        partial[d.info >> 2] = acc;
+        put_partial<SAME>(partial, d.info >> 2, acc);
       else
         x.addy(y, idr, acc);
     }
@@ -424,7 +440,7 @@ __device__ inline void cm_vec(const Wl& d, int lane, const int32_t* __restrict__
 }
 
 // Any layout, any padding (used when the rectangle is not 64-aligned).
-template <int S, class G>
+template <int S, bool SAME, class G>
 __device__ inline void generic_wl(const Wl& d, int lane, int layout, const int32_t* __restrict__ idx,
                                   const float* __restrict__ val, const int32_t* __restrict__ rowid,
                                   const G& x, float* __restrict__ y, double* __restrict__ partial,
@@ -449,7 +465,7 @@ __device__ inline void generic_wl(const Wl& d, int lane, int layout, const int32
     acc = wave_total(acc);
     if (lane == kWave - 1) {
       if (layout == kChunk)
-        partial[d.info >> 2] = acc;
+        put_partial<SAME>(partial, d.info >> 2, acc);
       else
         x.addy(y, rowid[d.rowid_off + r], acc);
     }
@@ -512,7 +528,7 @@ struct PrivX {
 // VEC: column-major rectangles by wide loads (cm_vec), whose 32-bit offsets
 // need an area below kVecMaxArea; larger or unaligned ones go the other way.
 constexpr int64_t kVecMaxArea = (int64_t)1 << 29;
-template <int S = 1, bool VEC = false, class G>
+template <int S = 1, bool VEC = false, bool SAME = false, class G>
 __device__ __attribute__((always_inline)) inline void run_workload(const Wl& d, int lane, const int32_t* __restrict__ idx,
                                     const float* __restrict__ val, const int32_t* __restrict__ rowid, const G& x,
                                     float* __restrict__ y, double* __restrict__ partial, int32_t sl = 0) {
@@ -541,10 +557,75 @@ __device__ __attribute__((always_inline)) inline void run_workload(const Wl& d, 
     else
       cm_rows<1, 8, S>(d, lane, idx, val, rowid, x, y, sl);
   } else if (layout != kCM && aligned && ((d.w_pad & 63) == 0 || (d.w_pad == 32 && layout == kRM))) {
-    rm_wide<S>(d, lane, idx, val, rowid, x, y, partial, layout == kChunk, sl);
+    rm_wide<S, SAME>(d, lane, idx, val, rowid, x, y, partial, layout == kChunk, sl);
   } else {
-    generic_wl<S>(d, lane, layout, idx, val, rowid, x, y, partial, sl);
+    generic_wl<S, SAME>(d, lane, layout, idx, val, rowid, x, y, partial, sl);
   }
+}
+
+// What a one-tile product writes besides its workloads' rows: the rows
+// without entries, and the split rows' sums, each by the wavefront that
+// finishes the row's last chunk (ticket[i] counts split row i's finished
+// chunks and goes back to 0 with the last).
+struct TileRest {
+  const int32_t* empty;
+  int64_t n_empty;
+  const SplitRow* split;
+  const int32_t* slot_split;  // partial slot -> split row
+  uint32_t* ticket;           // null: the caller sums the partial slots
+};
+
+// After a chunk's sum is in its slot: the wavefront of the row's last chunk
+// adds the slots left to right from 0.0 (the bits of sum_slots) and writes the
+// row.  The slots travel by agent-scope accesses, which pass the XCD's L2:
+// the wait makes this wavefront's slot complete there before its ticket is
+// drawn, so the last ticket's wavefront reads every slot.  No fence (an
+// agent-scope release would write back the whole L2) and no wavefront waits
+// for another.
+// (i, sr: the chunk's split row, read before the chunk is summed.)
+template <class X>
+__device__ inline void finish_chunk(int32_t i, const SplitRow& sr, int lane, const X& x, float* __restrict__ y,
+                                    const double* partial, const TileRest& rest) {
+  asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
+  uint32_t t = 0;
+  if (lane == 0) t = __hip_atomic_fetch_add(rest.ticket + i, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+  if (__builtin_amdgcn_readfirstlane(t) + 1 != (uint32_t)sr.n_slots) return;
+  asm volatile("" ::: "memory");
+  double acc = 0.0;
+  for (int32_t q = 0; q < sr.n_slots; q += kWave) {
+    const double v = q + lane < sr.n_slots ? __hip_atomic_load(partial + sr.slot_begin + q + lane, __ATOMIC_RELAXED,
+                                                               __HIP_MEMORY_SCOPE_AGENT)
+                                           : 0.0;
+    const int m = min(kWave, sr.n_slots - q);
+    for (int k = 0; k < m; ++k)
+      acc += __hiloint2double(__builtin_amdgcn_readlane(__double2hiint(v), k),
+                              __builtin_amdgcn_readlane(__double2loint(v), k));
+  }
+  if (lane == 0) {
+    x.addy(y, sr.row, acc);
+    __hip_atomic_store(rest.ticket + i, 0u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+  }
+}
+
+// A workload slice of a one-tile product (or, without tickets, of any tile)
+template <int S, bool VEC, class X>
+__device__ inline void tile_item(const Wl& d, int lane, const int32_t* __restrict__ idx, const float* __restrict__ val,
+                                 const int32_t* __restrict__ rowid, const X& x, float* __restrict__ y,
+                                 double* __restrict__ partial, int32_t sl, const TileRest& rest) {
+  const bool chunk = (d.info & 3) == kChunk && rest.ticket && sl == 0;
+  int32_t i = 0;
+  SplitRow sr{0, 0, 0, 0};
+  if (chunk) {
+    i = rest.slot_split[d.info >> 2];
+    sr = rest.split[i];
+  }
+  run_workload<S, VEC, true>(d, lane, idx, val, rowid, x, y, partial, sl);
+  if (chunk) finish_chunk(i, sr, lane, x, y, partial, rest);
+}
+
+template <class X>
+__device__ inline void write_empty(const TileRest& rest, const X& x, float* __restrict__ y, int64_t i, int64_t step) {
+  for (; i < rest.n_empty; i += step) x.addy(y, rest.empty[i], 0.0);
 }
 
 // p[0] + p[s] + ... + p[(n-1) s], added in that order; 32 loads go out
@@ -618,6 +699,15 @@ __global__ void k_gather_rows(const float* __restrict__ in, const int32_t* __res
   out[t] = in[(int64_t)perm[k] * w + q];
 }
 
+// ... of 4 * w4 floats (16-byte aligned rows), one 16-byte piece per thread
+__global__ void __launch_bounds__(kB) k_gather_rows4(const v4f* __restrict__ in, const int32_t* __restrict__ perm,
+                                                     int64_t n, uint32_t w4, v4f* __restrict__ out) {
+  const int64_t t = (int64_t)blockIdx.x * kB + threadIdx.x;
+  if (t >= n * w4) return;
+  const int64_t k = (w4 & (w4 - 1)) == 0 ? t >> __builtin_ctz(w4) : t / w4;
+  out[t] = in[(int64_t)perm[k] * w4 + (t - k * w4)];
+}
+
 template <int NV>
 __device__ inline void block_sum_store(double (&v)[NV], double* out_base, int64_t stride) {
   __shared__ double sm[NV][kB / kWave];
@@ -636,6 +726,50 @@ __device__ inline void block_sum_store(double (&v)[NV], double* out_base, int64_
       out_base[q * stride] = s;
     }
   }
+}
+
+// Sum of v over the block (the order of block_sum_store), in every thread.
+__device__ inline double block_sum(double v) {
+  __shared__ double sm[kB / kWave];
+  const double s = wave_sum(v);
+  __syncthreads();  // the previous sum's readers are done
+  if (lane_id() == 0) sm[threadIdx.x / kWave] = s;
+  __syncthreads();
+  double t = 0.0;
+  for (int w = 0; w < kB / kWave; ++w) t += sm[w];
+  return t;
+}
+
+// Sum of up to 64 partials by every wavefront that needs it (each lane reads
+// one): a launch of its own for it costs 2-5 us.
+__device__ inline double wave_parts(const double* __restrict__ parts, int np) {
+  return wave_sum(lane_id() < np ? parts[lane_id()] : 0.0);
+}
+
+// A reduction's second half in the same launch: every block gives its partial
+// sum (v, of thread 0), and the block that draws the last ticket may read them
+// all: true in that block.  The partials travel by agent-scope accesses, each
+// complete before its block draws (no fence: an agent-scope release writes
+// back the L2, 18 us where 1024 blocks did it); no block waits for another.
+// The last block sets the ticket back to 0.
+__device__ inline bool last_block(double* parts, double v, uint32_t* ticket) {
+  __shared__ uint32_t last;
+  if (threadIdx.x == 0) {
+    __hip_atomic_store(parts + blockIdx.x, v, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
+    last = __hip_atomic_fetch_add(ticket, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) + 1 == gridDim.x;
+    if (last) __hip_atomic_store(ticket, 0u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+  }
+  __syncthreads();
+  return last != 0;
+}
+
+// Sum of parts[b, e) in a fixed order, in the last block of last_block.
+__device__ inline double sum_parts(const double* parts, int b, int e) {
+  double s = 0.0;
+  for (int i = b + (int)threadIdx.x; i < e; i += kB)
+    s += __hip_atomic_load(parts + i, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+  return block_sum(s);
 }
 
 constexpr int kRedBlocks = 1024;

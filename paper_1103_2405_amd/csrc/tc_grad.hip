@@ -240,17 +240,6 @@ using namespace tc;
 // ---- differentiable RWR (host)
 namespace tc {
 namespace {
-// y := A x in the caller's ids (as tc_spmv)
-void spmv_user(tc_handle* h, const float* x, float* y, hipStream_t st) {
-  gather_rows(x, h->d_cperm, h->n_cols, 1, h->d_xbuf, st);
-  if (h->relabel) {
-    spmv_internal(h, h->d_xbuf, h->d_ybuf, st);
-    gather_rows(h->d_ybuf, h->d_rowmap, h->n_rows, 1, y, st);
-  } else {
-    spmv_internal(h, h->d_xbuf, y, st);
-  }
-}
-
 struct PoolBuf {
   void* p = nullptr;
   hipStream_t st;

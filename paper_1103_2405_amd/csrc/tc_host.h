@@ -38,10 +38,6 @@ void launch_tile(tc_handle* h, void (*kern)(KArgs...), dim3 grid, dim3 block, ui
   HIPC(hipGetLastError());
 }
 
-// LDS staging of tile t's x segment: the width to stage, or 0 (global gathers)
-int64_t lds_tile_width(const tc_handle* h, int t);
-int64_t lds_tile_blocks(const tc_handle* h, int64_t lw);
-
 // Row slices of tile t's workloads (the build option, or the measured rule).
 int32_t tile_slices(const tc_handle* h, int t, int64_t n_wl);
 template <class K>
@@ -61,6 +57,8 @@ void panel_pass(tc_handle* h, const float* x, float* y, hipStream_t st, const Pa
 // tilewise: one launch per tile even for a handle with row panels.
 void spmv_internal(tc_handle* h, const float* x, float* y, hipStream_t st, bool fuse_combine = false,
                    bool skip_zero = false, bool tilewise = false);
+// y := A x in the caller's ids (tc_spmv)
+void spmv_user(tc_handle* h, const float* x, float* y, hipStream_t st);
 // Y := A X for k right-hand sides in internal ids; epi: fused RWR restart.
 // partial_ext: split-row partial sums go there (at least n_slots * pieces * k
 // doubles) instead of the handle's pool buffer, and launches are not timed:
@@ -73,6 +71,35 @@ size_t spmm_partial_doubles(tc_handle* h, int32_t k);
 void gather_rows(const float* in, const int32_t* perm, int64_t n, int32_t w, float* out, hipStream_t st);
 // one double from the device (synchronises the stream)
 double read_f64(const double* d, hipStream_t st);
+// A result that the device hands to the host: its kernels store it to d (and, where
+// the library keeps page-locked blocks, to h, which the host reads after the
+// stream; else it is copied).
+struct HostResult {
+  hipStream_t st;
+  const double* d;
+  HostBlock b;
+  bool queued = false;  // kernels that write h may still run
+  HostResult(const double* dev, hipStream_t s) : st(s), d(dev) {
+    if (host_pool_on()) b = host_take(64, true);
+  }
+  ~HostResult() {
+    if (queued) (void)hipStreamSynchronize(st);
+    if (b.p) host_give(b);
+  }
+  HostResult(const HostResult&) = delete;
+  HostResult& operator=(const HostResult&) = delete;
+  double* h() {  // for a kernel argument
+    if (!b.pinned) return nullptr;
+    queued = true;
+    return (double*)b.p;
+  }
+  double read() {
+    if (!b.pinned) return read_f64(d, st);
+    HIPC(hipStreamSynchronize(st));
+    queued = false;
+    return *(volatile double*)b.p;
+  }
+};
 void need_square(const tc_handle* h, const char* who);
 
 // Runs f, turning errors into a status and the thread's last-error message.

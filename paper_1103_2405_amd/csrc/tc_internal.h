@@ -120,6 +120,7 @@ struct HostBlock {
 };
 HostBlock host_take(size_t bytes, bool pinned);  // throws std::bad_alloc when out of memory
 void host_give(const HostBlock& b);
+bool host_pool_on();  // freed host blocks are kept (TC_POOL)
 size_t host_release_cached();
 
 // n items of a plain type in a reusable host block (contents uninitialised)
@@ -179,10 +180,11 @@ struct tc_handle {
   int32_t* d_rowid = nullptr;
   tc::SplitRow* d_split = nullptr;
   double* d_partial = nullptr;
+  int32_t* d_slot_split = nullptr;  // partial slot -> split row (index into d_split)
+  uint32_t* d_ticket = nullptr;     // [n_split_rows] finished chunks of each split row; 0 between products
   float* d_xbuf = nullptr;          // internal-space x for spmv on user vectors
   float* d_ybuf = nullptr;
   double* d_red = nullptr;          // reduction scratch
-  unsigned long long* d_counters = nullptr;  // per-tile work counters of the persistent pass
   int32_t* d_empty = nullptr;       // internal rows without any entry (zeroed by every product)
   int64_t n_empty = 0;
   // XCD schedule: tile 0 on every XCD, tiles 1..xcd_groups at once, tile g
@@ -197,7 +199,6 @@ struct tc_handle {
   int64_t lds_floats = 0;           // floats of x one workgroup can stage (device limit)
   int64_t lds_cu_bytes = 0;         // LDS bytes per compute unit
   int64_t l2_bytes = 0;             // L2 bytes of one XCD (the L2 a workgroup's gathers see)
-  int32_t* d_half = nullptr;        // HITS: 0/1 half of each internal index (lazily built)
   // row panels: tile g = panel g / n_col_tiles, column tile g % n_col_tiles
   int32_t n_panels = 0, n_col_tiles = 0, panel_rows = 0, panel_waves = 0;
   std::vector<int64_t> panel_begin;  // [n_panels + 1] internal rows

@@ -195,6 +195,8 @@ void host_free_block(const HostBlock& b) {
 }
 }  // namespace
 
+bool host_pool_on() { return pool_enabled(); }
+
 HostBlock host_take(size_t bytes, bool pinned) {
   HostPoolState& P = host_pool();
   if (pool_enabled()) {

@@ -14,43 +14,6 @@ namespace tc {
 
 namespace {
 
-// x of a tile whose whole column range sits in LDS (a tile no wider than the
-// LDS of one workgroup): every gather of the tile is an LDS read.
-struct LdsX {
-  const float* xs;  // LDS copy of x[cb, cb + width)
-  int32_t cb;
-  __device__ float operator()(int32_t i) const { return xs[i - cb]; }
-  __device__ void addy(float* y, int32_t rid, double s) const { addy_first_touch(y, rid, s); }
-};
-
-// Tile pass with the tile's x segment staged in LDS (Section 3.1, Solution 1:
-// the segment of x a tile reads is kept in the nearest memory; on gfx950 that
-// is the 160 KB LDS of a compute unit).  Persistent: each workgroup copies
-// x[cb, cb + lw) into LDS once, then its wavefronts take the work items
-// (workload slices) w = global wavefront id, + total wavefronts, ... until
-// none is left, so every wavefront ends after a bounded number of items.
-constexpr int kLdsB = 1024;  // threads of an LDS-tile workgroup
-template <int S>
-__global__ void __launch_bounds__(kLdsB) k_tile_lds(const Wl* __restrict__ wl, int64_t n_wl,
-                                                    const int32_t* __restrict__ idx, const float* __restrict__ val,
-                                                    const int32_t* __restrict__ rowid, const float* __restrict__ x,
-                                                    int32_t cb, int32_t lw, float* __restrict__ y,
-                                                    double* __restrict__ partial) {
-  extern __shared__ float xs[];
-  const float* xsrc = x + cb;
-  stage_x<kLdsB>(xs, xsrc, lw);
-  __syncthreads();
-  const int lane = lane_id();
-  const int64_t waves = (int64_t)gridDim.x * (kLdsB / kWave);
-  const int64_t items = n_wl * S;
-  const LdsX xg{xs, cb};
-  for (int64_t w = (int64_t)blockIdx.x * (kLdsB / kWave) + __builtin_amdgcn_readfirstlane(threadIdx.x / kWave);
-       w < items; w += waves) {
-    const Wl d = wl[w / S];
-    run_workload<S>(d, lane, idx, val, rowid, xg, y, partial, (int32_t)(w % S));
-  }
-}
-
 // x of a row panel: gathers through the caches; the panel's rows of y sit in
 // LDS (ys[row - base]) and every tile adds its row sums there.  A panel row
 // is in at most one workload of a tile, and tiles are separated by barriers,
@@ -169,7 +132,7 @@ __global__ void __launch_bounds__(NW * kWave) k_panel_spmv(const Wl* __restrict_
     __syncthreads();
   }
   if (PR) {
-    const double dn = *pr.dmass / (double)pr.n, tele = (1.0 - pr.c) / (double)pr.n;
+    const double dn = wave_parts(pr.dparts, pr.nd) / (double)pr.n, tele = (1.0 - pr.c) / (double)pr.n;
     for (int32_t i = threadIdx.x; i < nr; i += NW * kWave) y[r0 + i] = (float)(pr.c * ((double)ys[i] + dn) + tele);
     const int64_t se = pr.psb[p + 1];
     for (int64_t q = pr.psb[p] + threadIdx.x; q < se; q += NW * kWave) pr.yraw[q] = ys[pr.split[q].row - r0];
@@ -224,12 +187,10 @@ __global__ void __launch_bounds__(kB) k_split_combine(const SplitRow* __restrict
     add_to_y(y, s.row, acc);
 }
 
-// Start of a product: zero the rows no tile writes, reset the tile counters.
-__global__ void k_begin_spmv(float* __restrict__ y, const int32_t* __restrict__ empty, int64_t n_empty,
-                             unsigned long long* __restrict__ counters, int32_t nt) {
+// Start of a product of several tiles: zero the rows no tile writes.
+__global__ void k_begin_spmv(float* __restrict__ y, const int32_t* __restrict__ empty, int64_t n_empty) {
   const int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
   if (i < n_empty) y[empty[i]] = 0.0f;
-  if (i < nt) counters[i] = 0ull;
 }
 
 // ---- streaming read (measurement): every 16-byte word of the buffer read
@@ -504,26 +465,6 @@ int32_t tile_slices(const tc_handle* h, int t, int64_t n_wl) {
   return n_wl >= kSliceMinWl && h->tile_wl[t] >= kSliceMinSize ? kSlicesDefault : 1;
 }
 
-// LDS staging of a tile's x segment: the tile must fit the LDS of one
-// workgroup, and carry enough entries for the copy (lw floats into every
-// resident workgroup) to be a small part of its traffic: at least
-// kLdsMinReuse gathers per staged float.  Returns the width to stage, or 0.
-constexpr int64_t kLdsMinReuse = 8;
-int64_t lds_tile_width(const tc_handle* h, int t) {
-  if (!h->lds_tiles || h->lds_floats <= 0) return 0;
-  const int64_t lw = h->tile_col_end[t] - h->tile_col_begin[t];
-  if (lw <= 0 || lw > h->lds_floats) return 0;
-  if (h->lds_tiles == 1 && h->tile_nnz[t] < kLdsMinReuse * lw * lds_tile_blocks(h, lw)) return 0;
-  return lw;
-}
-
-// Resident workgroups of the LDS tile kernel for a segment of lw floats (one
-// grid of them covers the GPU once).
-int64_t lds_tile_blocks(const tc_handle* h, int64_t lw) {
-  const int64_t per_cu = std::max<int64_t>(1, std::min<int64_t>(2, h->lds_cu_bytes / std::max<int64_t>(4 * lw, 1)));
-  return per_cu * h->n_cu;
-}
-
 // Floats of x that the row-panel pass stages in LDS (column tile 0, when it
 // fits behind the panel's rows of y and staging is not turned off), else 0.
 int64_t panel_stage_width(const tc_handle* h) {
@@ -553,7 +494,7 @@ void panel_pass(tc_handle* h, const float* x, float* y, hipStream_t st, const Pa
                        : (h->panel_waves == 4   ? k_panel_spmv<4, false, false>
                           : h->panel_waves == 8 ? k_panel_spmv<8, false, false>
                                                 : k_panel_spmv<16, false, false>));
-  const PanelPr none{0.0, nullptr, 0, nullptr, nullptr, nullptr};
+  const PanelPr none{0.0, nullptr, 0, 0, nullptr, nullptr, nullptr};
   if (lds > 65536) HIPC(hipFuncSetAttribute((const void*)kern, hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds));
   launch_tile(h, kern, dim3((unsigned)h->n_panels), dim3((unsigned)(h->panel_waves * kWave)), lds, st,
               (const Wl*)h->d_wl, (const int64_t*)h->d_tile_wl_begin, (const int64_t*)h->d_panel_ncb,
@@ -575,12 +516,16 @@ void spmv_internal(tc_handle* h, const float* x, float* y, hipStream_t st, bool 
     h->spmv_calls++;
     return;
   }
+  if (one_tile(h)) {  // the product, its zero rows and its split rows in one launch
+    run_tile(h, 0, PlainSpec{x}, y, st, tile_rest(h, !skip_zero));
+    h->spmv_calls++;
+    return;
+  }
   const bool xcd = h->xcd_groups > 0 && h->n_tiles > 1;
   const int64_t nzero = xcd ? h->n_zero0 : h->n_empty;
-  const int64_t nz = std::max<int64_t>(nzero, h->n_tiles);
-  if (nz > 0 && !(skip_zero && !xcd)) {
-    hipLaunchKernelGGL(k_begin_spmv, dim3(nblk(nz, kB)), dim3(kB), 0, st, y,
-                       (const int32_t*)(xcd ? h->d_zero0 : h->d_empty), nzero, h->d_counters, (int32_t)h->n_tiles);
+  if (nzero > 0 && !(skip_zero && !xcd)) {
+    hipLaunchKernelGGL(k_begin_spmv, dim3(nblk(nzero, kB)), dim3(kB), 0, st, y,
+                       (const int32_t*)(xcd ? h->d_zero0 : h->d_empty), nzero);
     HIPC(hipGetLastError());
   }
   if (h->kernel == 1) {  // TILE-COO: tiles in order, each an interval pass and its fix-up
@@ -609,19 +554,7 @@ void spmv_internal(tc_handle* h, const float* x, float* y, hipStream_t st, bool 
   for (int t = 0; t < (xcd ? 1 : h->n_tiles); ++t) {
     const int64_t b = h->tile_wl_begin[t], e = h->tile_wl_begin[t + 1];
     if (e == b) continue;
-    const int32_t S = tile_slices(h, t, e - b);
-    const int64_t lw = lds_tile_width(h, t);
-    if (lw > 0) {
-      auto kern = pick_slices(S, k_tile_lds<1>, k_tile_lds<2>, k_tile_lds<4>, k_tile_lds<8>);
-      if (lw * 4 > 65536) HIPC(hipFuncSetAttribute((const void*)kern, hipFuncAttributeMaxDynamicSharedMemorySize,
-                                                    (int)(lw * 4)));
-      const unsigned grid = (unsigned)std::min<int64_t>(lds_tile_blocks(h, lw), nblk((e - b) * S, kLdsB / kWave));
-      launch_tile(h, kern, dim3(grid), dim3(kLdsB), (uint32_t)(lw * 4), st, (const Wl*)(h->d_wl + b),
-                  (int64_t)(e - b), (const int32_t*)h->d_idx, (const float*)h->d_val, (const int32_t*)h->d_rowid, x,
-                  (int32_t)h->tile_col_begin[t], (int32_t)lw, y, h->d_partial);
-      continue;
-    }
-    run_tile(h, t, PlainSpec{x}, y, st);
+    run_tile(h, t, PlainSpec{x}, y, st, tile_rest(h, false));
   }
   if (xcd) {
     const int32_t G = h->n_tiles - 1;
@@ -648,8 +581,45 @@ void spmv_internal(tc_handle* h, const float* x, float* y, hipStream_t st, bool 
 
 void gather_rows(const float* in, const int32_t* perm, int64_t n, int32_t w, float* out, hipStream_t st) {
   if (n <= 0) return;
+  if (w % 4 == 0 && ((uintptr_t)in | (uintptr_t)out) % 16 == 0) {
+    hipLaunchKernelGGL(k_gather_rows4, dim3(nblk(n * (w / 4), kB)), dim3(kB), 0, st, (const v4f*)in, perm, n,
+                       (uint32_t)(w / 4), (v4f*)out);
+    HIPC(hipGetLastError());
+    return;
+  }
   hipLaunchKernelGGL(k_gather_rows, dim3(nblk(n * w, kB)), dim3(kB), 0, st, in, perm, n, w, out);
   HIPC(hipGetLastError());
+}
+
+// One-tile products in the caller's ids.  Up to kMapNnz entries one launch reads
+// x through cperm and writes y through rowinv: measured back to back, us with
+// x gathered first / with this, 10.3 / 7.9 at 12K entries, 11.5 / 9.3 at 228K,
+// 14.7 / 14.5 at 956K, 13.8 / 16.8 at 1.05M of a uniform matrix, 20.6 / 25.8 at
+// 2M (the map doubles the gathers).  Above it x is gathered first; up to
+// kUserRows rows the tile then writes y through rowinv, above them y is
+// gathered afterwards: rows through rowinv / y gathered 14.7 / 16.7 at 2^16
+// rows, 20.6 / 21.5 at 2^18, 18.5 / 18.7 at 2^19, 78.5 / 74.0 at 2^20 (the
+// dependent load at every row's end), 465 / 411 at 2^22.
+constexpr int64_t kMapNnz = (int64_t)1 << 19;
+constexpr int64_t kUserRows = (int64_t)1 << 18;
+
+// y := A x in the caller's ids
+void spmv_user(tc_handle* h, const float* x, float* y, hipStream_t st) {
+  if (one_tile(h) && h->nnz <= kMapNnz && hot_width(h, 0, h->n_wl) == 0) {
+    run_tile(h, 0, UserSpec<true>{x, h->d_cperm, h->d_rowinv}, y, st, tile_rest(h, true));
+    h->spmv_calls++;
+    return;
+  }
+  gather_rows(x, h->d_cperm, h->n_cols, 1, h->d_xbuf, st);
+  if (!h->relabel) {
+    spmv_internal(h, h->d_xbuf, y, st);
+  } else if (one_tile(h) && h->n_rows <= kUserRows) {
+    run_tile(h, 0, UserSpec<false>{h->d_xbuf, nullptr, h->d_rowinv}, y, st, tile_rest(h, true));
+    h->spmv_calls++;
+  } else {
+    spmv_internal(h, h->d_xbuf, h->d_ybuf, st);
+    gather_rows(h->d_ybuf, h->d_rowmap, h->n_rows, 1, y, st);
+  }
 }
 
 double read_f64(const double* d, hipStream_t st) {
@@ -693,13 +663,7 @@ extern "C" tc_status tc_spmv(const tc_handle* hc, const float* x, float* y, tc_s
     if ((const void*)x == (const void*)y && hc->n_rows > 0) throw Err{TC_EINVAL, "x and y must not alias"};
     tc_handle* h = const_cast<tc_handle*>(hc);
     hipStream_t st = (hipStream_t)stream;
-    gather_rows(x, h->d_cperm, h->n_cols, 1, h->d_xbuf, st);
-    if (h->relabel) {
-      spmv_internal(h, h->d_xbuf, h->d_ybuf, st);
-      gather_rows(h->d_ybuf, h->d_rowmap, h->n_rows, 1, y, st);
-    } else {
-      spmv_internal(h, h->d_xbuf, y, st);
-    }
+    spmv_user(h, x, y, st);
     return TC_OK;
   });
 }

@@ -13,21 +13,25 @@ namespace {
 
 // What a kernel is given to make a writer from: the product itself, ...
 struct PlainSpec {
+  static constexpr bool kMapped = false;  // x is in internal ids
   const float* x;
   using X = GlobalX;
   __device__ X make() const { return X{x}; }
 };
-// ... the PageRank update (d = *dmass, the dangling mass of x), ...
+// ... the PageRank update (the dangling mass of x in nd <= 64 partial sums), ...
 struct PrSpec {
+  static constexpr bool kMapped = false;
   const float* x;
   double c;
-  const double* dmass;
+  const double* dparts;
+  int32_t nd;
   int64_t n;
   using X = PrX;
-  __device__ X make() const { return X{x, c, *dmass / (double)n, (1.0 - c) / (double)n}; }
+  __device__ X make() const { return X{x, c, wave_parts(dparts, nd) / (double)n, (1.0 - c) / (double)n}; }
 };
 // ... or the restart of a one-query RWR (seed: an internal id on the device).
 struct RwrSpec {
+  static constexpr bool kMapped = false;
   const float* x;
   double c;
   const int32_t* seed;
@@ -35,23 +39,50 @@ struct RwrSpec {
   __device__ X make() const { return X{x, c, *seed}; }
 };
 
-// S wavefronts per workload of the tile (row slices; grid = workloads * S / 4).
+// ... and the product in the caller's ids: row r goes to y[rowinv[r]]; x in
+// internal ids, or (MAP) in the caller's, through cperm.
+template <bool MAP>
+struct UserSpec {
+  static constexpr bool kMapped = MAP;
+  const float* x;
+  const int32_t* cperm;
+  const int32_t* rowinv;
+  struct X {
+    const float* __restrict__ x;
+    const int32_t* __restrict__ cperm;
+    const int32_t* __restrict__ rowinv;
+    __device__ float operator()(int32_t i) const { return MAP ? x[cperm[i]] : x[i]; }
+    __device__ void addy(float* y, int32_t rid, double s) const { y[rowinv[rid & ~kAddFlag]] = (float)s; }
+  };
+  __device__ X make() const { return X{x, cperm, rowinv}; }
+};
+
+// S wavefronts per workload of the tile (row slices): wl_blocks blocks of
+// them, then blocks for the rows without entries.
+constexpr int kEmptyPer = 4;  // rows without entries per thread
 template <int S, class Spec>
-__global__ void __launch_bounds__(kB) k_tile(const Wl* __restrict__ wl, int64_t n_wl, const int32_t* __restrict__ idx,
-                                             const float* __restrict__ val, const int32_t* __restrict__ rowid,
-                                             Spec spec, float* __restrict__ y, double* __restrict__ partial) {
+__global__ void __launch_bounds__(kB) k_tile(const Wl* __restrict__ wl, int64_t n_wl, uint32_t wl_blocks,
+                                             const int32_t* __restrict__ idx, const float* __restrict__ val,
+                                             const int32_t* __restrict__ rowid, Spec spec, float* __restrict__ y,
+                                             double* __restrict__ partial, TileRest rest) {
   const int lane = lane_id();
+  if (blockIdx.x >= wl_blocks) {
+    write_empty(rest, spec.make(), y, (int64_t)(blockIdx.x - wl_blocks) * kB + threadIdx.x,
+                (int64_t)(gridDim.x - wl_blocks) * kB);
+    return;
+  }
   const int64_t w = (int64_t)blockIdx.x * kWpb + __builtin_amdgcn_readfirstlane(threadIdx.x / kWave);
   if (w >= n_wl * S) return;
   const Wl d = wl[w / S];
-  run_workload<S>(d, lane, idx, val, rowid, spec.make(), y, partial, (int32_t)(w % S));
+  tile_item<S, false>(d, lane, idx, val, rowid, spec.make(), y, partial, (int32_t)(w % S), rest);
 }
 
 // x with its first `hot` columns from cb on in LDS and the others gathered
 // through the caches.  Both reads run on every lane without a branch: a lane
 // whose column is staged gives its buffer load an offset past the buffer,
 // which returns 0 and makes no request, and the others read LDS word 0.
-template <class X>
+// ALL: every column of the tile is staged.
+template <class X, bool ALL>
 struct HotX {
   X b;
   const float* xs;
@@ -59,6 +90,7 @@ struct HotX {
   __amdgpu_buffer_rsrc_t r;  // x, limited to its 4 n_cols bytes
   __device__ float operator()(int32_t i) const {
     const uint32_t k = (uint32_t)(i - cb);
+    if constexpr (ALL) return xs[k];
     const bool in = k < (uint32_t)hot;
     const float l = xs[in ? k : 0];
     const float g = __builtin_bit_cast(
@@ -82,21 +114,22 @@ struct HotX {
 // 408 -> 370; uniform 2^20 x 16 117 -> 113.  What is left on the first: 10.6M
 // L2 read requests (23.5M before) at 130 G/s, and a tenth between the XCDs.
 constexpr int kHotB = 1024;
-template <int S, class Spec>
+template <int S, bool ALL, class Spec>
 __global__ void __launch_bounds__(kHotB) k_tile_hot(const Wl* __restrict__ wl, uint32_t n_wl,
                                                     const int32_t* __restrict__ idx, const float* __restrict__ val,
                                                     const int32_t* __restrict__ rowid, Spec spec, int32_t n_cols,
                                                     int32_t cb, int32_t hot, float* __restrict__ y,
-                                                    double* __restrict__ partial) {
+                                                    double* __restrict__ partial, TileRest rest) {
   extern __shared__ float xs[];  // the staged columns, then the item counter
   uint32_t* ctr = (uint32_t*)(xs + hot);
   if (threadIdx.x == 0) *ctr = 0;
   stage_x<kHotB>(xs, spec.x + cb, hot);
   __syncthreads();
   const int lane = lane_id();
-  const HotX<typename Spec::X> xg{
+  const HotX<typename Spec::X, ALL> xg{
       spec.make(), xs, cb, hot,
       __builtin_amdgcn_make_buffer_rsrc((void*)spec.x, (short)0, n_cols * 4, 0x00020000)};
+  write_empty(rest, xg, y, (int64_t)blockIdx.x * kHotB + threadIdx.x, (int64_t)gridDim.x * kHotB);
   const uint32_t items = n_wl * S, G = gridDim.x;
   auto take = [&]() -> uint32_t {
     uint32_t k = 0;
@@ -109,7 +142,7 @@ __global__ void __launch_bounds__(kHotB) k_tile_hot(const Wl* __restrict__ wl, u
   for (;;) {  // the next item and its descriptor are read while the current one runs
     const uint32_t wn = take();
     const Wl dn = wl[(wn < items ? wn : w) % n_wl];
-    run_workload<S, true>(d, lane, idx, val, rowid, xg, y, partial, (int32_t)(w / n_wl));
+    tile_item<S, true>(d, lane, idx, val, rowid, xg, y, partial, (int32_t)(w / n_wl), rest);
     if (wn >= items) break;
     d = dn;
     w = wn;
@@ -121,37 +154,56 @@ __global__ void __launch_bounds__(kHotB) k_tile_hot(const Wl* __restrict__ wl, u
 // wavefronts pay: measured k_tile / k_tile_hot over R-MAT, Chung-Lu and
 // uniform matrices of 2^12-2^20 columns, 0.71-1.02 up to 2.1M entries,
 // 1.01-1.24 on power-law and 0.96-0.98 on uniform ones at 3-4.2M, 0.99-1.67
-// from 6M on.  The build option lds_stage = 1 stages every tile, -1 none.  x
-// must fit the buffer load's 32-bit offsets.
+// from 6M on; a tile that is staged whole also with 8 entries per float staged
+// in every compute unit.  The build option lds_stage = 1 stages every tile, -1
+// none.  x must fit the buffer load's 32-bit offsets.
 constexpr int64_t kHotMinNnz = (int64_t)3 << 20;
+constexpr int64_t kHotMinReuse = 8;
 inline int64_t hot_width(const tc_handle* h, int t, int64_t items) {
   if (!h->lds_tiles || h->n_cols >= kBufMaxFloats || items >= ((int64_t)1 << 31)) return 0;
-  if (h->lds_tiles == 1 && h->tile_nnz[t] < kHotMinNnz) return 0;
   const int64_t room = h->lds_floats - 64;  // and the counter
-  return std::max<int64_t>(0, std::min(room, h->tile_col_end[t] - h->tile_col_begin[t]));
+  const int64_t width = h->tile_col_end[t] - h->tile_col_begin[t];
+  if (h->lds_tiles == 1 && h->tile_nnz[t] < kHotMinNnz &&
+      !(width <= room && h->tile_nnz[t] >= kHotMinReuse * width * h->n_cu))
+    return 0;
+  return std::max<int64_t>(0, std::min(room, width));
 }
 
-// y's rows of tile t through the writer of `sp` (split rows' chunks to the
-// partial slots).
+// The rest of a one-tile product of the composite kernel (empty: its rows
+// without entries too), or none where other launches write it.
+inline bool one_tile(const tc_handle* h) { return h->n_tiles == 1 && h->n_panels == 0 && h->kernel == 0; }
+inline TileRest tile_rest(const tc_handle* h, bool empty) {
+  if (!one_tile(h)) return TileRest{nullptr, 0, nullptr, nullptr, nullptr};
+  return TileRest{h->d_empty, empty ? h->n_empty : 0, h->d_split, h->d_slot_split, h->d_ticket};
+}
+
+// y's rows of tile t, and the rest, through the writer of `sp`.
 template <class Spec>
-void run_tile(tc_handle* h, int t, const Spec& sp, float* y, hipStream_t st) {
+void run_tile(tc_handle* h, int t, const Spec& sp, float* y, hipStream_t st, const TileRest& rest) {
   const int64_t b = h->tile_wl_begin[t], n = h->tile_wl_begin[t + 1] - b;
-  if (n == 0) return;
+  if (n == 0 && rest.n_empty == 0) return;
   const int32_t S = tile_slices(h, t, n);
-  const int64_t hot = hot_width(h, t, n * S);
-  if (hot > 0) {
-    auto kern = pick_slices(S, k_tile_hot<1, Spec>, k_tile_hot<2, Spec>, k_tile_hot<4, Spec>, k_tile_hot<8, Spec>);
-    const uint32_t lds = (uint32_t)(4 * (hot + 1));
-    if (lds > 65536) HIPC(hipFuncSetAttribute((const void*)kern, hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds));
-    const unsigned grid = (unsigned)std::min<int64_t>(h->n_cu, nblk(n * S, kHotB / kWave));
-    launch_tile(h, kern, dim3(grid), dim3(kHotB), lds, st, (const Wl*)(h->d_wl + b), (uint32_t)n,
-                (const int32_t*)h->d_idx, (const float*)h->d_val, (const int32_t*)h->d_rowid, sp, (int32_t)h->n_cols,
-                (int32_t)h->tile_col_begin[t], (int32_t)hot, y, h->d_partial);
-    return;
+  if constexpr (!Spec::kMapped) {  // staging takes x in internal ids
+    const int64_t hot = n > 0 ? hot_width(h, t, n * S) : 0;
+    if (hot > 0) {
+      auto kern = hot == h->tile_col_end[t] - h->tile_col_begin[t]
+                      ? pick_slices(S, k_tile_hot<1, true, Spec>, k_tile_hot<2, true, Spec>, k_tile_hot<4, true, Spec>,
+                                    k_tile_hot<8, true, Spec>)
+                      : pick_slices(S, k_tile_hot<1, false, Spec>, k_tile_hot<2, false, Spec>,
+                                    k_tile_hot<4, false, Spec>, k_tile_hot<8, false, Spec>);
+      const uint32_t lds = (uint32_t)(4 * (hot + 1));
+      if (lds > 65536) HIPC(hipFuncSetAttribute((const void*)kern, hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds));
+      const unsigned grid = (unsigned)std::min<int64_t>(h->n_cu, nblk(n * S, kHotB / kWave));
+      launch_tile(h, kern, dim3(grid), dim3(kHotB), lds, st, (const Wl*)(h->d_wl + b), (uint32_t)n,
+                  (const int32_t*)h->d_idx, (const float*)h->d_val, (const int32_t*)h->d_rowid, sp, (int32_t)h->n_cols,
+                  (int32_t)h->tile_col_begin[t], (int32_t)hot, y, h->d_partial, rest);
+      return;
+    }
   }
-  launch_tile(h, pick_slices(S, k_tile<1, Spec>, k_tile<2, Spec>, k_tile<4, Spec>, k_tile<8, Spec>),
-              dim3(nblk(n * S, kWpb)), dim3(kB), 0, st, (const Wl*)(h->d_wl + b), n, (const int32_t*)h->d_idx,
-              (const float*)h->d_val, (const int32_t*)h->d_rowid, sp, y, h->d_partial);
+  const unsigned wb = nblk(n * S, kWpb), eb = nblk(rest.n_empty, kB * kEmptyPer);
+  launch_tile(h, pick_slices(S, k_tile<1, Spec>, k_tile<2, Spec>, k_tile<4, Spec>, k_tile<8, Spec>), dim3(wb + eb),
+              dim3(kB), 0, st, (const Wl*)(h->d_wl + b), n, wb, (const int32_t*)h->d_idx, (const float*)h->d_val,
+              (const int32_t*)h->d_rowid, sp, y, h->d_partial, rest);
 }
 
 }  // namespace

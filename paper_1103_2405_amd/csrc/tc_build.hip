@@ -26,6 +26,7 @@
 #include <cstring>
 #include <numeric>
 
+#include "tc_expand.h"
 #include "tc_prims.h"
 
 namespace tc {
@@ -330,33 +331,10 @@ __global__ void k_strided(const int32_t* __restrict__ a, int64_t stride, int64_t
   if (t < cnt) out[t] = a[t * stride];
 }
 
-// Row id of every entry: lanes write their own short rows, the whole
-// wavefront writes each long row.
 // out[i] = a[i * stride] for i < n
 __global__ void k_strided64(const int64_t* __restrict__ a, int64_t stride, int64_t n, int64_t* __restrict__ out) {
   const int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
   if (i < n) out[i] = a[i * stride];
-}
-
-__global__ void k_expand_rows(const int64_t* __restrict__ rp, int64_t n_rows, int32_t* __restrict__ row_of) {
-  const int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-  const int lane = lane_id();
-  int64_t a = 0, b = 0;
-  if (i < n_rows) {
-    a = rp[i];
-    b = rp[i + 1];
-  }
-  const bool longrow = (b - a) > kWave;
-  if (!longrow)
-    for (int64_t k = a; k < b; ++k) row_of[k] = (int32_t)i;
-  uint64_t m = __ballot(longrow);
-  while (m) {
-    const int src = __ffsll((unsigned long long)m) - 1;
-    m &= m - 1;
-    const int64_t aa = __shfl(a, src, kWave), bb = __shfl(b, src, kWave);
-    const int32_t r = (int32_t)__shfl((int64_t)i, src, kWave);
-    for (int64_t k = aa + lane; k < bb; k += kWave) row_of[k] = r;
-  }
 }
 
 __global__ void k_icol(const int32_t* __restrict__ col, const int32_t* __restrict__ cpos, int64_t nnz,
@@ -1160,7 +1138,7 @@ void transpose(const tc_csr* A, int64_t* rpT, int32_t* colT, float* valT, int32_
   HIPX(hipMemcpyAsync(rpT + n_cols, &total, sizeof(int64_t), hipMemcpyHostToDevice, st));
   if (nnz > 0) {
     int32_t* row_of = tmp.get<int32_t>(nnz);
-    hipLaunchKernelGGL(k_expand_rows, dim3(nblk(n_rows, kB)), dim3(kB), 0, st, A->row_ptr, n_rows, row_of);
+    rows_of(A->row_ptr, n_rows, nnz, row_of, st);
     uint32_t* k0 = tmp.get<uint32_t>(nnz);
     uint32_t* k1 = tmp.get<uint32_t>(nnz);
     int32_t* v0 = tmp.get<int32_t>(nnz);
@@ -1691,7 +1669,7 @@ void build(const tc_csr* A, const tc_build_opts* o, hipStream_t st, tc_handle* h
       excl_scan_async<int32_t, int64_t>(ilen, n_rows, iptr, bs, nsb, st);
       HIPX(hipMemcpyAsync(iptr + n_rows, bs + nsb, sizeof(int64_t), hipMemcpyDeviceToDevice, st));
       int32_t* irow = tmp.get<int32_t>(nnz);
-      hipLaunchKernelGGL(k_expand_rows, dim3(nblk(n_rows, kB)), dim3(kB), 0, st, (const int64_t*)iptr, n_rows, irow);
+      rows_of(iptr, n_rows, nnz, irow, st);
       HIPX(hipGetLastError());
       row_of = tmp.get<int32_t>(nnz);
       pval = tmp.get<float>(nnz);
@@ -1722,7 +1700,7 @@ void build(const tc_csr* A, const tc_build_opts* o, hipStream_t st, tc_handle* h
     } else {
       if (!row_of) {
         row_of = tmp.get<int32_t>(nnz);
-        hipLaunchKernelGGL(k_expand_rows, dim3(nblk(n_rows, kB)), dim3(kB), 0, st, A->row_ptr, n_rows, row_of);
+        rows_of(A->row_ptr, n_rows, nnz, row_of, st);
         HIPX(hipGetLastError());
       }
       // LSD passes over 8-bit digits of the tile id; buffers alternate between
@@ -2190,7 +2168,7 @@ void build(const tc_csr* A, const tc_build_opts* o, hipStream_t st, tc_handle* h
     const int32_t* rows = b_row;
     if (!rows) {  // one tile: entries in CSR order
       int32_t* r = tmp.get<int32_t>(nnz);
-      hipLaunchKernelGGL(k_expand_rows, dim3(nblk(n_rows, kB)), dim3(kB), 0, st, A->row_ptr, n_rows, r);
+      rows_of(A->row_ptr, n_rows, nnz, r, st);
       HIPX(hipGetLastError());
       rows = r;
     }

@@ -5,7 +5,8 @@
 #include <cmath>
 #include <vector>
 
-#include "tc_host.h"
+#include "tc_expand.h"
+#include "tc_tile.h"
 
 namespace tc {
 
@@ -47,12 +48,15 @@ __global__ void k_edge_values(const float* __restrict__ feats, const int32_t* __
   if (e < nnz) val[e] = (float)(edge_w(feats + e * nf, theta, nf, nullptr) / S[col[e]]);
 }
 
-// Column sums over A^T's CSR: one wavefront per kColLanes-column group, a
-// group of kColLanes lanes per column, and a column of more than kColLong
-// entries by the whole wavefront (with more loads in flight).  Every lane
-// loads (a lane past the column's end at the column's first entry) and adds
-// only its own entries.  The per-entry passes that need a column's sum are
-// flat passes over the entries (the column of entry q: rowT[q]).
+// Column sums over A^T's CSR: groups of kColLanes lanes take one column each,
+// and the columns of more than kColLong entries go to a list whose columns
+// take a block each (hubs sit next to each other, so a wavefront that sums
+// those it meets is left with most of a graph's entries: S and cs of R-MAT 2^18
+// symmetrised, 7.6M entries, 72 and 145 us that way, 50 and 86 so).  Every
+// lane loads (a
+// lane past the column's end at the column's first entry) and adds only its
+// own entries.  The per-entry passes that need a column's sum are flat passes
+// over the entries (the column of entry q: rowT[q]).
 constexpr int kColLanes = 8;
 constexpr int kColLong = 512;
 constexpr int kGradBlocks = 1024;
@@ -84,9 +88,15 @@ __device__ inline double seg_part(int64_t a, int64_t b, int gl, F f) {
   return s;
 }
 
-// out[j] = post(j, sum over column j's entries q of f(q))
+// Columns of more than kColLong entries: how many, and which.
+struct LongCols {
+  uint32_t* count;  // zero before the pass
+  int32_t* list;
+};
+
+// out[j] = post(j, sum over column j's entries q of f(q)), short columns
 template <class F, class P>
-__device__ inline void col_sums(const int64_t* __restrict__ rpT, int64_t n_cols, F f, P post,
+__device__ inline void col_sums(const int64_t* __restrict__ rpT, int64_t n_cols, F f, P post, const LongCols& lc,
                                 double* __restrict__ out) {
   const int lane = lane_id(), gl = lane % kColLanes;
   const int64_t cg = (int64_t)blockIdx.x * kWpb + __builtin_amdgcn_readfirstlane(threadIdx.x / kWave);
@@ -100,21 +110,35 @@ __device__ inline void col_sums(const int64_t* __restrict__ rpT, int64_t n_cols,
   }
   const bool lng = b - a > kColLong;
   const double s = group_sum8(lng || j >= n_cols ? 0.0 : seg_part<kColLanes, 4>(a, b, gl, f));
-  if (!lng && j < n_cols && gl == 0) out[j] = post(j, s);
-  for (uint64_t m = __ballot(lng && gl == 0); m; m &= m - 1) {
-    const int src = __ffsll((unsigned long long)m) - 1;
-    const int64_t jj = j0 + src / kColLanes;
-    const int64_t aa = __shfl(a, src, kWave), bb = __shfl(b, src, kWave);
-    const double t = wave_sum(seg_part<kWave, 16>(aa, bb, lane, f));
-    if (lane == 0) out[jj] = post(jj, t);
+  if (gl != 0 || j >= n_cols) return;
+  if (lng)
+    lc.list[atomicAdd(lc.count, 1u)] = (int32_t)j;  // in any order: each has a sum of its own
+  else
+    out[j] = post(j, s);
+}
+
+// ... and the long ones
+template <class F, class P>
+__device__ inline void col_sums_long(const int64_t* __restrict__ rpT, F f, P post, const LongCols& lc,
+                                     double* __restrict__ out) {
+  const uint32_t n = *lc.count;
+  for (uint32_t i = blockIdx.x; i < n; i += gridDim.x) {
+    const int32_t j = lc.list[i];
+    const double s = block_sum(seg_part<kB, 8>(rpT[j], rpT[j + 1], threadIdx.x, f));
+    if (threadIdx.x == 0) out[j] = post(j, s);
   }
 }
 
 // S_j = sum of w over column j
+template <bool LONG>
 __global__ void __launch_bounds__(kB) k_col_norm(const int64_t* __restrict__ rpT, int64_t n_cols,
-                                                 const double* __restrict__ wT, double* __restrict__ S) {
-  col_sums(
-      rpT, n_cols, [&](int64_t q) { return wT[q]; }, [](int64_t, double s) { return s; }, S);
+                                                 const double* __restrict__ wT, LongCols lc, double* __restrict__ S) {
+  auto f = [&](int64_t q) { return wT[q]; };
+  auto post = [](int64_t, double s) { return s; };
+  if constexpr (LONG)
+    col_sums_long(rpT, f, post, lc, S);
+  else
+    col_sums(rpT, n_cols, f, post, lc, S);
 }
 
 // W^T's values fl32(w / S_j)
@@ -130,58 +154,85 @@ __global__ void k_rwr_step(const float* __restrict__ y, float* __restrict__ r, i
   if (i < n) r[i] = (float)(c * (double)y[i] + (i == seed ? 1.0 - c : 0.0));
 }
 
-__global__ void k_scale(const float* __restrict__ y, float* __restrict__ g, int64_t n, double c) {
-  const int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-  if (i < n) g[i] = (float)(c * (double)y[i]);
-}
-
-// G_q += sum over the steps of one checkpoint segment, latest step first, of
-// g^{k+1}_i r^k_j for the entry q = (i, j) of A (row j of A^T, column i of
-// A^T: gidx = A^T's column array, ridx = A^T's row of every entry).  gi and ri
-// hold g^{k+1} and r^k of the segment's m steps k = k0 + t interleaved by node
-// (node i's m values at i * m), so an entry reads its values from one or two
-// cache lines.
-__global__ void k_edge_accum_seg(const int32_t* __restrict__ gidx, const int32_t* __restrict__ ridx, int64_t nnz,
-                                 const float* __restrict__ gi, const float* __restrict__ ri, int32_t m,
-                                 double* __restrict__ G) {
-  const int64_t q = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-  if (q >= nnz) return;
-  const float* gp = gi + (int64_t)gidx[q] * m;
-  const float* rp = ri + (int64_t)ridx[q] * m;
-  double acc = G[q];
-  for (int32_t t = m - 1; t >= 0; --t) acc = fma((double)gp[t], (double)rp[t], acc);
-  G[q] = acc;
-}
-
-// dst[i * m + t] = src[t * n + i]: m vectors of n, interleaved by index
-__global__ void k_interleave(const float* __restrict__ src, int32_t m, int64_t n, float* __restrict__ dst) {
-  const int64_t x = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-  if (x >= n * m) return;
-  dst[x] = src[(x % m) * n + x / m];
-}
-
-
-// row index of every entry: short rows by their thread, long rows (> 64
-// entries) by the whole wavefront in turn
-__global__ void k_rows_of(const int64_t* __restrict__ rp, int64_t n_rows, int32_t* __restrict__ row_of) {
-  const int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
+// Rows for the per-entry sums: row u of dst (ROW floats) holds user id u's
+// value in each of m <= ROW vectors.  inv: internal -> user id of the vectors
+// (null: they are in user ids).  A wavefront reads 64 values of each vector
+// and writes whole rows through LDS.
+template <int ROW>
+__global__ void __launch_bounds__(kB) k_step_rows(const float* __restrict__ src, int32_t m, int64_t n,
+                                                  const int32_t* __restrict__ inv, float* __restrict__ dst) {
+  constexpr int P = ROW + 1, L = ROW / 4, R = kWave / L;  // padded row; lanes per row, rows per store
+  __shared__ float sm[kWpb][kWave * P];
   const int lane = lane_id();
-  int64_t a = 0, b = 0;
-  if (i < n_rows) {
-    a = rp[i];
-    b = rp[i + 1];
+  float* t = sm[threadIdx.x / kWave];
+  const int64_t i0 = ((int64_t)blockIdx.x * kWpb + threadIdx.x / kWave) * kWave;
+  if (i0 >= n) return;
+  const int64_t i = i0 + lane < n ? i0 + lane : i0;
+#pragma unroll 8
+  for (int32_t q = 0; q < m; ++q) t[lane * P + q] = src[(int64_t)q * n + i];
+  for (int32_t q = m; q < ROW; ++q) t[lane * P + q] = 0.0f;
+  __builtin_amdgcn_wave_barrier();
+  const int32_t u = inv ? inv[i] : (int32_t)i;
+#pragma unroll
+  for (int r = 0; r < kWave; r += R) {
+    const int row = r + lane / L, c = 4 * (lane % L);
+    const int64_t ur = __shfl(u, row, kWave);
+    const float* p = t + row * P + c;
+    if (i0 + row < n && c < m) *(v4f*)(dst + ur * ROW + c) = v4f{p[0], p[1], p[2], p[3]};
   }
-  const bool longrow = (b - a) > kWave;
-  if (!longrow)
-    for (int64_t e = a; e < b; ++e) row_of[e] = (int32_t)i;
-  uint64_t m = __ballot(longrow);
-  while (m) {
-    const int src = __ffsll((unsigned long long)m) - 1;
-    m &= m - 1;
-    const int64_t aa = __shfl(a, src, kWave), bb = __shfl(b, src, kWave);
-    const int32_t r = (int32_t)__shfl((int64_t)i, src, kWave);
-    for (int64_t e = aa + lane; e < bb; e += kWave) row_of[e] = r;
+}
+
+// G_q (+)= sum over a batch of m <= ROW steps, latest first, of g^{k+1}_i r^k_j
+// for the entry q = (i, j) of A (row j of A^T, column i of A^T: gidx = A^T's
+// column array, ridx = A^T's row of every entry); the steps' values of i and j
+// are the first m of their rows of gr and rr (k_step_rows).  The random rows,
+// those of i, come through LDS: ROW / 4 lanes read a row (one 128-byte line for
+// ROW = 32) at once, then each lane adds its own entry's steps.  Bound by those
+// lines: 7.6M entries, 30 steps, 118 us (64 G lines/s); a pass per checkpoint
+// segment of 6 read as many lines each time and took 5 x 174.
+template <int ROW, bool FIRST>
+__global__ void __launch_bounds__(kB) k_edge_accum(const int32_t* __restrict__ gidx, const int32_t* __restrict__ ridx,
+                                                   int64_t nnz, const float* __restrict__ gr,
+                                                   const float* __restrict__ rr, int32_t m, double* __restrict__ G) {
+  constexpr int P = ROW + 1, L = ROW / 4, R = kWave / L;
+  __shared__ float sm[kWpb][kWave * P];
+  const int lane = lane_id();
+  float* t = sm[threadIdx.x / kWave];
+  const int64_t q0 = ((int64_t)blockIdx.x * kWpb + threadIdx.x / kWave) * kWave;
+  if (q0 >= nnz) return;
+  const int64_t q = q0 + lane < nnz ? q0 + lane : q0;
+  const int32_t gi = gidx[q];
+  const float* rp = rr + (int64_t)ridx[q] * ROW;
+  double acc = FIRST ? 0.0 : G[q];
+  const int c = 4 * (lane % L);
+  v4f a[L];
+#pragma unroll
+  for (int u = 0; u < L; ++u) {  // R rows per load; pieces past m: the row's first
+    const int32_t row = __shfl(gi, u * R + lane / L, kWave);
+    a[u] = *(const v4f*)(gr + (int64_t)row * ROW + (c < m ? c : 0));
   }
+#pragma unroll
+  for (int u = 0; u < L; ++u) {
+    float* p = t + (u * R + lane / L) * P + c;
+    p[0] = a[u].x, p[1] = a[u].y, p[2] = a[u].z, p[3] = a[u].w;
+  }
+  __builtin_amdgcn_wave_barrier();
+  const float* gp = t + lane * P;
+  int32_t s = 0;
+  for (; s + 4 <= m; s += 4) {
+    const v4f r = *(const v4f*)(rp + s);
+    acc = fma((double)gp[s], (double)r.x, acc);
+    acc = fma((double)gp[s + 1], (double)r.y, acc);
+    acc = fma((double)gp[s + 2], (double)r.z, acc);
+    acc = fma((double)gp[s + 3], (double)r.w, acc);
+  }
+  for (; s < m; ++s) acc = fma((double)gp[s], (double)rp[s], acc);
+  if (q0 + lane < nnz) G[q] = acc;
+}
+
+// a seed's internal id (no seed: -1)
+__global__ void k_set_seed(int32_t* __restrict__ out, const int32_t* __restrict__ map, int32_t seed) {
+  if (threadIdx.x == 0 && blockIdx.x == 0) *out = seed < 0 ? -1 : map[seed];
 }
 
 __global__ void k_onehot(float* __restrict__ r, int64_t n, int32_t seed) {
@@ -191,12 +242,17 @@ __global__ void k_onehot(float* __restrict__ r, int64_t n, int32_t seed) {
 
 // per column j: cs_j = sum over its entries of dL/dW W, with dL/dW = c G and
 // W = w / S_j, taken as (c / S_j) sum G w
+template <bool LONG>
 __global__ void __launch_bounds__(kB) k_col_dot(const int64_t* __restrict__ rpT, int64_t n_cols,
                                                 const double* __restrict__ GT, const double* __restrict__ wT,
-                                                const double* __restrict__ S, double c, double* __restrict__ cs) {
-  col_sums(
-      rpT, n_cols, [&](int64_t q) { return GT[q] * wT[q]; }, [&](int64_t j, double s) { return c / S[j] * s; },
-      cs);
+                                                const double* __restrict__ S, double c, LongCols lc,
+                                                double* __restrict__ cs) {
+  auto f = [&](int64_t q) { return GT[q] * wT[q]; };
+  auto post = [&](int64_t j, double s) { return c / S[j] * s; };
+  if constexpr (LONG)
+    col_sums_long(rpT, f, post, lc, cs);
+  else
+    col_sums(rpT, n_cols, f, post, lc, cs);
 }
 
 // dL/dz = (c G - cs_j) / S_j * sigmoid(z) per entry (column j = rowT[q]);
@@ -252,6 +308,62 @@ struct PoolBuf {
   T* as() const { return (T*)p; }
 };
 
+// the long columns of a pass over nnz entries (their count starts at zero)
+constexpr unsigned kLongBlocks = 1024;
+struct LongList {
+  PoolBuf b;
+  LongCols c;
+  LongList(int64_t nnz, hipStream_t st) : b(256 + sizeof(int32_t) * (size_t)(nnz / kColLong + 1), st) {
+    c = LongCols{b.as<uint32_t>(), (int32_t*)((char*)b.p + 256)};
+    HIPC(hipMemsetAsync(b.p, 0, 4, st));
+  }
+};
+
+// The power steps of W (or W^T) in the order its products work in: internal
+// ids with the update written by the product (one tile), or the caller's ids
+// with a product and an update.
+struct Steps {
+  tc_handle* h;
+  double c;
+  int32_t seed;  // caller's id, -1: none
+  PoolBuf id;    // its internal id (one tile)
+  PoolBuf tmp;   // a product (other formats)
+  bool inner;
+  hipStream_t st;
+  Steps(tc_handle* hh, float cc, int32_t s, hipStream_t q)
+      : h(hh), c((double)cc), seed(s), id(4, q), tmp(one_tile(hh) ? 1 : sizeof(float) * (size_t)hh->n_rows, q),
+        inner(one_tile(hh)), st(q) {
+    if (!inner) return;
+    hipLaunchKernelGGL(k_set_seed, dim3(1), dim3(64), 0, st, id.as<int32_t>(), (const int32_t*)h->d_rowmap, seed);
+    HIPC(hipGetLastError());
+  }
+  // working order -> caller's ids, or null
+  const int32_t* inv() const { return inner ? h->d_rowinv : nullptr; }
+  void copy(const float* v, const int32_t* perm, float* out) const {
+    if (inner)
+      gather_rows(v, perm, h->n_rows, 1, out, st);
+    else if (h->n_rows > 0)
+      HIPC(hipMemcpyAsync(out, v, sizeof(float) * h->n_rows, hipMemcpyDeviceToDevice, st));
+  }
+  void to_user(const float* v, float* out) const { copy(v, h->d_rowmap, out); }
+  void from_user(const float* v, float* out) const { copy(v, h->d_rowinv, out); }
+  // out = fl32(c fl32(A in) + (1 - c) [seed])
+  void step(const float* in, float* out) const {
+    if (inner) {
+      run_tile(h, 0, RwrSpec{in, c, id.as<const int32_t>()}, out, st, tile_rest(h, true));
+      h->spmv_calls++;
+      return;
+    }
+    spmv_user(h, in, tmp.as<float>(), st);
+    hipLaunchKernelGGL(k_rwr_step, dim3(nblk(h->n_rows, kB)), dim3(kB), 0, st, tmp.as<const float>(), out, h->n_rows,
+                       seed, c);
+    HIPC(hipGetLastError());
+  }
+};
+
+// vectors of one batch of the adjoint pass (beyond one segment's, which the caller chose)
+constexpr int64_t kBatchBytes = (int64_t)256 << 20;
+
 int32_t n_checkpoints(int32_t K, int32_t every) { return K <= 0 ? 0 : (K + every - 1) / every; }
 }  // namespace
 }  // namespace tc
@@ -274,13 +386,19 @@ extern "C" tc_status tc_rwr_edge_weights(int64_t n_cols, int64_t nnz, const int3
       HIPC(hipGetLastError());
     }
     if (n_cols > 0) {
-      hipLaunchKernelGGL(k_col_norm, dim3(nblk(nblk(n_cols, kWave / kColLanes), kWpb)), dim3(kB), 0, st, d_rpT,
-                         n_cols, (const double*)d_wT, d_S);
+      LongList lc(nnz, st);
+      hipLaunchKernelGGL(k_col_norm<false>, dim3(nblk(nblk(n_cols, kWave / kColLanes), kWpb)), dim3(kB), 0, st, d_rpT,
+                         n_cols, (const double*)d_wT, lc.c, d_S);
       HIPC(hipGetLastError());
+      if (nnz > kColLong) {
+        hipLaunchKernelGGL(k_col_norm<true>, dim3(kLongBlocks), dim3(kB), 0, st, d_rpT, n_cols, (const double*)d_wT,
+                           lc.c, d_S);
+        HIPC(hipGetLastError());
+      }
     }
     if (nnz > 0) {
       PoolBuf rowT(sizeof(int32_t) * (size_t)nnz, st);
-      hipLaunchKernelGGL(k_rows_of, dim3(nblk(n_cols, kB)), dim3(kB), 0, st, d_rpT, n_cols, rowT.as<int32_t>());
+      rows_of(d_rpT, n_cols, nnz, rowT.as<int32_t>(), st);
       HIPC(hipGetLastError());
       hipLaunchKernelGGL(k_values_T, dim3(nblk(nnz, kB)), dim3(kB), 0, st, rowT.as<const int32_t>(), nnz,
                          (const double*)d_wT, (const double*)d_S, d_valT);
@@ -306,18 +424,18 @@ extern "C" tc_status tc_rwr_iterates(const tc_handle* hc, int32_t seed, float c,
     tc_handle* h = const_cast<tc_handle*>(hc);
     hipStream_t st = (hipStream_t)stream;
     const int64_t n = h->n_rows;
-    PoolBuf y(sizeof(float) * n, st);
+    const Steps W(h, c, seed, st);
+    PoolBuf r0(sizeof(float) * n, st), r1(sizeof(float) * n, st);
+    float *cur = r0.as<float>(), *nxt = r1.as<float>();
     hipLaunchKernelGGL(k_onehot, dim3(nblk(n, kB)), dim3(kB), 0, st, d_rK, n, seed);
     HIPC(hipGetLastError());
+    if (K > 0) W.from_user(d_rK, cur);
     for (int32_t k = 0; k < K; ++k) {
-      if (k % every == 0)
-        HIPC(hipMemcpyAsync(d_ckpt + (int64_t)(k / every) * n, d_rK, sizeof(float) * n, hipMemcpyDeviceToDevice,
-                            st));
-      spmv_user(h, d_rK, y.as<float>(), st);
-      hipLaunchKernelGGL(k_rwr_step, dim3(nblk(n, kB)), dim3(kB), 0, st, y.as<const float>(), d_rK, n, seed,
-                         (double)c);
-      HIPC(hipGetLastError());
+      if (k % every == 0) W.to_user(cur, d_ckpt + (int64_t)(k / every) * n);
+      W.step(cur, nxt);
+      std::swap(cur, nxt);
     }
+    if (K > 0) W.to_user(cur, d_rK);
     return TC_OK;
   });
 }
@@ -339,53 +457,64 @@ extern "C" tc_status tc_rwr_adjoint(const tc_handle* hc, const tc_handle* htc, c
     tc_handle* h = const_cast<tc_handle*>(hc);
     tc_handle* ht = const_cast<tc_handle*>(htc);
     hipStream_t st = (hipStream_t)stream;
+    const Steps W(h, c, seed, st), Wt(ht, c, -1, st);
+    // Steps per pass over the entries: whole segments while they fit a row of 32
+    // and the vectors stay within kBatchBytes; a longer segment goes through
+    // in batches of its own.  The sums run latest step first in any case.
     const int32_t seglen = std::min(every, std::max(K, 1));
-    PoolBuf seg(sizeof(float) * (size_t)n * seglen, st), gseg(sizeof(float) * (size_t)n * seglen, st),
-        segi(sizeof(float) * (size_t)n * seglen, st), gsegi(sizeof(float) * (size_t)n * seglen, st),
-        g(sizeof(float) * n, st), tmp(sizeof(float) * n, st),
+    const int64_t fit = kBatchBytes / (8 * std::max<int64_t>(n, 1));
+    const int32_t cap = (int32_t)std::max<int64_t>(seglen, std::min<int64_t>(std::max(K, 1), std::min<int64_t>(32, fit)));
+    const int32_t row = cap <= 8 ? 8 : 32;
+    const size_t vec = sizeof(float) * (size_t)n, rowb = nnz > 0 ? vec * row : 1;
+    PoolBuf seg(vec * cap, st), gseg(vec * (cap + 1), st), rowr(rowb, st), rowg(rowb, st),
         rows(sizeof(int32_t) * (size_t)std::max<int64_t>(nnz, 1), st);
     if (nnz > 0) {
-      HIPC(hipMemsetAsync(d_G, 0, sizeof(double) * nnz, st));
-      hipLaunchKernelGGL(k_rows_of, dim3(nblk(n, kB)), dim3(kB), 0, st, d_rpT, n, rows.as<int32_t>());
+      rows_of(d_rpT, n, nnz, rows.as<int32_t>(), st);
       HIPC(hipGetLastError());
     }
-    if (n > 0) HIPC(hipMemcpyAsync(g.p, d_gK, sizeof(float) * n, hipMemcpyDeviceToDevice, st));
-    float* S = seg.as<float>();
+    // steps in S and GS, latest first; GS's next slot holds the current g
+    float *S = seg.as<float>(), *GS = gseg.as<float>();
+    Wt.from_user(d_gK, GS);
+    int32_t have = 0;
+    bool first = true;
+    auto flush = [&]() {
+      for (int32_t b = 0; b < have && nnz > 0; b += row) {
+        const int32_t m = std::min(row, have - b);
+        auto put = row == 8 ? k_step_rows<8> : k_step_rows<32>;
+        hipLaunchKernelGGL(put, dim3(nblk(n, kB)), dim3(kB), 0, st, (const float*)(GS + (int64_t)b * n), m, n,
+                           Wt.inv(), rowg.as<float>());
+        HIPC(hipGetLastError());
+        hipLaunchKernelGGL(put, dim3(nblk(n, kB)), dim3(kB), 0, st, (const float*)(S + (int64_t)b * n), m, n, W.inv(),
+                           rowr.as<float>());
+        HIPC(hipGetLastError());
+        auto sum = row == 8 ? (first ? k_edge_accum<8, true> : k_edge_accum<8, false>)
+                            : (first ? k_edge_accum<32, true> : k_edge_accum<32, false>);
+        hipLaunchKernelGGL(sum, dim3(nblk(nnz, kB)), dim3(kB), 0, st, d_colT, rows.as<const int32_t>(), nnz,
+                           rowg.as<const float>(), rowr.as<const float>(), m, d_G);
+        HIPC(hipGetLastError());
+        first = false;
+      }
+    };
     for (int32_t q = n_checkpoints(K, every) - 1; q >= 0; --q) {
-      const int32_t k0 = q * every, k1 = std::min(K, k0 + every);
-      // recompute r^{k0} .. r^{k1-1} from the checkpoint
-      HIPC(hipMemcpyAsync(S, d_ckpt + (int64_t)q * n, sizeof(float) * n, hipMemcpyDeviceToDevice, st));
-      for (int32_t t = 1; t < k1 - k0; ++t) {
-        spmv_user(h, S + (int64_t)(t - 1) * n, tmp.as<float>(), st);
-        hipLaunchKernelGGL(k_rwr_step, dim3(nblk(n, kB)), dim3(kB), 0, st, tmp.as<const float>(), S + (int64_t)t * n,
-                           n, seed, (double)c);
-        HIPC(hipGetLastError());
+      const int32_t k0 = q * every, m = std::min(K, k0 + every) - k0;
+      if (have + m > cap) {
+        flush();
+        HIPC(hipMemcpyAsync(GS, GS + (int64_t)have * n, vec, hipMemcpyDeviceToDevice, st));
+        have = 0;
       }
-      // adjoint vectors g^{k+1} of the segment, latest first, kept for one
-      // pass over the entries (which then reads them per step)
-      float* GS = gseg.as<float>();
-      for (int32_t k = k1 - 1; k >= k0; --k) {
-        if (n > 0)
-          HIPC(hipMemcpyAsync(GS + (int64_t)(k - k0) * n, g.p, sizeof(float) * n, hipMemcpyDeviceToDevice, st));
-        spmv_user(ht, g.as<const float>(), tmp.as<float>(), st);
-        hipLaunchKernelGGL(k_scale, dim3(nblk(n, kB)), dim3(kB), 0, st, tmp.as<const float>(), g.as<float>(), n,
-                           (double)c);
-        HIPC(hipGetLastError());
-      }
-      if (nnz > 0) {
-        const int32_t m = k1 - k0;
-        hipLaunchKernelGGL(k_interleave, dim3(nblk(n * m, kB)), dim3(kB), 0, st, (const float*)GS, m, n,
-                           gsegi.as<float>());
-        HIPC(hipGetLastError());
-        hipLaunchKernelGGL(k_interleave, dim3(nblk(n * m, kB)), dim3(kB), 0, st, (const float*)S, m, n,
-                           segi.as<float>());
-        HIPC(hipGetLastError());
-        hipLaunchKernelGGL(k_edge_accum_seg, dim3(nblk(nnz, kB)), dim3(kB), 0, st, d_colT, rows.as<const int32_t>(),
-                           nnz, gsegi.as<const float>(), segi.as<const float>(), m, d_G);
-        HIPC(hipGetLastError());
-      }
+      // r^k at slot have + (k0 + m - 1 - k), recomputed from the checkpoint, which
+      // is the segment's last slot
+      float* end = S + (int64_t)(have + m - 1) * n;
+      W.from_user(d_ckpt + (int64_t)q * n, end);
+      for (int32_t t = 1; t < m; ++t) W.step(end - (int64_t)(t - 1) * n, end - (int64_t)t * n);
+      // g^{k+1} likewise; its product is g^k (g^0 only where it is asked for)
+      const int32_t steps = q == 0 && !d_g0 ? m - 1 : m;
+      for (int32_t t = 0; t < steps; ++t) Wt.step(GS + (int64_t)(have + t) * n, GS + (int64_t)(have + t + 1) * n);
+      have += m;
     }
-    if (d_g0 && n > 0) HIPC(hipMemcpyAsync(d_g0, g.p, sizeof(float) * n, hipMemcpyDeviceToDevice, st));
+    flush();
+    if (nnz > 0 && first) HIPC(hipMemsetAsync(d_G, 0, sizeof(double) * nnz, st));
+    if (d_g0) Wt.to_user(GS + (int64_t)have * n, d_g0);
     return TC_OK;
   });
 }
@@ -403,10 +532,16 @@ extern "C" tc_status tc_rwr_theta_grad(int64_t n_cols, int64_t nnz, const int64_
         rowT(sizeof(int32_t) * (size_t)std::max<int64_t>(nnz, 1), st),
         parts(sizeof(double) * (size_t)kGradBlocks * nf, st), out(sizeof(double) * nf, st);
     if (n_cols > 0) {
-      hipLaunchKernelGGL(k_col_dot, dim3(nblk(nblk(n_cols, kWave / kColLanes), kWpb)), dim3(kB), 0, st, d_rpT,
-                         n_cols, d_G, d_wT, d_S, (double)c, cs.as<double>());
+      LongList lc(nnz, st);
+      hipLaunchKernelGGL(k_col_dot<false>, dim3(nblk(nblk(n_cols, kWave / kColLanes), kWpb)), dim3(kB), 0, st, d_rpT,
+                         n_cols, d_G, d_wT, d_S, (double)c, lc.c, cs.as<double>());
       HIPC(hipGetLastError());
-      hipLaunchKernelGGL(k_rows_of, dim3(nblk(n_cols, kB)), dim3(kB), 0, st, d_rpT, n_cols, rowT.as<int32_t>());
+      if (nnz > kColLong) {
+        hipLaunchKernelGGL(k_col_dot<true>, dim3(kLongBlocks), dim3(kB), 0, st, d_rpT, n_cols, d_G, d_wT, d_S,
+                           (double)c, lc.c, cs.as<double>());
+        HIPC(hipGetLastError());
+      }
+      if (nnz > 0) rows_of(d_rpT, n_cols, nnz, rowT.as<int32_t>(), st);
       HIPC(hipGetLastError());
     }
     hipLaunchKernelGGL(k_theta_grad, dim3(kGradBlocks), dim3(kB), 0, st, rowT.as<const int32_t>(), nnz, nf, d_featsT,

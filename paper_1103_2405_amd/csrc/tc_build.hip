@@ -59,60 +59,107 @@ struct Fail {
       throw Fail{TC_EHIP, std::string(#call) + ": " + hipGetErrorString(e_)};        \
   } while (0)
 
-// Temporary device buffers of one build, freed when the build ends.
 // Temporary device arrays of one build, taken from the library's pool on the
-// build stream and handed back (stream-ordered) when released or at the end.
+// build stream.  A released one serves the build's later requests; all go back
+// at the end, or the released ones when memory runs out.
 struct Tmp {
   hipStream_t st;
-  std::vector<void*> bufs;
+  struct Buf {
+    void* p;
+    size_t bytes;
+    bool used;
+  };
+  std::vector<Buf> bufs;
   explicit Tmp(hipStream_t s) : st(s) {}
+  // A released block serves the build's next request that it fits, without an
+  // event: everything runs on one stream.
   template <class T>
   T* get(int64_t n) {
-    size_t bytes = (size_t)std::max<int64_t>(n, 1) * sizeof(T);
-    void* p = pool_alloc(bytes, st);
+    const size_t bytes = (size_t)std::max<int64_t>(n, 1) * sizeof(T);
+    Buf* best = nullptr;
+    for (Buf& b : bufs)
+      if (!b.used && b.bytes >= bytes && b.bytes <= bytes + bytes / 4 + ((size_t)2 << 20) &&
+          (!best || b.bytes < best->bytes))
+        best = &b;
+    if (best) {
+      best->used = true;
+      return (T*)best->p;
+    }
+    void* p = alloc(bytes, st);
     if (!p) throw Fail{TC_ENOMEM, "device allocation of " + std::to_string(bytes) + " bytes failed"};
-    bufs.push_back(p);
+    bufs.push_back(Buf{p, bytes, true});
     return (T*)p;
   }
   void release(void* p) {
-    for (auto& b : bufs)
-      if (b == p) {
-        pool_free(b, st, false);
-        b = nullptr;
-      }
+    for (Buf& b : bufs)
+      if (b.p == p) b.used = false;
   }
+  // from the pool, which gets the released blocks back where it has nothing left
+  void* alloc(size_t bytes, hipStream_t s) {
+    void* p = pool_alloc(bytes, s);
+    if (p) return p;
+    give_back();
+    return pool_alloc(bytes, s);
+  }
+  void give_back() {
+    for (const Buf& b : bufs)
+      if (!b.used) pool_free(b.p, st, false);
+    bufs.erase(std::remove_if(bufs.begin(), bufs.end(), [](const Buf& b) { return !b.used; }), bufs.end());
+  }
+  // the blocks go back to the pool idle: an event per block costs the host
+  // more than this wait, which a build ends with anyway
   ~Tmp() {
-    for (void* p : bufs)
-      if (p) pool_free(p, st, false);
+    const bool idle = hipStreamSynchronize(st) == hipSuccess;
+    for (const Buf& b : bufs) pool_free(b.p, st, idle);
   }
 };
 
 template <class T>
-T* hold(tc_handle* h, int64_t n) {
+T* hold(tc_handle* h, Tmp& tmp, int64_t n) {
   size_t bytes = (size_t)std::max<int64_t>(n, 1) * sizeof(T);
   void* p = nullptr;
   if (h->alloc) {
     p = h->alloc(bytes, h->alloc_ctx);
     if (!p) throw Fail{TC_ENOMEM, "allocator callback returned NULL for " + std::to_string(bytes) + " bytes"};
-  } else if (!(p = pool_alloc(bytes, h->stream))) {
+  } else if (!(p = tmp.alloc(bytes, h->stream))) {
     throw Fail{TC_ENOMEM, "device allocation of " + std::to_string(bytes) + " bytes failed"};
   }
   h->owned.push_back(p);
   return (T*)p;
 }
 
+// n items of T in a page-locked host block from the library's host pool, for
+// the life of one build step.  The block goes back to the pool when its
+// holder ends, after the build stream has finished every copy that may still
+// read or write it.
+template <class T>
+struct Staged {
+  HostBlock b;
+  hipStream_t st;
+  T* p;
+  Staged(int64_t n, hipStream_t s)
+      : b(host_take(sizeof(T) * (size_t)std::max<int64_t>(n, 1), true)), st(s), p((T*)b.p) {}
+  ~Staged() {
+    (void)hipStreamSynchronize(st);
+    host_give(b);
+  }
+  Staged(const Staged&) = delete;
+  Staged& operator=(const Staged&) = delete;
+  T& operator[](int64_t i) { return p[i]; }
+};
+
 // ----------------------------------------------------------------- kernels
-__global__ void k_validate_rows(const int64_t* __restrict__ rp, int64_t n_rows, int64_t nnz, int* flag) {
+// (bad: set to 1 by any thread that finds an error)
+__global__ void k_validate_rows(const int64_t* __restrict__ rp, int64_t n_rows, int64_t nnz, int64_t* bad) {
   int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
   if (i > n_rows) return;
   int64_t a = rp[i];
-  bool bad = (i == 0 && a != 0) || (i == n_rows && a != nnz) || (i < n_rows && rp[i + 1] < a);
-  if (bad) atomicOr(flag, 1);
+  if ((i == 0 && a != 0) || (i == n_rows && a != nnz) || (i < n_rows && rp[i + 1] < a)) *bad = 1;
 }
 
-__global__ void k_validate_cols(const int32_t* __restrict__ col, int64_t nnz, int64_t n_cols, int* flag) {
+__global__ void k_validate_cols(const int32_t* __restrict__ col, int64_t nnz, int64_t n_cols, int64_t* bad) {
   int64_t k = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-  if (k < nnz && (col[k] < 0 || (int64_t)col[k] >= n_cols)) atomicOr(flag, 2);
+  if (k < nnz && (col[k] < 0 || (int64_t)col[k] >= n_cols)) *bad = 1;
 }
 
 __global__ void k_fill_i32(int32_t* a, int64_t n, int32_t v) {
@@ -202,54 +249,193 @@ __global__ void __launch_bounds__(256) k_col_count_hot(const int32_t* __restrict
     if (key[i] != -1 && cnt[i]) atomicAdd(&clen[key[i]], cnt[i]);
 }
 
-// a1, bucketed: a counting-sort pass groups the column ids by their high
-// bits, then each block counts one window of kCntWin columns of one bucket
-// (a slice of its ids) in LDS and writes the window's lengths: plain stores
-// when the bucket is one slice, atomics on the few buckets that need several.
-constexpr int kCntWin = 32768;  // 128 KB of LDS counters
+// a1, bucketed: the ids are grouped by their high bits (k_cols_scan counts and
+// validates them, k_cols_place groups them; their order inside a group does
+// not matter, so nothing ranks equal keys), then each block counts a slice of
+// one group in LDS, one window of columns at a time, and writes the window's
+// lengths: plain stores when the group is one slice, else atomics.  Everything
+// is planned on the device.  The passes move 16 bytes an entry but are bound by
+// their LDS adds: 118M entries 0.24 + 0.36 + 0.19 ms (2.4 TB/s), with the plan
+// 0.90, where a stable counting-sort pass, a host wait for the plan and slices
+// of 2^20 ids took 1.42; 15.6M entries 0.13 instead of 0.36 ms.
+constexpr int kColBuckets = 256;
+constexpr int kColBlock = 1024;
+constexpr int kColPer = 8;
+constexpr int64_t kColStep = (int64_t)kColBlock * kColPer;
+constexpr int kCntWin = 32768;  // most LDS counters of a block (128 KB)
 constexpr int kCntBlock = 1024;
-constexpr int64_t kCntSlice = 1 << 20;
+constexpr int64_t kCntSlice = 1 << 17;
 
-struct ColBucketOp {
-  const int32_t* cin;
-  int32_t* cout;
-  int shift;
-  using Item = int32_t;
-  __device__ Item load(int64_t k) const { return cin[k]; }
-  __device__ uint32_t bucket_of(Item c) const { return (uint32_t)c >> shift; }
-  __device__ void store(int64_t p, Item c) const { cout[p] = c; }
-};
+// block blk of nblk takes the ids [blk * per, ...), per a multiple of kColStep
+__global__ void __launch_bounds__(kColBlock) k_cols_scan(const int32_t* __restrict__ col, int64_t nnz, int64_t n_cols,
+                                                         int shift, int64_t per, int32_t* __restrict__ hist,
+                                                         int64_t* bad) {
+  __shared__ int32_t cnt[kColBlock / kWave][kColBuckets];  // one set per wavefront
+  int32_t* mine = cnt[threadIdx.x / kWave];
+  for (int i = threadIdx.x; i < (kColBlock / kWave) * kColBuckets; i += kColBlock) (&cnt[0][0])[i] = 0;
+  __syncthreads();
+  const int64_t b = (int64_t)blockIdx.x * per, e = min(nnz, b + per);
+  bool wrong = false;
+  for (int64_t k0 = b + threadIdx.x; k0 < e; k0 += kColStep) {
+    int32_t c[kColPer];
+#pragma unroll
+    for (int u = 0; u < kColPer; ++u) c[u] = col[k0 + u * kColBlock < e ? k0 + u * kColBlock : k0];
+#pragma unroll
+    for (int u = 0; u < kColPer; ++u) {
+      if (k0 + u * kColBlock >= e) continue;
+      if ((uint64_t)(uint32_t)c[u] < (uint64_t)n_cols)
+        atomicAdd(&mine[(uint32_t)c[u] >> shift], 1);
+      else
+        wrong = true;
+    }
+  }
+  if (wrong) *bad = 1;
+  __syncthreads();
+  for (int i = threadIdx.x; i < kColBuckets; i += kColBlock) {
+    int32_t t = 0;
+    for (int w = 0; w < kColBlock / kWave; ++w) t += cnt[w][i];
+    hist[(int64_t)i * gridDim.x + blockIdx.x] = t;
+  }
+}
+
+// the same blocks: ids to their groups (ids out of range, which end the
+// build, are left out), by way of LDS so that a group's ids leave together
+__global__ void __launch_bounds__(kColBlock) k_cols_place(const int32_t* __restrict__ col, int64_t nnz, int64_t n_cols,
+                                                          int shift, int64_t per, const int64_t* __restrict__ offs,
+                                                          int32_t* __restrict__ out) {
+  __shared__ int32_t li[kColStep];
+  __shared__ int32_t cnt[kColBuckets], start[kColBuckets];
+  __shared__ int64_t gpos[kColBuckets];
+  __shared__ int32_t wsum[kColBuckets / kWave];
+  const int tid = threadIdx.x;
+  if (tid < kColBuckets) {
+    gpos[tid] = offs[(int64_t)tid * gridDim.x + blockIdx.x];
+    cnt[tid] = 0;
+  }
+  __syncthreads();
+  const int64_t b = (int64_t)blockIdx.x * per, e = min(nnz, b + per);
+  for (int64_t k0 = b; k0 < e; k0 += kColStep) {
+    int32_t c[kColPer], rank[kColPer];
+#pragma unroll
+    for (int u = 0; u < kColPer; ++u) {
+      const int64_t k = k0 + u * kColBlock + tid;
+      c[u] = col[k < e ? k : k0];
+      if (k >= e || (uint64_t)(uint32_t)c[u] >= (uint64_t)n_cols) c[u] = -1;
+    }
+#pragma unroll
+    for (int u = 0; u < kColPer; ++u) rank[u] = c[u] >= 0 ? atomicAdd(&cnt[(uint32_t)c[u] >> shift], 1) : 0;
+    __syncthreads();
+    int32_t mine = 0, inc = 0;
+    if (tid < kColBuckets) {
+      mine = cnt[tid];
+      inc = wave_incl_scan(mine);
+      if (lane_id() == kWave - 1) wsum[tid / kWave] = inc;
+    }
+    __syncthreads();
+    if (tid < kColBuckets) {
+      for (int w = 0; w < tid / kWave; ++w) inc += wsum[w];
+      start[tid] = inc - mine;
+    }
+    __syncthreads();
+#pragma unroll
+    for (int u = 0; u < kColPer; ++u)
+      if (c[u] >= 0) li[start[(uint32_t)c[u] >> shift] + rank[u]] = c[u];
+    __syncthreads();
+    const int32_t total = start[kColBuckets - 1] + cnt[kColBuckets - 1];
+    for (int32_t i = tid; i < total; i += kColBlock) {
+      const int32_t v = li[i];
+      const uint32_t q = (uint32_t)v >> shift;
+      out[gpos[q] + (i - start[q])] = v;
+    }
+    __syncthreads();
+    if (tid < kColBuckets) {
+      gpos[tid] += cnt[tid];
+      cnt[tid] = 0;
+    }
+    __syncthreads();
+  }
+}
 
 struct CntTask {
-  int64_t begin, end;  // slice of the bucketed ids
+  int64_t begin, end;  // slice of the grouped ids
   int32_t base;        // first column of the window
   int32_t atomic;      // several slices share the window
 };
 
-__global__ void __launch_bounds__(kCntBlock) k_col_count_lds(const int32_t* __restrict__ bcol,
-                                                             const CntTask* __restrict__ tasks, int64_t n_cols,
-                                                             int32_t* __restrict__ clen) {
-  extern __shared__ int32_t cnt_lds[];
-  const CntTask t = tasks[blockIdx.x];
-  for (int i = threadIdx.x; i < kCntWin; i += kCntBlock) cnt_lds[i] = 0;
+// The counting tasks: group g's ids (from offs[g * nblk] to the next group's, in
+// all *total) cut into slices of kCntSlice, one task per slice and window;
+// *n_tasks = their number.
+__global__ void __launch_bounds__(kColBuckets) k_cnt_tasks(const int64_t* __restrict__ offs, int64_t nblk,
+                                                           const int64_t* __restrict__ total, int shift, int64_t win,
+                                                           int64_t n_cols, CntTask* __restrict__ tasks,
+                                                           int32_t* __restrict__ n_tasks) {
+  __shared__ int32_t wsum[kColBuckets / kWave];
+  __shared__ int32_t end[kColBuckets], slices[kColBuckets];
+  __shared__ int64_t from[kColBuckets + 1];
+  const int g = threadIdx.x;
+  from[g] = offs[(int64_t)g * nblk];
+  if (g == 0) from[kColBuckets] = *total;
   __syncthreads();
-  int64_t k = t.begin + threadIdx.x;
-  for (; k + 7 * kCntBlock < t.end; k += 8 * kCntBlock) {  // eight loads in flight
+  const int64_t base = (int64_t)g << shift;
+  const int32_t ns = (int32_t)((from[g + 1] - from[g] + kCntSlice - 1) / kCntSlice);
+  const int32_t nw = base < n_cols ? (int32_t)((min<int64_t>((int64_t)1 << shift, n_cols - base) + win - 1) / win) : 0;
+  int32_t inc = wave_incl_scan(ns * nw);
+  if (lane_id() == kWave - 1) wsum[g / kWave] = inc;
+  __syncthreads();
+  for (int w = 0; w < g / kWave; ++w) inc += wsum[w];
+  end[g] = inc;
+  slices[g] = ns;
+  __syncthreads();
+  const int32_t n = end[kColBuckets - 1];
+  if (g == 0) *n_tasks = n;
+  for (int32_t t = g; t < n; t += kColBuckets) {
+    int lo = 0, hi = kColBuckets - 1;  // the group whose tasks hold t
+    while (lo < hi) {
+      const int mid = (lo + hi) / 2;
+      if (end[mid] > t)
+        hi = mid;
+      else
+        lo = mid + 1;
+    }
+    const int32_t r = t - (lo > 0 ? end[lo - 1] : 0), w = r / slices[lo], j = r % slices[lo];
+    const int64_t b = from[lo] + (int64_t)j * kCntSlice;
+    tasks[t] = CntTask{b, min(from[lo + 1], b + kCntSlice), (int32_t)(((int64_t)lo << shift) + w * win),
+                       slices[lo] > 1 ? 1 : 0};
+  }
+}
+
+__global__ void __launch_bounds__(kCntBlock) k_col_count_lds(const int32_t* __restrict__ bcol,
+                                                             const CntTask* __restrict__ tasks,
+                                                             const int32_t* __restrict__ n_tasks, int32_t win,
+                                                             int64_t n_cols, int32_t* __restrict__ clen) {
+  extern __shared__ int32_t cnt_lds[];
+  if ((int32_t)blockIdx.x >= *n_tasks) return;
+  const CntTask t = tasks[blockIdx.x];
+  for (int i = threadIdx.x; i < win; i += kCntBlock) cnt_lds[i] = 0;
+  __syncthreads();
+  const int lane = lane_id();
+  for (int64_t k0 = t.begin + threadIdx.x; k0 < t.end; k0 += 8 * kCntBlock) {  // eight loads in flight
     int32_t v[8];
 #pragma unroll
-    for (int u = 0; u < 8; ++u) v[u] = bcol[k + u * kCntBlock];
+    for (int u = 0; u < 8; ++u) v[u] = bcol[k0 + u * kCntBlock < t.end ? k0 + u * kCntBlock : k0];
 #pragma unroll
     for (int u = 0; u < 8; ++u) {
       const uint32_t c = (uint32_t)(v[u] - t.base);
-      if (c < (uint32_t)kCntWin) atomicAdd(&cnt_lds[c], 1);
+      const bool in = k0 + u * kCntBlock < t.end && c < (uint32_t)win;
+      // the first lane's column by one add for all lanes that hold it: a hub
+      // column fills a slice, and adds of 64 lanes to one counter take turns
+      const uint64_t ins = __ballot(in);
+      if (!ins) continue;
+      const int first = (int)__builtin_ctzll(ins);
+      const uint64_t same = __ballot(in && c == (uint32_t)__builtin_amdgcn_readlane((int)c, first));
+      if (lane == first)
+        atomicAdd(&cnt_lds[c], (int32_t)__popcll(same));
+      else if (in && !((same >> lane) & 1))
+        atomicAdd(&cnt_lds[c], 1);
     }
   }
-  for (; k < t.end; k += kCntBlock) {
-    const uint32_t c = (uint32_t)(bcol[k] - t.base);
-    if (c < (uint32_t)kCntWin) atomicAdd(&cnt_lds[c], 1);
-  }
   __syncthreads();
-  const int64_t lim = min<int64_t>(kCntWin, n_cols - t.base);
+  const int64_t lim = min<int64_t>(win, n_cols - t.base);
   for (int i = threadIdx.x; i < lim; i += kCntBlock) {
     const int32_t v = cnt_lds[i];
     if (t.atomic) {
@@ -260,26 +446,44 @@ __global__ void __launch_bounds__(kCntBlock) k_col_count_lds(const int32_t* __re
   }
 }
 
-// maximum of a non-negative array: grid-stride, one atomic per block
-__global__ void __launch_bounds__(256) k_max_i32(const int32_t* __restrict__ a, int64_t n, int32_t* out) {
+// maximum of a non-negative array, one per block (the host takes theirs)
+constexpr int kMaxBlocks = 256;
+__global__ void __launch_bounds__(256) k_max_i32(const int32_t* __restrict__ a, int64_t n, int64_t* __restrict__ out) {
   __shared__ int32_t wm[256 / kWave];
   int32_t v = 0;
-  for (int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; i < n; i += (int64_t)gridDim.x * blockDim.x)
-    v = max(v, a[i]);
+  const int64_t step = (int64_t)gridDim.x * 256;
+  for (int64_t i0 = (int64_t)blockIdx.x * 256 + threadIdx.x; i0 < n; i0 += 8 * step) {
+    int32_t t[8];
+#pragma unroll
+    for (int u = 0; u < 8; ++u) t[u] = a[i0 + u * step < n ? i0 + u * step : i0];
+#pragma unroll
+    for (int u = 0; u < 8; ++u) v = max(v, t[u]);
+  }
   for (int d = 32; d > 0; d >>= 1) v = max(v, __shfl_xor(v, d, kWave));
   if (lane_id() == 0) wm[threadIdx.x / kWave] = v;
   __syncthreads();
   if (threadIdx.x == 0) {
     for (int w = 1; w < 256 / kWave; ++w) v = max(v, wm[w]);
-    atomicMax(out, v);
+    out[blockIdx.x] = v;
   }
 }
 
-__global__ void k_count_eq(const int32_t* __restrict__ a, int64_t n, int32_t v, unsigned long long* out) {
-  int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-  bool e = i < n && a[i] == v;
-  uint64_t m = __ballot(e);
-  if (lane_id() == 0 && m) atomicAdd(out, (unsigned long long)__popcll(m));
+// first i in [0, n) with a[i] == 0, a non-increasing (n: none), by one wavefront
+__global__ void k_first_zero(const int32_t* __restrict__ a, int64_t n, int64_t* __restrict__ out) {
+  const int lane = lane_id();
+  int64_t lo = 0, hi = n;  // the answer is in [lo, hi]
+  while (lo < hi) {
+    const int64_t step = (hi - lo + kWave - 1) / kWave, q = lo + (int64_t)lane * step;
+    const uint64_t m = __ballot(q < hi && a[q < hi ? q : lo] > 0);
+    if (!(m & 1)) {
+      hi = lo;
+    } else {
+      const int64_t at = lo + (int64_t)(63 - __builtin_clzll(m)) * step;
+      hi = at + step < hi ? at + step : hi;
+      lo = at + 1;
+    }
+  }
+  if (lane == 0) *out = lo;
 }
 
 __global__ void k_desc_keys(const int32_t* __restrict__ len, int64_t n, int32_t maxv, uint32_t* __restrict__ keys,
@@ -503,25 +707,35 @@ __global__ void __launch_bounds__(kScanBlock) k_seghead_emit(const int32_t* __re
 
 // a5 with one tile: internal row i is a segment if its original row is non-empty
 __global__ void k_rowseg_flags(const int64_t* __restrict__ rp, const int32_t* __restrict__ rowinv, int64_t n_rows,
-                               int32_t* __restrict__ flags) {
+                               int32_t* __restrict__ flags, int32_t* __restrict__ len) {
   const int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
   if (i >= n_rows) return;
   const int32_t o = rowinv[i];
-  flags[i] = rp[o + 1] > rp[o];
+  const int32_t l = (int32_t)(rp[o + 1] - rp[o]);
+  flags[i] = l > 0;
+  len[i] = l;
 }
 
-__global__ void k_rowseg_emit(const int32_t* __restrict__ flags, const int32_t* __restrict__ pos,
+// ... its segment, or its place in the list of rows without entries, and its
+// first tile (0x7fffffff: only chunks, or nothing, write it); row panels
+// (first == null) make those two themselves
+__global__ void k_rowseg_emit(const int32_t* __restrict__ pos, const int32_t* __restrict__ len,
                               const int64_t* __restrict__ rp, const int32_t* __restrict__ rowinv, int64_t n_rows,
-                              int32_t* __restrict__ seg_start, int32_t* __restrict__ seg_row,
-                              int32_t* __restrict__ seg_tile, int32_t* __restrict__ seg_len) {
+                              int64_t split, int32_t* __restrict__ seg_start, int32_t* __restrict__ seg_row,
+                              int32_t* __restrict__ seg_tile, int32_t* __restrict__ seg_len,
+                              int32_t* __restrict__ empty, int32_t* __restrict__ first) {
   const int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-  if (i >= n_rows || !flags[i]) return;
-  const int32_t s = pos[i], o = rowinv[i];
-  const int64_t a = rp[o];
-  seg_start[s] = (int32_t)a;
+  if (i >= n_rows) return;
+  const int32_t s = pos[i], l = len[i];
+  if (first) first[i] = l > 0 && !(split > 0 && (int64_t)l > split) ? 0 : 0x7fffffff;
+  if (l == 0) {
+    if (first) empty[i - s] = (int32_t)i;
+    return;
+  }
+  seg_start[s] = (int32_t)rp[rowinv[i]];
   seg_row[s] = (int32_t)i;
   seg_tile[s] = 0;
-  seg_len[s] = (int32_t)(rp[o + 1] - a);
+  seg_len[s] = l;
 }
 
 __global__ void k_seg_len(const int32_t* __restrict__ seg_start, int64_t nseg, int64_t nnz, int32_t* __restrict__ seg_len) {
@@ -699,8 +913,10 @@ __global__ void __launch_bounds__(kB) k_pack(const Wl* __restrict__ dwl, const P
                                              const int32_t* __restrict__ rows_len,
                                              const int32_t* __restrict__ rows_sorted,
                                              const int32_t* __restrict__ b_icol, const float* __restrict__ b_val,
-                                             const int32_t* __restrict__ first, int32_t* __restrict__ idx,
-                                             float* __restrict__ val, int32_t* __restrict__ rowid, float pad) {
+                                             const int32_t* __restrict__ cpos, const int32_t* __restrict__ first,
+                                             int32_t* __restrict__ idx, float* __restrict__ val,
+                                             int32_t* __restrict__ rowid, float pad) {
+  // (cpos: b_icol holds the caller's columns, mapped here)
   // kPackSlices wavefronts per workload, slice sl taking every kPackSlices-th
   // row (RM), row block of 64 (CM) or 64-entry block (chunk).  Four positions'
   // loads go out together, then their stores: a position past its row's L
@@ -729,6 +945,11 @@ __global__ void __launch_bounds__(kB) k_pack(const Wl* __restrict__ dwl, const P
   const int64_t area = (int64_t)wd.w_pad * wd.h_pad;
   d.extra = (camping && area % 512 == 0) ? 64 : 0;  // the camping pad after the rectangle
   const int64_t off = d.data_off;
+  auto map4 = [&](int32_t (&t)[4]) {
+    if (!cpos) return;
+#pragma unroll
+    for (int u = 0; u < 4; ++u) t[u] = cpos[t[u]];
+  };
   if (x.chunk_off >= 0) {
     const int32_t s = d.row_begin;
     const int64_t st = (int64_t)srt_start[s] + x.chunk_off;
@@ -743,6 +964,7 @@ __global__ void __launch_bounds__(kB) k_pack(const Wl* __restrict__ dwl, const P
         ti[u] = b_icol[q];
         tv[u] = b_val[q];
       }
+      map4(ti);
 #pragma unroll
       for (int u = 0; u < 4; ++u) {
         const int64_t c = c0 + u * step;
@@ -768,6 +990,7 @@ __global__ void __launch_bounds__(kB) k_pack(const Wl* __restrict__ dwl, const P
           ti[u] = b_icol[q];
           tv[u] = b_val[q];
         }
+        map4(ti);
 #pragma unroll
         for (int u = 0; u < 4; ++u) {
           const int64_t c = c0 + u * kWave;
@@ -802,6 +1025,7 @@ __global__ void __launch_bounds__(kB) k_pack(const Wl* __restrict__ dwl, const P
           ti[u] = b_icol[q];
           tv[u] = b_val[q];
         }
+        map4(ti);
 #pragma unroll
         for (int u = 0; u < 4; ++u) {
           const int32_t c = c0 + u;
@@ -907,33 +1131,60 @@ struct TileOp {
 };
 
 // ------------------------------------------------------------ host helpers
+
+// Whole numbers that the build's kernels hand to the host: they store to
+// dev(i), which is page-locked host memory where the library has it, and
+// wait() makes what the stream has queued readable through [].
+struct Scalars {
+  static constexpr int64_t n = 2048;
+  Staged<int64_t> box;
+  int64_t* d = nullptr;
+  hipStream_t st;
+  int64_t used = 0;
+  Scalars(Tmp& tmp, hipStream_t s) : box(n, s), st(s) {
+    if (!box.b.pinned) d = tmp.get<int64_t>(n);
+    std::memset(box.p, 0, sizeof(int64_t) * n);
+    if (d) HIPX(hipMemcpyAsync(d, box.p, sizeof(int64_t) * n, hipMemcpyHostToDevice, st));
+  }
+  int64_t take(int64_t count = 1) {
+    if (used + count > n) throw Fail{TC_EINVAL, "internal error: too many build scalars"};
+    used += count;
+    return used - count;
+  }
+  int64_t* dev(int64_t i) { return (d ? d : box.p) + i; }
+  void wait() {
+    if (d) HIPX(hipMemcpyAsync(box.p, d, sizeof(int64_t) * n, hipMemcpyDeviceToHost, st));
+    HIPX(hipStreamSynchronize(st));
+  }
+  int64_t operator[](int64_t i) const { return ((volatile const int64_t*)box.p)[i]; }
+};
+
+// total (device-visible, may be null) receives the sum
 template <typename In, typename Out>
-void excl_scan_async(const In* in, int64_t n, Out* out, int64_t* bs, int64_t nb, hipStream_t st) {
-  if (n > 0) {
-    hipLaunchKernelGGL((k_scan_reduce<In>), dim3((unsigned)nb), dim3(kScanBlock), 0, st, in, n, bs);
+void excl_scan_async(const In* in, int64_t n, Out* out, int64_t* total, Tmp& tmp, hipStream_t st) {
+  if (n <= kSmallScan) {
+    hipLaunchKernelGGL((k_scan_small<In, Out>), dim3(1), dim3(kSmallBlock), 0, st, in, n, out, total);
     HIPX(hipGetLastError());
-  } else {
-    HIPX(hipMemsetAsync(bs, 0, sizeof(int64_t), st));
+    return;
   }
-  hipLaunchKernelGGL(k_scan_blocks, dim3(1), dim3(kScanBlock), 0, st, bs, nb, bs + nb);
+  const int64_t nb = (n + kScanTile - 1) / kScanTile;
+  int64_t* bs = tmp.get<int64_t>(nb);
+  hipLaunchKernelGGL((k_scan_reduce<In>), dim3((unsigned)nb), dim3(kScanBlock), 0, st, in, n, bs);
   HIPX(hipGetLastError());
-  if (n > 0) {
-    hipLaunchKernelGGL((k_scan_down<In, Out>), dim3((unsigned)nb), dim3(kScanBlock), 0, st, in, n, bs, out);
-    HIPX(hipGetLastError());
-  }
+  hipLaunchKernelGGL(k_scan_blocks, dim3(1), dim3(kScanBlock), 0, st, bs, nb, total);
+  HIPX(hipGetLastError());
+  hipLaunchKernelGGL((k_scan_down<In, Out>), dim3((unsigned)nb), dim3(kScanBlock), 0, st, in, n, bs, out);
+  HIPX(hipGetLastError());
+  tmp.release(bs);
 }
 
 // exclusive scan; returns the total (which waits for the stream)
 template <typename In, typename Out>
-int64_t excl_scan(const In* in, int64_t n, Out* out, Tmp& tmp, hipStream_t st) {
-  const int64_t nb = std::max<int64_t>(1, (n + kScanTile - 1) / kScanTile);
-  int64_t* bs = tmp.get<int64_t>(nb + 1);
-  excl_scan_async(in, n, out, bs, nb, st);
-  int64_t total = 0;
-  HIPX(hipMemcpyAsync(&total, bs + nb, sizeof(int64_t), hipMemcpyDeviceToHost, st));
-  HIPX(hipStreamSynchronize(st));
-  tmp.release(bs);
-  return total;
+int64_t excl_scan(const In* in, int64_t n, Out* out, Scalars& sc, Tmp& tmp, hipStream_t st) {
+  const int64_t at = sc.take();
+  excl_scan_async(in, n, out, sc.dev(at), tmp, st);
+  sc.wait();
+  return sc[at];
 }
 
 // One stable counting-sort pass over `nbits` bits of the key (stream
@@ -970,14 +1221,12 @@ void cs_pass(const Op& op, int64_t n, int nbits, Tmp& tmp, hipStream_t st, int32
   const int64_t nh = (int64_t)nbuckets * nchunks;
   int32_t* hist = pre_hist ? pre_hist : tmp.get<int32_t>(nh);
   int64_t* offs = tmp.get<int64_t>(nh);
-  const int64_t nsb = std::max<int64_t>(1, (nh + kScanTile - 1) / kScanTile);
-  int64_t* bs = tmp.get<int64_t>(nsb + 1);
   if (!pre_hist) {
     hipLaunchKernelGGL((k_cs_hist<Op>), dim3(grid), dim3(kCsBlock), kCsWaves * nbuckets * sizeof(int32_t), st, op,
                        n, nbuckets, chunk, nchunks, hist);
     HIPX(hipGetLastError());
   }
-  excl_scan_async<int32_t, int64_t>(hist, nh, offs, bs, nsb, st);
+  excl_scan_async<int32_t, int64_t>(hist, nh, offs, nullptr, tmp, st);
   const size_t stage = (size_t)kCsWaves * ((size_t)chunk * sizeof(Item) + 16 * (size_t)nbuckets);
   HIPX(hipFuncSetAttribute((const void*)k_cs_scatter_staged<Op>, hipFuncAttributeMaxDynamicSharedMemorySize,
                            (int)stage));
@@ -986,24 +1235,33 @@ void cs_pass(const Op& op, int64_t n, int nbits, Tmp& tmp, hipStream_t st, int32
   HIPX(hipGetLastError());
   if (!pre_hist) tmp.release(hist);
   tmp.release(offs);
-  tmp.release(bs);
 }
 
-int32_t dev_max(const int32_t* a, int64_t n, Tmp& tmp, hipStream_t st) {
-  int32_t* d = tmp.get<int32_t>(1);
-  HIPX(hipMemsetAsync(d, 0, sizeof(int32_t), st));
-  if (n > 0) hipLaunchKernelGGL(k_max_i32, dim3((unsigned)std::min<int64_t>(1024, nblk(n, kB))), dim3(kB), 0, st, a, n, d);
-  HIPX(hipGetLastError());
-  int32_t v = 0;
-  HIPX(hipMemcpyAsync(&v, d, sizeof(int32_t), hipMemcpyDeviceToHost, st));
-  HIPX(hipStreamSynchronize(st));
-  tmp.release(d);
-  return v;
+// the maximum of a (non-negative), readable at the returned place after a wait
+struct MaxOf {
+  int64_t at = 0;
+  int blocks = 0;
+  int32_t read(const Scalars& sc) const {
+    int64_t v = 0;
+    for (int b = 0; b < blocks; ++b) v = std::max<int64_t>(v, sc[at + b]);
+    return (int32_t)v;
+  }
+};
+MaxOf max_async(const int32_t* a, int64_t n, Scalars& sc, hipStream_t st) {
+  MaxOf m;
+  m.blocks = (int)std::min<int64_t>(kMaxBlocks, nblk(n, 8 * 256));
+  m.at = sc.take(m.blocks);
+  if (m.blocks > 0) {
+    hipLaunchKernelGGL(k_max_i32, dim3((unsigned)m.blocks), dim3(256), 0, st, a, n, sc.dev(m.at));
+    HIPX(hipGetLastError());
+  }
+  return m;
 }
 
 // a1 for small inputs and very wide matrices: global atomics, with the
 // hottest columns (found from a 1/64 sample) counted in a per-block LDS table.
-void col_count_atomic(const int32_t* col_idx, int64_t nnz, int64_t n_cols, int32_t* clen, Tmp& tmp, hipStream_t st) {
+void col_count_atomic(const int32_t* col_idx, int64_t nnz, int64_t n_cols, int32_t* clen, Scalars& sc, Tmp& tmp,
+                      hipStream_t st) {
   int32_t n_hot = 0;
   int32_t* hot = nullptr;
   if (nnz >= (int64_t)kSampleStep * 1024) {
@@ -1027,7 +1285,7 @@ void col_count_atomic(const int32_t* col_idx, int64_t nnz, int64_t n_cols, int32
       hipLaunchKernelGGL(k_ge_flags, dim3(nblk(n_cols, kB)), dim3(kB), 0, st, (const int32_t*)samp, n_cols,
                          (int32_t)1 << b, fl);
       HIPX(hipGetLastError());
-      n_hot = (int32_t)excl_scan<int32_t, int32_t>(fl, n_cols, ps, tmp, st);
+      n_hot = (int32_t)excl_scan<int32_t, int32_t>(fl, n_cols, ps, sc, tmp, st);
       hot = tmp.get<int32_t>(n_hot);
       hipLaunchKernelGGL(k_compact_idx, dim3(nblk(n_cols, kB)), dim3(kB), 0, st, (const int32_t*)fl,
                          (const int32_t*)ps, n_cols, hot);
@@ -1041,58 +1299,79 @@ void col_count_atomic(const int32_t* col_idx, int64_t nnz, int64_t n_cols, int32
   }
 }
 
-// a1 for everything else: see k_col_count_lds
-void col_count_bucketed(const int32_t* col, int64_t nnz, int64_t n_cols, int cshift, int64_t windows, int32_t* clen,
-                        Tmp& tmp, hipStream_t st) {
-  const int nbits = 8, nb = 1 << nbits;
-  const int64_t chunk = 4096;
-  const int64_t nchunks = (nnz + chunk - 1) / chunk;
-  const unsigned grid = (unsigned)((nchunks + kCsWaves - 1) / kCsWaves);
+// a1 for everything else: see k_col_count_lds.  Also checks the ids: *bad (at
+// sc's place) is readable after the next wait, and no id out of range is used.
+bool col_count_is_bucketed(int64_t nnz, int64_t n_cols) {
+  return nnz >= 4096 && n_cols <= ((int64_t)kColBuckets << 17);
+}
+void col_count_bucketed(const int32_t* col, int64_t nnz, int64_t n_cols, int32_t* clen, int64_t* bad, Tmp& tmp,
+                        hipStream_t st) {
+  const int cbits = bits_for((uint64_t)(n_cols > 1 ? n_cols - 1 : 0));
+  // groups of at least 4096 columns: narrower ones give short runs, and more
+  // columns per counter set more counters to clear and write for each slice
+  const int shift = std::max(12, cbits - 8);
+  const int64_t win = std::min<int64_t>(kCntWin, (int64_t)1 << shift);
+  const int64_t per = std::max<int64_t>(1, (nnz + 1024 * kColStep - 1) / (1024 * kColStep)) * kColStep;
+  const int64_t nb = (nnz + per - 1) / per;
   int32_t* bcol = tmp.get<int32_t>(nnz);
-  int32_t* hist = tmp.get<int32_t>((int64_t)nb * nchunks);
-  int64_t* offs = tmp.get<int64_t>((int64_t)nb * nchunks + 1);
-  const ColBucketOp op{col, bcol, cshift};
-  hipLaunchKernelGGL((k_cs_hist<ColBucketOp>), dim3(grid), dim3(kCsBlock), kCsWaves * nb * sizeof(int32_t), st, op, nnz,
-                     nb, chunk, nchunks, hist);
+  int32_t* hist = tmp.get<int32_t>(kColBuckets * nb);
+  int64_t* offs = tmp.get<int64_t>(kColBuckets * nb + 1);
+  int64_t* total = offs + kColBuckets * nb;
+  const int64_t windows = ((int64_t)1 << shift) / win;
+  const int64_t most = (kColBuckets + nnz / kCntSlice) * windows;
+  CntTask* tasks = tmp.get<CntTask>(most);
+  int32_t* n_tasks = tmp.get<int32_t>(1);
+  hipLaunchKernelGGL(k_cols_scan, dim3((unsigned)nb), dim3(kColBlock), 0, st, col, nnz, n_cols, shift, per, hist, bad);
   HIPX(hipGetLastError());
-  excl_scan<int32_t, int64_t>(hist, (int64_t)nb * nchunks, offs, tmp, st);
-  // staged in LDS, so each bucket's run of a chunk is written coalesced
-  const size_t stage = (size_t)kCsWaves * (chunk * sizeof(ColBucketOp::Item) + 16 * (size_t)nb);
-  HIPX(hipFuncSetAttribute((const void*)k_cs_scatter_staged<ColBucketOp>, hipFuncAttributeMaxDynamicSharedMemorySize,
-                           (int)stage));
-  hipLaunchKernelGGL((k_cs_scatter_staged<ColBucketOp>), dim3(grid), dim3(kCsBlock), stage, st, op, nnz, nb, nbits,
-                     chunk, nchunks, (const int64_t*)offs, (const int32_t*)hist);
+  excl_scan_async<int32_t, int64_t>(hist, kColBuckets * nb, offs, total, tmp, st);
+  hipLaunchKernelGGL(k_cnt_tasks, dim3(1), dim3(kColBuckets), 0, st, (const int64_t*)offs, nb, (const int64_t*)total,
+                     shift, win, n_cols, tasks, n_tasks);
   HIPX(hipGetLastError());
-  // bucket starts: offs[b * nchunks]
-  int64_t* d_bs = tmp.get<int64_t>(nb);
-  hipLaunchKernelGGL(k_strided64, dim3(1), dim3(nb), 0, st, (const int64_t*)offs, nchunks, (int64_t)nb, d_bs);
+  hipLaunchKernelGGL(k_cols_place, dim3((unsigned)nb), dim3(kColBlock), 0, st, col, nnz, n_cols, shift, per,
+                     (const int64_t*)offs, bcol);
   HIPX(hipGetLastError());
-  std::vector<int64_t> bs(nb + 1);
-  HIPX(hipMemcpyAsync(bs.data(), d_bs, sizeof(int64_t) * nb, hipMemcpyDeviceToHost, st));
-  HIPX(hipStreamSynchronize(st));
-  bs[nb] = nnz;
-  std::vector<CntTask> tasks;
-  for (int b = 0; b < nb; ++b) {
-    const int64_t len = bs[b + 1] - bs[b];
-    if (len == 0) continue;
-    const int64_t ns = (len + kCntSlice - 1) / kCntSlice;
-    for (int64_t w = 0; w < windows; ++w) {
-      const int64_t base = ((int64_t)b << cshift) + w * kCntWin;
-      if (base >= n_cols) break;
-      for (int64_t j = 0; j < ns; ++j)
-        tasks.push_back(CntTask{bs[b] + len * j / ns, bs[b] + len * (j + 1) / ns, (int32_t)base, ns > 1 ? 1 : 0});
-    }
+  if (win * (int64_t)sizeof(int32_t) > 65536)
+    HIPX(hipFuncSetAttribute((const void*)k_col_count_lds, hipFuncAttributeMaxDynamicSharedMemorySize,
+                             kCntWin * (int)sizeof(int32_t)));
+  hipLaunchKernelGGL(k_col_count_lds, dim3((unsigned)most), dim3(kCntBlock), win * sizeof(int32_t), st,
+                     (const int32_t*)bcol, (const CntTask*)tasks, (const int32_t*)n_tasks, (int32_t)win, n_cols, clen);
+  HIPX(hipGetLastError());
+  tmp.release(bcol);
+  tmp.release(hist);
+  tmp.release(offs);
+  tmp.release(tasks);
+  tmp.release(n_tasks);
+}
+
+// Checks A and makes its column lengths (clen, zeroed here); what to look at
+// after the next wait, before any other use of A.
+struct Checked {
+  int64_t rows_at, cols_at;
+  void need(const Scalars& sc) const {
+    if (sc[rows_at]) throw Fail{TC_EINVAL, "invalid CSR: row_ptr must start at 0, not decrease and end at nnz"};
+    if (sc[cols_at]) throw Fail{TC_EINVAL, "invalid CSR: a column id is outside [0, n_cols)"};
   }
-  if (tasks.empty()) return;
-  CntTask* d_tasks = tmp.get<CntTask>((int64_t)tasks.size());
-  HIPX(hipMemcpyAsync(d_tasks, tasks.data(), sizeof(CntTask) * tasks.size(), hipMemcpyHostToDevice, st));
-  HIPX(hipFuncSetAttribute((const void*)k_col_count_lds, hipFuncAttributeMaxDynamicSharedMemorySize,
-                           kCntWin * (int)sizeof(int32_t)));
-  hipLaunchKernelGGL(k_col_count_lds, dim3((unsigned)tasks.size()), dim3(kCntBlock), kCntWin * sizeof(int32_t), st,
-                     (const int32_t*)bcol, (const CntTask*)d_tasks, n_cols, clen);
+};
+Checked check_and_count(const tc_csr* A, int32_t* clen, Scalars& sc, Tmp& tmp, hipStream_t st) {
+  const Checked c{sc.take(), sc.take()};
+  hipLaunchKernelGGL(k_validate_rows, dim3(nblk(A->n_rows + 1, kB)), dim3(kB), 0, st, A->row_ptr, A->n_rows, A->nnz,
+                     sc.dev(c.rows_at));
   HIPX(hipGetLastError());
-  // the task list is host memory: finish before it goes out of scope
-  HIPX(hipStreamSynchronize(st));
+  if (A->n_cols > 0) {
+    hipLaunchKernelGGL(k_fill_i32, dim3(nblk(A->n_cols, kB)), dim3(kB), 0, st, clen, A->n_cols, 0);
+    HIPX(hipGetLastError());
+  }
+  if (A->n_cols > 0 && col_count_is_bucketed(A->nnz, A->n_cols)) {
+    col_count_bucketed(A->col_idx, A->nnz, A->n_cols, clen, sc.dev(c.cols_at), tmp, st);
+  } else if (A->nnz > 0) {
+    hipLaunchKernelGGL(k_validate_cols, dim3(nblk(A->nnz, kB)), dim3(kB), 0, st, A->col_idx, A->nnz, A->n_cols,
+                       sc.dev(c.cols_at));
+    HIPX(hipGetLastError());
+    sc.wait();
+    c.need(sc);
+    col_count_atomic(A->col_idx, A->nnz, A->n_cols, clen, sc, tmp, st);
+  }
+  return c;
 }
 
 // transpose: entry e' of A^T is entry v[e'] of A
@@ -1113,28 +1392,13 @@ __global__ void k_transpose_gather(const int32_t* __restrict__ v, const int32_t*
 void transpose(const tc_csr* A, int64_t* rpT, int32_t* colT, float* valT, int32_t* permT, hipStream_t st) {
   const int64_t n_rows = A->n_rows, n_cols = A->n_cols, nnz = A->nnz;
   Tmp tmp(st);
-  {
-    int* flag = tmp.get<int>(1);
-    HIPX(hipMemsetAsync(flag, 0, sizeof(int), st));
-    hipLaunchKernelGGL(k_validate_rows, dim3(nblk(n_rows + 1, kB)), dim3(kB), 0, st, A->row_ptr, n_rows, nnz, flag);
-    if (nnz > 0) hipLaunchKernelGGL(k_validate_cols, dim3(nblk(nnz, kB)), dim3(kB), 0, st, A->col_idx, nnz, n_cols, flag);
-    HIPX(hipGetLastError());
-    int f = 0;
-    HIPX(hipMemcpyAsync(&f, flag, sizeof(int), hipMemcpyDeviceToHost, st));
-    HIPX(hipStreamSynchronize(st));
-    if (f & 1) throw Fail{TC_EINVAL, "invalid CSR: row_ptr must start at 0, not decrease and end at nnz"};
-    if (f & 2) throw Fail{TC_EINVAL, "invalid CSR: a column id is outside [0, n_cols)"};
-  }
+  Scalars sc(tmp, st);
   int32_t* clen = tmp.get<int32_t>(n_cols);
-  if (n_cols > 0) HIPX(hipMemsetAsync(clen, 0, sizeof(int32_t) * n_cols, st));
   const int cbits = bits_for((uint64_t)(n_cols > 1 ? n_cols - 1 : 0));
-  const int cshift = std::max(15, cbits - 8);
-  const int64_t windows = (int64_t)1 << (cshift - 15);
-  if (nnz >= 4096 && windows <= 4)
-    col_count_bucketed(A->col_idx, nnz, n_cols, cshift, windows, clen, tmp, st);
-  else if (n_cols > 0 && nnz > 0)
-    col_count_atomic(A->col_idx, nnz, n_cols, clen, tmp, st);
-  const int64_t total = n_cols > 0 ? excl_scan<int32_t, int64_t>(clen, n_cols, rpT, tmp, st) : 0;
+  const Checked checked = check_and_count(A, clen, sc, tmp, st);
+  const int64_t total = n_cols > 0 ? excl_scan<int32_t, int64_t>(clen, n_cols, rpT, sc, tmp, st) : 0;
+  if (n_cols == 0) sc.wait();
+  checked.need(sc);
   HIPX(hipMemcpyAsync(rpT + n_cols, &total, sizeof(int64_t), hipMemcpyHostToDevice, st));
   if (nnz > 0) {
     int32_t* row_of = tmp.get<int32_t>(nnz);
@@ -1300,26 +1564,6 @@ void parallel_for(int64_t n, int64_t min_par, F&& f) {
   for (int64_t i = 0; i < n; ++i) f(i);
 }
 
-// n items of T in a page-locked host block from the library's host pool, for
-// the life of one build step.  The block goes back to the pool when its
-// holder ends, after the build stream has finished every copy that may still
-// read or write it.
-template <class T>
-struct Staged {
-  HostBlock b;
-  hipStream_t st;
-  T* p;
-  Staged(int64_t n, hipStream_t s)
-      : b(host_take(sizeof(T) * (size_t)std::max<int64_t>(n, 1), true)), st(s), p((T*)b.p) {}
-  ~Staged() {
-    (void)hipStreamSynchronize(st);
-    host_give(b);
-  }
-  Staged(const Staged&) = delete;
-  Staged& operator=(const Staged&) = delete;
-  T& operator[](int64_t i) { return p[i]; }
-};
-
 // what a build needs to know of a device
 struct DeviceLimits {
   int32_t n_cu = 0;
@@ -1380,7 +1624,7 @@ void device_limits(tc_handle* h) {
 // panel bounds, and in *d_pb_out a device copy (int32).
 std::vector<int64_t> make_panels(const int32_t* seg_tile, const int32_t* seg_row, const int32_t* seg_len,
                                  int64_t nseg, int64_t n_rows, const int64_t* d_split_col, int32_t P, int64_t rows,
-                                 int32_t nct, Tmp& tmp, hipStream_t st, int32_t** d_pb_out) {
+                                 int32_t nct, Scalars& sc, Tmp& tmp, hipStream_t st, int32_t** d_pb_out) {
   std::vector<int64_t> pb{0};
   if (n_rows == 0) return pb;
   int32_t* w = tmp.get<int32_t>(n_rows);
@@ -1391,7 +1635,7 @@ std::vector<int64_t> make_panels(const int32_t* seg_tile, const int32_t* seg_row
     HIPX(hipGetLastError());
   }
   int64_t* pre = tmp.get<int64_t>(n_rows + 1);
-  const int64_t total = excl_scan<int32_t, int64_t>(w, n_rows, pre, tmp, st);
+  const int64_t total = excl_scan<int32_t, int64_t>(w, n_rows, pre, sc, tmp, st);
   HIPX(hipMemcpyAsync(pre + n_rows, &total, sizeof(int64_t), hipMemcpyHostToDevice, st));
   std::vector<int64_t> tgt(P), lb(P);
   for (int32_t p = 0; p < P; ++p) tgt[p] = ((int64_t)(p + 1) * total + P - 1) / P;
@@ -1460,43 +1704,24 @@ void build(const tc_csr* A, const tc_build_opts* o, hipStream_t st, tc_handle* h
   Tmp tmp(st);
   h->stream = st;
 
-  // ---- validation
-  {
-    int* flag = tmp.get<int>(1);
-    HIPX(hipMemsetAsync(flag, 0, sizeof(int), st));
-    hipLaunchKernelGGL(k_validate_rows, dim3(nblk(n_rows + 1, kB)), dim3(kB), 0, st, A->row_ptr, n_rows, nnz, flag);
-    HIPX(hipGetLastError());
-    if (nnz > 0) hipLaunchKernelGGL(k_validate_cols, dim3(nblk(nnz, kB)), dim3(kB), 0, st, A->col_idx, nnz, n_cols, flag);
-    HIPX(hipGetLastError());
-    int f = 0;
-    HIPX(hipMemcpyAsync(&f, flag, sizeof(int), hipMemcpyDeviceToHost, st));
-    HIPX(hipStreamSynchronize(st));
-    if (f & 1) throw Fail{TC_EINVAL, "invalid CSR: row_ptr must start at 0, not decrease and end at nnz"};
-    if (f & 2) throw Fail{TC_EINVAL, "invalid CSR: a column id is outside [0, n_cols)"};
-  }
-
-  clk.mark("validation");
-  // ---- a1: column lengths
-  int32_t* clen = hold<int32_t>(h, n_cols);
+  Scalars sc(tmp, st);
+  // ---- validation and a1: column lengths
+  int32_t* clen = hold<int32_t>(h, tmp, n_cols);
   h->d_clen = clen;
-  if (n_cols > 0) HIPX(hipMemsetAsync(clen, 0, sizeof(int32_t) * n_cols, st));
-  const int cbits = bits_for((uint64_t)(n_cols > 1 ? n_cols - 1 : 0));
-  const int cshift = std::max(15, cbits - 8);  // bucket = column >> cshift (at most 256 buckets)
-  const int64_t windows = (int64_t)1 << (cshift - 15);
-  if (nnz >= 4096 && windows <= 4) {
-    col_count_bucketed(A->col_idx, nnz, n_cols, cshift, windows, clen, tmp, st);
-  } else if (n_cols > 0) {
-    col_count_atomic(A->col_idx, nnz, n_cols, clen, tmp, st);
-  }
-  const int32_t maxclen = dev_max(clen, n_cols, tmp, st);
+  const Checked checked = check_and_count(A, clen, sc, tmp, st);
+  const MaxOf clen_max = max_async(clen, n_cols, sc, st);
+  sc.wait();
+  checked.need(sc);
+  const int32_t maxclen = clen_max.read(sc);
 
   clk.mark("a1 column lengths");
   // ---- a2: stable sort of columns by decreasing length
-  int32_t* cperm = hold<int32_t>(h, n_cols);
-  int32_t* cpos = hold<int32_t>(h, n_cols);
+  int32_t* cperm = hold<int32_t>(h, tmp, n_cols);
+  int32_t* cpos = hold<int32_t>(h, tmp, n_cols);
   int32_t* clen_sorted = tmp.get<int32_t>(n_cols);
   h->d_cperm = cperm;
   h->d_cpos = cpos;
+  const int64_t zero_at = sc.take();  // first column without entries
   if (n_cols > 0) {
     uint32_t* k0 = tmp.get<uint32_t>(n_cols);
     uint32_t* k1 = tmp.get<uint32_t>(n_cols);
@@ -1513,17 +1738,12 @@ void build(const tc_csr* A, const tc_build_opts* o, hipStream_t st, tc_handle* h
     hipLaunchKernelGGL(k_cols_finish, dim3(nblk(n_cols, kB)), dim3(kB), 0, st, k0, v0, n_cols, maxclen, cperm, cpos,
                        clen_sorted);
     HIPX(hipGetLastError());
-    unsigned long long* cnt = tmp.get<unsigned long long>(1);
-    HIPX(hipMemsetAsync(cnt, 0, sizeof(*cnt), st));
-    hipLaunchKernelGGL(k_count_eq, dim3(nblk(n_cols, kB)), dim3(kB), 0, st, clen_sorted, n_cols, 0, cnt);
+    hipLaunchKernelGGL(k_first_zero, dim3(1), dim3(kWave), 0, st, (const int32_t*)clen_sorted, n_cols,
+                       sc.dev(zero_at));
     HIPX(hipGetLastError());
-    unsigned long long nd = 0;
-    HIPX(hipMemcpyAsync(&nd, cnt, sizeof(nd), hipMemcpyDeviceToHost, st));
-    HIPX(hipStreamSynchronize(st));
-    h->n_dangling = (int64_t)nd;
   }
-  int32_t* rowmap = hold<int32_t>(h, n_rows);
-  int32_t* rowinv = hold<int32_t>(h, n_rows);
+  int32_t* rowmap = hold<int32_t>(h, tmp, n_rows);
+  int32_t* rowinv = hold<int32_t>(h, tmp, n_rows);
   h->d_rowmap = rowmap;
   h->d_rowinv = rowinv;
   if (n_rows > 0) {
@@ -1544,7 +1764,7 @@ void build(const tc_csr* A, const tc_build_opts* o, hipStream_t st, tc_handle* h
     const int64_t head = std::min<int64_t>(W, n_cols);
     const int64_t m = n_cols - head;
     int64_t* pre = tmp.get<int64_t>(m + 1);
-    const int64_t rest = excl_scan<int32_t, int64_t>(clen_sorted + head, m, pre, tmp, st);
+    const int64_t rest = excl_scan<int32_t, int64_t>(clen_sorted + head, m, pre, sc, tmp, st);
     HIPX(hipMemcpyAsync(pre + m, &rest, sizeof(int64_t), hipMemcpyHostToDevice, st));
     const int G = h->xcd_groups;
     int64_t* need = tmp.get<int64_t>(G);
@@ -1595,6 +1815,8 @@ void build(const tc_csr* A, const tc_build_opts* o, hipStream_t st, tc_handle* h
   } else {
     if (o->n_tiles >= 0) {
       T = (int32_t)std::min<int64_t>(o->n_tiles, NT);
+    } else if (NT == 1) {
+      T = maxclen >= 2 ? 1 : 0;  // the longest column is the tile's first
     } else if (NT > 0) {
       int32_t* samp = tmp.get<int32_t>(NT);
       hipLaunchKernelGGL(k_strided, dim3(nblk(NT, kB)), dim3(kB), 0, st, clen_sorted, (int64_t)W, NT, samp);
@@ -1652,8 +1874,10 @@ void build(const tc_csr* A, const tc_build_opts* o, hipStream_t st, tc_handle* h
   // and the segment sort in a5 needs no passes over the row bits.
   const bool perm_rows = !one_tile && h->relabel && h->kernel != 1;
   const bool rows_in_order = one_tile || perm_rows || !h->relabel;
+  // One tile of the composite kernel: the pack maps the columns itself
+  const bool map_in_pack = one_tile && h->kernel != 1;
   if (nnz > 0) {
-    int32_t* icol = tmp.get<int32_t>(nnz);
+    int32_t* icol = map_in_pack ? nullptr : tmp.get<int32_t>(nnz);
     int32_t* row_of = nullptr;
     float* pval = nullptr;
     int32_t* hist0 = nullptr;  // histogram of the first tile pass, when made by the permutation
@@ -1664,10 +1888,7 @@ void build(const tc_csr* A, const tc_build_opts* o, hipStream_t st, tc_handle* h
       hipLaunchKernelGGL(k_irow_len, dim3(nblk(n_rows, kB)), dim3(kB), 0, st, A->row_ptr, (const int32_t*)rowinv,
                          n_rows, ilen, istart);
       HIPX(hipGetLastError());
-      const int64_t nsb = std::max<int64_t>(1, (n_rows + kScanTile - 1) / kScanTile);
-      int64_t* bs = tmp.get<int64_t>(nsb + 1);
-      excl_scan_async<int32_t, int64_t>(ilen, n_rows, iptr, bs, nsb, st);
-      HIPX(hipMemcpyAsync(iptr + n_rows, bs + nsb, sizeof(int64_t), hipMemcpyDeviceToDevice, st));
+      excl_scan_async<int32_t, int64_t>(ilen, n_rows, iptr, iptr + n_rows, tmp, st);
       int32_t* irow = tmp.get<int32_t>(nnz);
       rows_of(iptr, n_rows, nnz, irow, st);
       HIPX(hipGetLastError());
@@ -1688,15 +1909,15 @@ void build(const tc_csr* A, const tc_build_opts* o, hipStream_t st, tc_handle* h
       tmp.release(irow);
       tmp.release(iptr);
       tmp.release(ilen);
-      tmp.release(bs);
-    } else {
+    } else if (icol) {
       hipLaunchKernelGGL(k_icol, dim3(nblk(nnz, kB)), dim3(kB), 0, st, A->col_idx, cpos, nnz, icol);
       HIPX(hipGetLastError());
     }
     const int tb = bits_for((uint64_t)(ntiles > 1 ? ntiles - 1 : 0));
     if (one_tile) {
-      b_icol = icol;
+      b_icol = icol ? icol : const_cast<int32_t*>(A->col_idx);
       b_val = vsrc;
+      tstart[ntiles] = nnz;
     } else {
       if (!row_of) {
         row_of = tmp.get<int32_t>(nnz);
@@ -1726,11 +1947,13 @@ void build(const tc_csr* A, const tc_build_opts* o, hipStream_t st, tc_handle* h
       b_val = cv;
     }
     clk.mark("a4 bucket passes");
-    d_ts = tmp.get<int64_t>(ntiles + 1);
-    hipLaunchKernelGGL(k_tile_bounds, dim3(nblk(ntiles + 1, kB)), dim3(kB), 0, st, b_icol, nnz, tmap, ntiles, d_ts);
-    HIPX(hipGetLastError());
-    HIPX(hipMemcpyAsync(tstart.data(), d_ts, sizeof(int64_t) * (ntiles + 1), hipMemcpyDeviceToHost, st));
-    HIPX(hipStreamSynchronize(st));
+    if (!one_tile) {
+      d_ts = tmp.get<int64_t>(ntiles + 1);
+      hipLaunchKernelGGL(k_tile_bounds, dim3(nblk(ntiles + 1, kB)), dim3(kB), 0, st, b_icol, nnz, tmap, ntiles, d_ts);
+      HIPX(hipGetLastError());
+      HIPX(hipMemcpyAsync(tstart.data(), d_ts, sizeof(int64_t) * (ntiles + 1), hipMemcpyDeviceToHost, st));
+      HIPX(hipStreamSynchronize(st));
+    }
   }
   h->tile_nnz.resize(ntiles);
   for (int t = 0; t < ntiles; ++t) h->tile_nnz[t] = tstart[t + 1] - tstart[t];
@@ -1740,8 +1963,10 @@ void build(const tc_csr* A, const tc_build_opts* o, hipStream_t st, tc_handle* h
   if (ntiles > 0)
     HIPX(hipMemcpyAsync(d_split_t, h->tile_split.data(), sizeof(int64_t) * ntiles, hipMemcpyHostToDevice, st));
   int32_t* first = tmp.get<int32_t>(n_rows);
-  int32_t* touched = tmp.get<int32_t>(n_rows);
-  if (n_rows > 0) {
+  // one tile: `first` and the rows without entries are written with the segments
+  const bool rows_direct = one_tile && h->n_panels == 0 && nnz > 0;
+  int32_t* touched = rows_direct ? nullptr : tmp.get<int32_t>(n_rows);
+  if (n_rows > 0 && touched) {
     hipLaunchKernelGGL(k_fill_i32, dim3(nblk(n_rows, kB)), dim3(kB), 0, st, first, n_rows, (int32_t)0x7fffffff);
     hipLaunchKernelGGL(k_fill_i32, dim3(nblk(n_rows, kB)), dim3(kB), 0, st, touched, n_rows, (int32_t)0);
     HIPX(hipGetLastError());
@@ -1759,22 +1984,32 @@ void build(const tc_csr* A, const tc_build_opts* o, hipStream_t st, tc_handle* h
   int64_t nruns = 0;
   if (nnz > 0) {
     int32_t *seg_start, *seg_row, *seg_tile, *seg_len;
+    MaxOf len_max;
     if (one_tile) {
       // one segment per non-empty row, emitted in increasing internal row
       int32_t* flags = tmp.get<int32_t>(n_rows);
       int32_t* pos = tmp.get<int32_t>(n_rows);
-      hipLaunchKernelGGL(k_rowseg_flags, dim3(nblk(n_rows, kB)), dim3(kB), 0, st, A->row_ptr, rowinv, n_rows, flags);
+      int32_t* len = tmp.get<int32_t>(n_rows);
+      hipLaunchKernelGGL(k_rowseg_flags, dim3(nblk(n_rows, kB)), dim3(kB), 0, st, A->row_ptr, rowinv, n_rows, flags,
+                         len);
       HIPX(hipGetLastError());
-      nseg = excl_scan<int32_t, int32_t>(flags, n_rows, pos, tmp, st);
+      len_max = max_async(len, n_rows, sc, st);
+      nseg = excl_scan<int32_t, int32_t>(flags, n_rows, pos, sc, tmp, st);
+      if (rows_direct) {
+        h->n_empty = n_rows - nseg;
+        h->d_empty = hold<int32_t>(h, tmp, h->n_empty);
+      }
       seg_start = tmp.get<int32_t>(nseg);
       seg_row = tmp.get<int32_t>(nseg);
       seg_tile = tmp.get<int32_t>(nseg);
       seg_len = tmp.get<int32_t>(nseg);
-      hipLaunchKernelGGL(k_rowseg_emit, dim3(nblk(n_rows, kB)), dim3(kB), 0, st, flags, pos, A->row_ptr, rowinv,
-                         n_rows, seg_start, seg_row, seg_tile, seg_len);
+      hipLaunchKernelGGL(k_rowseg_emit, dim3(nblk(n_rows, kB)), dim3(kB), 0, st, (const int32_t*)pos,
+                         (const int32_t*)len, A->row_ptr, rowinv, n_rows, h->tile_split[0], seg_start, seg_row,
+                         seg_tile, seg_len, h->d_empty, rows_direct ? first : (int32_t*)nullptr);
       HIPX(hipGetLastError());
       tmp.release(flags);
       tmp.release(pos);
+      tmp.release(len);
     } else {
       // heads counted per scan block, their block offsets scanned, then the
       // segments written at their positions (no per-entry flag array)
@@ -1783,10 +2018,11 @@ void build(const tc_csr* A, const tc_build_opts* o, hipStream_t st, tc_handle* h
       hipLaunchKernelGGL(k_seghead_count, dim3((unsigned)nb), dim3(kScanBlock), 0, st, b_row, nnz,
                          (const int64_t*)d_ts, ntiles, bs);
       HIPX(hipGetLastError());
-      hipLaunchKernelGGL(k_scan_blocks, dim3(1), dim3(kScanBlock), 0, st, bs, nb, bs + nb);
+      const int64_t nseg_at = sc.take();
+      hipLaunchKernelGGL(k_scan_blocks, dim3(1), dim3(kScanBlock), 0, st, bs, nb, sc.dev(nseg_at));
       HIPX(hipGetLastError());
-      HIPX(hipMemcpyAsync(&nseg, bs + nb, sizeof(int64_t), hipMemcpyDeviceToHost, st));
-      HIPX(hipStreamSynchronize(st));
+      sc.wait();
+      nseg = sc[nseg_at];
       seg_start = tmp.get<int32_t>(nseg);
       seg_row = tmp.get<int32_t>(nseg);
       seg_tile = tmp.get<int32_t>(nseg);
@@ -1805,7 +2041,7 @@ void build(const tc_csr* A, const tc_build_opts* o, hipStream_t st, tc_handle* h
       const int32_t nct = ntiles;
       int32_t* d_pb = nullptr;
       h->panel_begin = make_panels(seg_tile, seg_row, seg_len, nseg, n_rows, d_split_t, h->n_panels,
-                                   h->panel_rows, nct, tmp, st, &d_pb);
+                                   h->panel_rows, nct, sc, tmp, st, &d_pb);
       h->n_panels = (int32_t)h->panel_begin.size() - 1;
       // segment tiles become (panel, column tile) tiles; first touches with them
       const int lds_pb = h->n_panels + 1 <= 8192 ? 1 : 0;
@@ -1833,12 +2069,16 @@ void build(const tc_csr* A, const tc_build_opts* o, hipStream_t st, tc_handle* h
       trow.assign(ntiles + 1, 0);
     }
     clk.mark("a5 segments formed");
-    if (h->n_panels == 0) {
+    if (h->n_panels == 0 && !rows_direct) {
       hipLaunchKernelGGL(k_first_touch, dim3(nblk(nseg, kB)), dim3(kB), 0, st, seg_tile, seg_len, seg_row, nseg,
                          (const int64_t*)d_split_t, first, touched);
       HIPX(hipGetLastError());
     }
-    const int32_t maxlen = dev_max(seg_len, nseg, tmp, st);
+    if (!one_tile) {
+      len_max = max_async(seg_len, nseg, sc, st);
+      sc.wait();
+    }
+    const int32_t maxlen = len_max.read(sc);
     const int lb = bits_for((uint64_t)maxlen);
     const int rb = bits_for((uint64_t)(n_rows > 1 ? n_rows - 1 : 0));
     const int tb = bits_for((uint64_t)(ntiles > 1 ? ntiles - 1 : 0));
@@ -1859,8 +2099,8 @@ void build(const tc_csr* A, const tc_build_opts* o, hipStream_t st, tc_handle* h
       std::swap(v0, v1);
     }
     clk.mark("a5 segments sorted");
-    rows_sorted = hold<int32_t>(h, nseg);
-    rows_len = hold<int32_t>(h, nseg);
+    rows_sorted = hold<int32_t>(h, tmp, nseg);
+    rows_len = hold<int32_t>(h, tmp, nseg);
     srt_start = tmp.get<int32_t>(nseg);
     hipLaunchKernelGGL(k_seg_decode, dim3(nblk(nseg, kB)), dim3(kB), 0, st, (const uint64_t*)k0, (const int32_t*)v0,
                        nseg, maxlen, lb, rb, rows_sorted, rows_len, srt_start);
@@ -1872,8 +2112,7 @@ void build(const tc_csr* A, const tc_build_opts* o, hipStream_t st, tc_handle* h
     if (h->n_panels > 0) {
       // entries of every (panel, column tile) tile: sums of its sorted rows' lengths
       int64_t* pre = tmp.get<int64_t>(nseg + 1);
-      const int64_t tot = excl_scan<int32_t, int64_t>(rows_len, nseg, pre, tmp, st);
-      HIPX(hipMemcpyAsync(pre + nseg, &tot, sizeof(int64_t), hipMemcpyHostToDevice, st));
+      excl_scan_async<int32_t, int64_t>(rows_len, nseg, pre, pre + nseg, tmp, st);
       int64_t* d_tn = tmp.get<int64_t>(ntiles);
       hipLaunchKernelGGL(k_tile_entries, dim3(nblk(ntiles, kB)), dim3(kB), 0, st, (const int64_t*)pre,
                          (const int64_t*)d_off, ntiles, d_tn);
@@ -1885,7 +2124,7 @@ void build(const tc_csr* A, const tc_build_opts* o, hipStream_t st, tc_handle* h
     int32_t* rpos = tmp.get<int32_t>(nseg);
     hipLaunchKernelGGL(k_run_flags, dim3(nblk(nseg, kB)), dim3(kB), 0, st, k0, nseg, rb, rflags);
     HIPX(hipGetLastError());
-    nruns = excl_scan<int32_t, int32_t>(rflags, nseg, rpos, tmp, st);
+    nruns = excl_scan<int32_t, int32_t>(rflags, nseg, rpos, sc, tmp, st);
     int64_t* d_rp = tmp.get<int64_t>(nruns);
     int32_t* d_rl = tmp.get<int32_t>(nruns);
     hipLaunchKernelGGL(k_run_emit, dim3(nblk(nseg, kB)), dim3(kB), 0, st, rflags, rpos, rows_len, nseg, d_rp, d_rl);
@@ -1908,6 +2147,8 @@ void build(const tc_csr* A, const tc_build_opts* o, hipStream_t st, tc_handle* h
     h->n_panels = 0;
     h->n_col_tiles = 0;
   }
+  if (nnz == 0) sc.wait();  // else the segments' waits came after it
+  h->n_dangling = n_cols > 0 ? n_cols - sc[zero_at] : 0;
   h->d_rows_sorted = rows_sorted;
   h->d_rows_len = rows_len;
   h->n_rows_sorted = nseg;
@@ -2006,7 +2247,7 @@ void build(const tc_csr* A, const tc_build_opts* o, hipStream_t st, tc_handle* h
     troff[t + 1] += troff[t];
   }
   clk.mark("a6 sizes and partition");
-  h->d_tile_wl_begin = hold<int64_t>(h, ntiles + 1);
+  h->d_tile_wl_begin = hold<int64_t>(h, tmp, ntiles + 1);
   HIPX(hipMemcpyAsync(h->d_tile_wl_begin, h->tile_wl_begin.data(), sizeof(int64_t) * (ntiles + 1),
                       hipMemcpyHostToDevice, st));
   const int64_t nwl = (int64_t)wls.size();
@@ -2024,10 +2265,10 @@ void build(const tc_csr* A, const tc_build_opts* o, hipStream_t st, tc_handle* h
     }
     cbv[nct] = (int64_t)chunks.size();
     std::vector<int32_t> pb32(h->panel_begin.begin(), h->panel_begin.end());
-    h->d_panel_ncb = hold<int64_t>(h, std::max<int64_t>(ntiles, 1));
-    h->d_panel_cb = hold<int64_t>(h, nct + 1);
-    h->d_panel_chunks = hold<int64_t>(h, std::max<int64_t>((int64_t)chunks.size(), 1));
-    h->d_panel_begin = hold<int32_t>(h, h->n_panels + 1);
+    h->d_panel_ncb = hold<int64_t>(h, tmp, std::max<int64_t>(ntiles, 1));
+    h->d_panel_cb = hold<int64_t>(h, tmp, nct + 1);
+    h->d_panel_chunks = hold<int64_t>(h, tmp, std::max<int64_t>((int64_t)chunks.size(), 1));
+    h->d_panel_begin = hold<int32_t>(h, tmp, h->n_panels + 1);
     HIPX(hipMemcpyAsync(h->d_panel_ncb, ncb.data(), sizeof(int64_t) * ntiles, hipMemcpyHostToDevice, st));
     HIPX(hipMemcpyAsync(h->d_panel_cb, cbv.data(), sizeof(int64_t) * (nct + 1), hipMemcpyHostToDevice, st));
     if (!chunks.empty())
@@ -2101,10 +2342,10 @@ void build(const tc_csr* A, const tc_build_opts* o, hipStream_t st, tc_handle* h
   // ---- a7: pack, pipelined with the descriptors: the tiles go in a few
   // batches, and each batch's descriptors are copied and packed on the stream
   // while the host makes the next batch's
-  h->d_idx = hold<int32_t>(h, doff);
-  h->d_val = hold<float>(h, doff);
-  h->d_rowid = hold<int32_t>(h, roff);
-  h->d_wl = hold<Wl>(h, nwl);
+  h->d_idx = hold<int32_t>(h, tmp, doff);
+  h->d_val = hold<float>(h, tmp, doff);
+  h->d_rowid = hold<int32_t>(h, tmp, roff);
+  h->d_wl = hold<Wl>(h, tmp, nwl);
   PackX* d_px = tmp.get<PackX>(nwl);
   Staged<int32_t> tfirst(ntiles, st);
   for (int t = 0; t < ntiles; ++t) tfirst[t] = (int32_t)h->tile_col_begin[t];
@@ -2149,13 +2390,13 @@ void build(const tc_csr* A, const tc_build_opts* o, hipStream_t st, tc_handle* h
       hipLaunchKernelGGL(k_pack, dim3(nblk(nb * kPackSlices, kB / kWave)), dim3(kB), 0, st,
                          (const Wl*)(h->d_wl + j0), (const PackX*)(d_px + j0), nb, (const int32_t*)d_tfirst,
                          h->camping_pad ? 1 : 0, srt_start, rows_len, rows_sorted, b_icol, b_val,
-                         (const int32_t*)first, h->d_idx, h->d_val, h->d_rowid, o->value_map ? pad_minus_one() : 0.0f);
+                         map_in_pack ? (const int32_t*)cpos : (const int32_t*)nullptr, (const int32_t*)first, h->d_idx, h->d_val, h->d_rowid, o->value_map ? pad_minus_one() : 0.0f);
       HIPX(hipGetLastError());
     }
   }
   clk.mark("a6 descriptors + a7 pack");
   if (o->value_map) {
-    h->d_vmap = hold<int32_t>(h, doff);
+    h->d_vmap = hold<int32_t>(h, tmp, doff);
     if (doff > 0) {
       hipLaunchKernelGGL(k_vmap_finish, dim3(nblk(doff, kB)), dim3(kB), 0, st, h->d_val, doff, A->val, h->d_vmap);
       HIPX(hipGetLastError());
@@ -2182,22 +2423,22 @@ void build(const tc_csr* A, const tc_build_opts* o, hipStream_t st, tc_handle* h
                          (const int32_t*)rowmap, nnz, cfirst);
       HIPX(hipGetLastError());
     }
-    h->d_coo_row = hold<int32_t>(h, nnz);
-    h->d_coo_col = hold<int32_t>(h, nnz);
-    h->d_coo_val = hold<float>(h, nnz);
+    h->d_coo_row = hold<int32_t>(h, tmp, nnz);
+    h->d_coo_col = hold<int32_t>(h, tmp, nnz);
+    h->d_coo_val = hold<float>(h, tmp, nnz);
     hipLaunchKernelGGL(k_coo_pack, dim3(nblk(nnz, kB)), dim3(kB), 0, st, rows, (const int32_t*)b_icol, b_val,
                        (const int64_t*)d_ts, ntiles, (const int32_t*)rowmap, (const int32_t*)cfirst, nnz,
                        h->d_coo_row, h->d_coo_col, h->d_coo_val);
     HIPX(hipGetLastError());
   }
   // rows without any entry: every product writes their zero
-  if (n_rows > 0) {
+  if (n_rows > 0 && touched) {
     int32_t* ef = tmp.get<int32_t>(n_rows);
     int32_t* ep = tmp.get<int32_t>(n_rows);
     hipLaunchKernelGGL(k_not, dim3(nblk(n_rows, kB)), dim3(kB), 0, st, (const int32_t*)touched, n_rows, ef);
     HIPX(hipGetLastError());
-    h->n_empty = excl_scan<int32_t, int32_t>(ef, n_rows, ep, tmp, st);
-    h->d_empty = hold<int32_t>(h, h->n_empty);
+    h->n_empty = excl_scan<int32_t, int32_t>(ef, n_rows, ep, sc, tmp, st);
+    h->d_empty = hold<int32_t>(h, tmp, h->n_empty);
     hipLaunchKernelGGL(k_compact_idx, dim3(nblk(n_rows, kB)), dim3(kB), 0, st, (const int32_t*)ef,
                        (const int32_t*)ep, n_rows, h->d_empty);
     HIPX(hipGetLastError());
@@ -2208,23 +2449,23 @@ void build(const tc_csr* A, const tc_build_opts* o, hipStream_t st, tc_handle* h
     int32_t* zp = tmp.get<int32_t>(n_rows);
     hipLaunchKernelGGL(k_ne, dim3(nblk(n_rows, kB)), dim3(kB), 0, st, (const int32_t*)first, n_rows, 0, zf);
     HIPX(hipGetLastError());
-    h->n_zero0 = excl_scan<int32_t, int32_t>(zf, n_rows, zp, tmp, st);
-    h->d_zero0 = hold<int32_t>(h, h->n_zero0);
+    h->n_zero0 = excl_scan<int32_t, int32_t>(zf, n_rows, zp, sc, tmp, st);
+    h->d_zero0 = hold<int32_t>(h, tmp, h->n_zero0);
     hipLaunchKernelGGL(k_compact_idx, dim3(nblk(n_rows, kB)), dim3(kB), 0, st, (const int32_t*)zf,
                        (const int32_t*)zp, n_rows, h->d_zero0);
     HIPX(hipGetLastError());
-    h->d_ypriv = hold<float>(h, (int64_t)h->xcd_groups * n_rows);
+    h->d_ypriv = hold<float>(h, tmp, (int64_t)h->xcd_groups * n_rows);
     HIPX(hipMemsetAsync(h->d_ypriv, 0, sizeof(float) * (size_t)h->xcd_groups * n_rows, st));
   }
-  h->d_split = hold<SplitRow>(h, (int64_t)srows.size());
-  h->d_partial = hold<double>(h, std::max<int64_t>(h->n_slots, 1) * 256);
+  h->d_split = hold<SplitRow>(h, tmp, (int64_t)srows.size());
+  h->d_partial = hold<double>(h, tmp, std::max<int64_t>(h->n_slots, 1) * 256);
   std::vector<int32_t> slot_split((size_t)h->n_slots);
   if (!srows.empty()) {
     HIPX(hipMemcpyAsync(h->d_split, srows.data(), sizeof(SplitRow) * srows.size(), hipMemcpyHostToDevice, st));
     for (size_t i = 0; i < srows.size(); ++i)
       std::fill_n(slot_split.begin() + srows[i].slot_begin, srows[i].n_slots, (int32_t)i);
-    h->d_slot_split = hold<int32_t>(h, h->n_slots);
-    h->d_ticket = hold<uint32_t>(h, h->n_split_rows);
+    h->d_slot_split = hold<int32_t>(h, tmp, h->n_slots);
+    h->d_ticket = hold<uint32_t>(h, tmp, h->n_split_rows);
     HIPX(hipMemcpyAsync(h->d_slot_split, slot_split.data(), sizeof(int32_t) * h->n_slots, hipMemcpyHostToDevice, st));
     HIPX(hipMemsetAsync(h->d_ticket, 0, sizeof(uint32_t) * h->n_split_rows, st));
   }
@@ -2238,13 +2479,13 @@ void build(const tc_csr* A, const tc_build_opts* o, hipStream_t st, tc_handle* h
       while (q < srows.size() && srows[q].row < lo) ++q;
       psb[p] = p == h->n_panels ? (int64_t)srows.size() : (int64_t)q;
     }
-    h->d_panel_split_begin = hold<int64_t>(h, h->n_panels + 1);
-    h->d_panel_yraw = hold<float>(h, std::max<int64_t>((int64_t)srows.size(), 1));
+    h->d_panel_split_begin = hold<int64_t>(h, tmp, h->n_panels + 1);
+    h->d_panel_yraw = hold<float>(h, tmp, std::max<int64_t>((int64_t)srows.size(), 1));
     HIPX(hipMemcpyAsync(h->d_panel_split_begin, psb.data(), sizeof(int64_t) * psb.size(), hipMemcpyHostToDevice, st));
   }
-  h->d_xbuf = hold<float>(h, std::max(n_rows, n_cols));
-  h->d_ybuf = hold<float>(h, std::max(n_rows, n_cols));
-  h->d_red = hold<double>(h, 4096);
+  h->d_xbuf = hold<float>(h, tmp, std::max(n_rows, n_cols));
+  h->d_ybuf = hold<float>(h, tmp, std::max(n_rows, n_cols));
+  h->d_red = hold<double>(h, tmp, 4096);
   HIPX(hipStreamSynchronize(st));
   clk.mark("a7 pack + metadata");
 }

@@ -3,6 +3,7 @@
 // launch, so small graphs share the GPU.
 #include <algorithm>
 #include <cmath>
+#include <cstring>
 #include <vector>
 
 #include "tc_host.h"
@@ -45,7 +46,7 @@ __device__ inline int last_le(int n, int64_t j, K key) {
 // compiler, and every access through it would be a flat (not global) access.
 #define TC_GLOBAL __attribute__((address_space(1)))
 struct MultiSegG {
-  const Wl* wl;  // one record per wavefront: left generic
+  const Wl* wl;  // read by ld_uniform
   int64_t begin;
   const TC_GLOBAL int32_t* idx;
   const TC_GLOBAL float* val;
@@ -58,26 +59,57 @@ struct MultiSegG {
 #undef TC_GLOBAL
 static_assert(sizeof(MultiSegG) == sizeof(MultiSeg), "MultiSegG mirrors MultiSeg");
 
-// the same with the RWR restart of each graph fused into its row writes
+// A record that no kernel of the launch writes, at a wavefront-uniform address:
+// read by scalar loads.
+template <class T>
+__device__ inline T ld_uniform(const T* p) {
+  static_assert(sizeof(T) % 8 == 0, "read as 64-bit words");
+  struct Words {
+    uint64_t w[sizeof(T) / 8];
+  } t;
+  const auto q = (const __attribute__((address_space(4))) uint64_t*)p;
+#pragma unroll
+  for (int i = 0; i < (int)(sizeof(T) / 8); ++i) t.w[i] = q[i];
+  return __builtin_bit_cast(T, t);
+}
+
+// The segment of wavefront j: from[j / kFromStep] is that of the step's first,
+// and few begin within a step (a search of all of them is five loads that wait
+// for each other).
+constexpr int kFromStep = 64;
+__device__ inline int seg_of(const MultiSeg* __restrict__ segs, int32_t n, const int32_t* __restrict__ from,
+                             int64_t j) {
+  int i = from[j / kFromStep];
+  while (i + 1 < n && segs[i + 1].begin <= j) ++i;
+  return __builtin_amdgcn_readfirstlane(i);
+}
+
+// The product of tile t of every graph, with the RWR restart of each graph fused
+// into its row writes.  Bound by the gathers: 32 graphs of 2^10-2^16 vertices
+// (18.6M entries, 22.4M with padding) in 88 us, 255 G gathers/s;
+// random ones into an x of their size (2.5 MB) reach 213.  With the segment found by
+// search and it and the descriptor read through plain pointers (vector loads, so
+// every branch and address of the workload in vector registers) it took 117.
 __global__ void __launch_bounds__(kB) k_tile_spmv_multi_rwr(const MultiSeg* __restrict__ segs, int32_t n_segs,
-                                                            int64_t total, double c) {
+                                                            const int32_t* __restrict__ from, int64_t total,
+                                                            double c) {
   const int lane = lane_id();
   const int64_t j = (int64_t)blockIdx.x * kWpb + __builtin_amdgcn_readfirstlane(threadIdx.x / kWave);
   if (j >= total) return;
-  const int i = __builtin_amdgcn_readfirstlane(last_le(n_segs, j, [&](int m) { return segs[m].begin; }));
-  const MultiSegG s = ((const MultiSegG*)segs)[i];
-  run_workload(s.wl[j - s.begin], lane, (const int32_t*)s.idx, (const float*)s.val, (const int32_t*)s.rowid,
+  const int i = seg_of(segs, n_segs, from, j);
+  const MultiSegG s = ld_uniform((const MultiSegG*)segs + i);
+  run_workload(ld_uniform(s.wl + (j - s.begin)), lane, (const int32_t*)s.idx, (const float*)s.val, (const int32_t*)s.rowid,
                RwrX{(const float*)s.x, c, (int32_t)s.seed}, (float*)s.y, (double*)s.partial);
 }
 
 __global__ void __launch_bounds__(kB) k_tile_spmv_multi(const MultiSeg* __restrict__ segs, int32_t n_segs,
-                                                        int64_t total) {
+                                                        const int32_t* __restrict__ from, int64_t total) {
   const int lane = lane_id();
   const int64_t j = (int64_t)blockIdx.x * kWpb + __builtin_amdgcn_readfirstlane(threadIdx.x / kWave);
   if (j >= total) return;
-  const int i = __builtin_amdgcn_readfirstlane(last_le(n_segs, j, [&](int m) { return segs[m].begin; }));
-  const MultiSegG s = ((const MultiSegG*)segs)[i];
-  run_workload(s.wl[j - s.begin], lane, (const int32_t*)s.idx, (const float*)s.val, (const int32_t*)s.rowid,
+  const int i = seg_of(segs, n_segs, from, j);
+  const MultiSegG s = ld_uniform((const MultiSegG*)segs + i);
+  run_workload(ld_uniform(s.wl + (j - s.begin)), lane, (const int32_t*)s.idx, (const float*)s.val, (const int32_t*)s.rowid,
                GlobalX{(const float*)s.x}, (float*)s.y, (double*)s.partial);
 }
 
@@ -179,6 +211,16 @@ __global__ void k_rwr_init_multi(const MultiVec* __restrict__ v, int32_t nv, int
   m.r[i] = i == m.seed ? 1.0f : 0.0f;
 }
 
+// every graph's iterate in the caller's ids, in one launch (a launch per graph
+// cost the host 13 us each, more than a graph's whole iteration)
+__global__ void k_out_multi(const MultiVec* __restrict__ v, int32_t nv, int64_t total) {
+  const int64_t t = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
+  if (t >= total) return;
+  const MultiVec m = v[last_le(nv, t, [&](int q) { return v[q].begin; })];
+  const int64_t i = t - m.begin;
+  m.y[i] = m.r[m.list[i]];
+}
+
 __global__ void k_map_ids_multi(const int32_t* const* __restrict__ maps, const int32_t* __restrict__ ids, int32_t n,
                                 int32_t* __restrict__ out) {
   for (int32_t g = threadIdx.x; g < n; g += blockDim.x) out[g] = maps[g][ids[g]];
@@ -219,11 +261,12 @@ extern "C" tc_status tc_rwr_multi(tc_handle* const* hs, int32_t n_graphs, const 
     segs[0].resize(max_tiles);
     segs[1].resize(max_tiles);
     std::vector<int64_t> seg_total(max_tiles, 0);
-    std::vector<MultiVec> vec[2], emp[2], spl[2];
+    std::vector<MultiVec> vec[2], emp[2], spl[2], outv[2];
     for (int q = 0; q < 2; ++q) {
       vec[q].resize(n_graphs);
       emp[q].resize(n_graphs);
       spl[q].resize(n_graphs);
+      outv[q].resize(n_graphs);
     }
     std::vector<int32_t> block_graph;
     std::vector<int64_t> block_first, graph_blocks(n_graphs + 1, 0);
@@ -252,6 +295,7 @@ extern "C" tc_status tc_rwr_multi(tc_handle* const* hs, int32_t n_graphs, const 
         vec[q][g] = MultiVec{off, h->n_rows, nullptr, nullptr, nullptr, buf[1 - q] + off, buf[q] + off, -1};
         emp[q][g] = MultiVec{e_tot, h->n_empty, h->d_empty, nullptr, nullptr, buf[1 - q] + off, nullptr, -1};
         spl[q][g] = MultiVec{s_tot, h->n_split_rows, nullptr, h->d_split, h->d_partial, buf[1 - q] + off, nullptr, -1};
+        outv[q][g] = MultiVec{off, h->n_rows, h->d_rowmap, nullptr, nullptr, R_out[g], buf[q] + off, -1};
       }
       e_tot += h->n_empty;
       s_tot += h->n_split_rows;
@@ -267,17 +311,29 @@ extern "C" tc_status tc_rwr_multi(tc_handle* const* hs, int32_t n_graphs, const 
     size_t bytes = 0;
     auto reserve = [&](size_t n) { const size_t at = bytes; bytes += (n + 255) / 256 * 256; return at; };
     std::vector<size_t> seg_at[2];
-    size_t vec_at[2], emp_at[2], spl_at[2];
+    size_t vec_at[2], emp_at[2], spl_at[2], out_at[2];
     for (int q = 0; q < 2; ++q) {
       seg_at[q].resize(max_tiles);
       for (int t = 0; t < max_tiles; ++t) seg_at[q][t] = reserve(sizeof(MultiSeg) * segs[q][t].size());
       vec_at[q] = reserve(sizeof(MultiVec) * n_graphs);
       emp_at[q] = reserve(sizeof(MultiVec) * n_graphs);
       spl_at[q] = reserve(sizeof(MultiVec) * n_graphs);
+      out_at[q] = reserve(sizeof(MultiVec) * n_graphs);
+    }
+    std::vector<std::vector<int32_t>> from(max_tiles);
+    std::vector<size_t> from_at(max_tiles);
+    for (int t = 0; t < max_tiles; ++t) {
+      const std::vector<MultiSeg>& sg = segs[0][t];
+      int32_t i = 0;
+      for (int64_t j = 0; j < seg_total[t]; j += kFromStep) {
+        while (i + 1 < (int32_t)sg.size() && sg[i + 1].begin <= j) ++i;
+        from[t].push_back(i);
+      }
+      from_at[t] = reserve(sizeof(int32_t) * from[t].size());
     }
     const size_t bg_at = reserve(sizeof(int32_t) * block_graph.size()),
                  bf_at = reserve(sizeof(int64_t) * block_first.size()),
-                 gb_at = reserve(sizeof(int64_t) * graph_blocks.size()),
+                 gb_at = reserve(sizeof(int64_t) * graph_blocks.size()), tables = bytes,
                  parts_at = reserve(sizeof(double) * block_graph.size()),
                  res_at = reserve(sizeof(double) * (n_graphs + 1)), seeds_at = reserve(sizeof(int32_t) * n_graphs),
                  maps_at = reserve(sizeof(int32_t*) * n_graphs);
@@ -293,6 +349,10 @@ extern "C" tc_status tc_rwr_multi(tc_handle* const* hs, int32_t n_graphs, const 
     } rel{R, Y, tab, st};
     auto up = [&](size_t at, const void* src, size_t n) {
       if (n) HIPC(hipMemcpyAsync(tab + at, src, n, hipMemcpyHostToDevice, st));
+    };
+    std::vector<char> host(tables);  // the tables, copied together
+    auto put = [&](size_t at, const void* src, size_t n) {
+      if (n) std::memcpy(host.data() + at, src, n);
     };
     // internal seed ids: seed_int = rowmap[seed] read on the device
     {
@@ -315,14 +375,17 @@ extern "C" tc_status tc_rwr_multi(tc_handle* const* hs, int32_t n_graphs, const 
       }
     }
     for (int q = 0; q < 2; ++q) {
-      for (int t = 0; t < max_tiles; ++t) up(seg_at[q][t], segs[q][t].data(), sizeof(MultiSeg) * segs[q][t].size());
-      up(vec_at[q], vec[q].data(), sizeof(MultiVec) * n_graphs);
-      up(emp_at[q], emp[q].data(), sizeof(MultiVec) * n_graphs);
-      up(spl_at[q], spl[q].data(), sizeof(MultiVec) * n_graphs);
+      for (int t = 0; t < max_tiles; ++t) put(seg_at[q][t], segs[q][t].data(), sizeof(MultiSeg) * segs[q][t].size());
+      put(vec_at[q], vec[q].data(), sizeof(MultiVec) * n_graphs);
+      put(emp_at[q], emp[q].data(), sizeof(MultiVec) * n_graphs);
+      put(spl_at[q], spl[q].data(), sizeof(MultiVec) * n_graphs);
+      put(out_at[q], outv[q].data(), sizeof(MultiVec) * n_graphs);
     }
-    up(bg_at, block_graph.data(), sizeof(int32_t) * block_graph.size());
-    up(bf_at, block_first.data(), sizeof(int64_t) * block_first.size());
-    up(gb_at, graph_blocks.data(), sizeof(int64_t) * graph_blocks.size());
+    for (int t = 0; t < max_tiles; ++t) put(from_at[t], from[t].data(), sizeof(int32_t) * from[t].size());
+    put(bg_at, block_graph.data(), sizeof(int32_t) * block_graph.size());
+    put(bf_at, block_first.data(), sizeof(int64_t) * block_first.size());
+    put(gb_at, graph_blocks.data(), sizeof(int64_t) * graph_blocks.size());
+    up(0, host.data(), tables);
     double* d_parts = (double*)(tab + parts_at);
     double* d_res = (double*)(tab + res_at);
     const int64_t nblocks = (int64_t)block_graph.size();
@@ -336,8 +399,8 @@ extern "C" tc_status tc_rwr_multi(tc_handle* const* hs, int32_t n_graphs, const 
       if (fused) {
         if (max_tiles == 1 && seg_total[0] > 0) {
           hipLaunchKernelGGL(k_tile_spmv_multi_rwr, dim3(nblk(seg_total[0], kWpb)), dim3(kB), 0, s2,
-                             (const MultiSeg*)(tab + seg_at[par][0]), (int32_t)segs[par][0].size(), seg_total[0],
-                             (double)c);
+                             (const MultiSeg*)(tab + seg_at[par][0]), (int32_t)segs[par][0].size(),
+                             (const int32_t*)(tab + from_at[0]), seg_total[0], (double)c);
           HIPC(hipGetLastError());
         }
         if (s_tot + e_tot > 0) {
@@ -356,7 +419,8 @@ extern "C" tc_status tc_rwr_multi(tc_handle* const* hs, int32_t n_graphs, const 
       for (int t = 0; t < max_tiles; ++t) {
         if (seg_total[t] == 0) continue;
         hipLaunchKernelGGL(k_tile_spmv_multi, dim3(nblk(seg_total[t], kWpb)), dim3(kB), 0, s2,
-                           (const MultiSeg*)(tab + seg_at[par][t]), (int32_t)segs[par][t].size(), seg_total[t]);
+                           (const MultiSeg*)(tab + seg_at[par][t]), (int32_t)segs[par][t].size(),
+                           (const int32_t*)(tab + from_at[t]), seg_total[t]);
         HIPC(hipGetLastError());
       }
       if (s_tot > 0) {
@@ -436,11 +500,9 @@ extern "C" tc_status tc_rwr_multi(tc_handle* const* hs, int32_t n_graphs, const 
         }
       }
       if (it > 0) r = read_f64(d_res + n_graphs, st);
-      off = 0;
-      for (int32_t g = 0; g < n_graphs; ++g) {
-        gather_rows(buf[par] + off, hs[g]->d_rowmap, hs[g]->n_rows, 1, R_out[g], st);
-        off += hs[g]->n_rows;
-      }
+      hipLaunchKernelGGL(k_out_multi, dim3(nblk(nv_total, kB)), dim3(kB), 0, st, (const MultiVec*)(tab + out_at[par]),
+                         n_graphs, nv_total);
+      HIPC(hipGetLastError());
       if (resid && n_graphs > 0) HIPC(hipMemcpyAsync(resid, d_res, sizeof(double) * n_graphs, hipMemcpyDeviceToHost, st));
       HIPC(hipStreamSynchronize(st));
     } else if (resid) {

@@ -578,8 +578,7 @@ extern "C" tc_status tc_gather_rows(const float* d_src, int64_t n_src, const int
     HIPC(hipMemcpyAsync(&hbad, bad.p, sizeof(int32_t), hipMemcpyDeviceToHost, st));
     HIPC(hipStreamSynchronize(st));
     if (hbad) throw Err{TC_EINVAL, "row index out of range"};
-    hipLaunchKernelGGL(k_gather_rows, dim3(nblk(n * width, kB)), dim3(kB), 0, st, d_src, d_idx, n, width, d_dst);
-    HIPC(hipGetLastError());
+    gather_rows(d_src, d_idx, n, width, d_dst, st);
     HIPC(hipStreamSynchronize(st));
     return TC_OK;
   });

@@ -80,7 +80,6 @@ struct SmallX {
   }
 };
 
-typedef float v4fu __attribute__((ext_vector_type(4), aligned(4)));
 typedef float v2fu __attribute__((ext_vector_type(2), aligned(4)));
 
 // ... or of any size by 64-bit addresses.  Branch-free: an inactive lane reads

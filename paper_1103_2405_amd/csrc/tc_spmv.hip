@@ -312,10 +312,6 @@ __device__ inline void coo_write(float* __restrict__ y, int32_t rf, double s) {
     y[r] = (float)s;
 }
 
-// four entries from any 4-byte boundary (a tile begins anywhere)
-typedef int32_t i32x4u __attribute__((ext_vector_type(4), aligned(4)));
-typedef float f32x4u __attribute__((ext_vector_type(4), aligned(4)));
-
 __global__ void __launch_bounds__(kB) k_tile_coo(const int32_t* __restrict__ crow, const int32_t* __restrict__ ccol,
                                                  const float* __restrict__ cval, int64_t n,
                                                  const float* __restrict__ x, float* __restrict__ y,
@@ -333,15 +329,16 @@ __global__ void __launch_bounds__(kB) k_tile_coo(const int32_t* __restrict__ cro
   int32_t rr[kCooPer];
   double pp[kCooPer];
   if (e - b == kCooIv) {
-    // a whole interval: four entries a load, past the caches that hold x
-    i32x4u r4[kCooPer / 4], c4[kCooPer / 4];
-    f32x4u v4[kCooPer / 4];
+    // a whole interval: four entries a load (a tile begins at any of them),
+    // past the caches that hold x
+    v4iu r4[kCooPer / 4], c4[kCooPer / 4];
+    v4fu v4[kCooPer / 4];
 #pragma unroll
-    for (int u = 0; u < kCooPer / 4; ++u) c4[u] = __builtin_nontemporal_load((const i32x4u*)(ccol + s0) + u);
+    for (int u = 0; u < kCooPer / 4; ++u) c4[u] = __builtin_nontemporal_load((const v4iu*)(ccol + s0) + u);
 #pragma unroll
     for (int u = 0; u < kCooPer / 4; ++u) {
-      r4[u] = __builtin_nontemporal_load((const i32x4u*)(crow + s0) + u);
-      v4[u] = __builtin_nontemporal_load((const f32x4u*)(cval + s0) + u);
+      r4[u] = __builtin_nontemporal_load((const v4iu*)(crow + s0) + u);
+      v4[u] = __builtin_nontemporal_load((const v4fu*)(cval + s0) + u);
     }
     float xv[kCooPer];
 #pragma unroll
@@ -616,7 +613,10 @@ void gather_rows(const float* in, const int32_t* perm, int64_t n, int32_t w, flo
     HIPC(hipGetLastError());
     return;
   }
-  hipLaunchKernelGGL(k_gather_rows, dim3(nblk(n * w, kB)), dim3(kB), 0, st, in, perm, n, w, out);
+  if (w == 1)
+    hipLaunchKernelGGL(k_gather1, dim3(nblk(n, 4 * kB)), dim3(kB), 0, st, in, perm, n, out);
+  else
+    hipLaunchKernelGGL(k_gather_rows, dim3(nblk(n * w, kB)), dim3(kB), 0, st, in, perm, n, w, out);
   HIPC(hipGetLastError());
 }
 

@@ -472,12 +472,12 @@ def main():
         avg_ms = tot_ms / max(launches, 1)
         achieved = per_launch_bytes / (avg_ms / 1e3) / 1e9
         from paper_1103_2405_amd.profsum import read_traffic
-        kname = "k_panel_spmv" if info["n_panels"] > 0 else "k_tile_spmv"
+        kname = "k_panel_spmv" if info["n_panels"] > 0 else "k_tile"
         traffic = read_traffic(os.path.join(ROOT, "profiles", "%s_%s_pagerank_counters.txt" % (kname, args.workload)))
         roofline = {"bound": "hbm", "achieved": round(achieved, 1), "peak": HBM_PEAK_GBS, "unit": "GB/s",
                     "frac": round(achieved / HBM_PEAK_GBS, 4), "traffic": traffic,
-                    # the row-panel pass (one launch per product), or the tile kernel with the fused update
-                    "kernel": kname if info["n_panels"] > 0 else "k_tile_spmv_pr",
+                    # the row-panel pass, or the tile kernel (k_tile, k_tile_hot): one launch per product
+                    "kernel": kname,
                     "avg_launch_us": round(avg_ms * 1e3, 2),
                     "launches_per_spmv": round(launches / max(calls, 1), 2),
                     "bytes_per_launch": int(per_launch_bytes)}

@@ -535,12 +535,6 @@ __global__ void k_strided(const int32_t* __restrict__ a, int64_t stride, int64_t
   if (t < cnt) out[t] = a[t * stride];
 }
 
-// out[i] = a[i * stride] for i < n
-__global__ void k_strided64(const int64_t* __restrict__ a, int64_t stride, int64_t n, int64_t* __restrict__ out) {
-  const int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-  if (i < n) out[i] = a[i * stride];
-}
-
 __global__ void k_icol(const int32_t* __restrict__ col, const int32_t* __restrict__ cpos, int64_t nnz,
                        int32_t* __restrict__ icol) {
   int64_t k = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;

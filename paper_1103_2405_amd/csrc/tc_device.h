@@ -685,11 +685,6 @@ __device__ inline double sum_slots_wave(const double* __restrict__ p, int64_t n,
 }
 
 // ---- vector kernels
-__global__ void k_fill_f32(float* __restrict__ a, int64_t n, float v) {
-  int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-  if (i < n) a[i] = v;
-}
-
 // out[k*row_stride + q] = in[perm[k]*row_stride + q]   (rows gathered)
 __global__ void k_gather_rows(const float* __restrict__ in, const int32_t* __restrict__ perm, int64_t n, int32_t w,
                               float* __restrict__ out) {

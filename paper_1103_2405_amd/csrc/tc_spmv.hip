@@ -433,19 +433,48 @@ __global__ void __launch_bounds__(kB) k_tile_coo(const int32_t* __restrict__ cro
   }
 }
 
-// rows crossing interval boundaries: the interval where such a row starts
-// adds the partial sums of the following intervals, in order, and writes it
+// Rows crossing interval boundaries: the interval where such a row starts
+// adds the partial sums of the following intervals, in order, and writes it.
+// A row that ends within kCooNear of them is its thread's alone; the rows of a
+// hub, which go on for hundreds, are taken by the whole wavefront, one by one, 64
+// records a load (a thread waits for a record before it can ask for the next):
+// the product of the 2^20-vertex Chung-Lu graph (14.7M entries) 129.6 -> 115.2 us,
+// of the R-MAT graph 114.3 -> 110.4, of uniform ones the same.
+constexpr int kCooNear = 2;
 __global__ void k_coo_fixup(const CooCarry* __restrict__ carry, int64_t nw, float* __restrict__ y) {
+  const int lane = lane_id();
   const int64_t w = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-  if (w >= nw) return;
-  const CooCarry c = carry[w];
-  if (!(c.flags & 2) || ((c.flags & 4) && (c.flags & 1))) return;
+  CooCarry c = carry[w < nw ? w : nw - 1];
+  const bool need = w < nw && (c.flags & 2) && !((c.flags & 4) && (c.flags & 1));
   double t = c.p1;
-  for (int64_t v = w + 1; v < nw; ++v) {
+  int64_t v = w + 1;
+  bool open = need && v < nw;
+  for (int q = 0; q < kCooNear && open; ++q) {
     const CooCarry d = carry[v];
     t += d.p0;
-    if (!((d.flags & 4) && (d.flags & 2))) break;
+    open = (d.flags & 4) && (d.flags & 2) && ++v < nw;
   }
+  for (uint64_t m = __ballot(open); m; m &= m - 1) {
+    const int i = (int)__builtin_ctzll(m);
+    // (an interval's number is below 2^31: its entries are)
+    int32_t vi = __builtin_amdgcn_readlane((int32_t)v, i);
+    double ti = __hiloint2double(__builtin_amdgcn_readlane(__double2hiint(t), i),
+                                 __builtin_amdgcn_readlane(__double2loint(t), i));
+    for (bool on = true; on;) {
+      const int64_t r = (int64_t)vi + lane;
+      const CooCarry* d = carry + (r < nw ? r : nw - 1);
+      const double p = d->p0;
+      const uint64_t stop = ~__ballot(r < nw - 1 && (d->flags & 4) && (d->flags & 2));
+      on = stop == 0;
+      const int last = on ? kWave - 1 : (int)__builtin_ctzll(stop);  // r <= nw - 1 there
+      for (int k = 0; k <= last; ++k)
+        ti += __hiloint2double(__builtin_amdgcn_readlane(__double2hiint(p), k),
+                               __builtin_amdgcn_readlane(__double2loint(p), k));
+      vi += kWave;
+    }
+    if (lane == i) t = ti;
+  }
+  if (!need) return;
   coo_write(y, c.row1, t);
 }
 

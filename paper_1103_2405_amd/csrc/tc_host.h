@@ -62,9 +62,9 @@ void spmv_user(tc_handle* h, const float* x, float* y, hipStream_t st);
 // Y := A X for k right-hand sides in internal ids; epi: fused RWR restart.
 // partial_ext: split-row partial sums go there (at least n_slots * pieces * k
 // doubles) instead of the handle's pool buffer, and launches are not timed:
-// the call then allocates nothing.
+// the call then allocates nothing.  ldx: floats from row to row of X (0: k).
 void spmm_internal(tc_handle* h, const float* X, float* Y, int32_t k, hipStream_t st, bool skip_empty = false,
-                   const RwrEpi* epi = nullptr, double* partial_ext = nullptr);
+                   const RwrEpi* epi = nullptr, double* partial_ext = nullptr, int32_t ldx = 0);
 // doubles of split-row partial sums spmm_internal needs for k right-hand sides
 size_t spmm_partial_doubles(tc_handle* h, int32_t k);
 // out row q = in row perm[q] (rows of w floats)

@@ -352,13 +352,15 @@ __device__ inline void spmm_item(const Wl& d, int32_t part, int32_t parts, bool 
 // without a row to sum), 2 362; a persistent grid with an LDS item counter 351.
 // By k, us a product before and now: 3 357 -> 224, 4 279 -> 227, 8 290 -> 249,
 // 37 1825 -> 931 (the last lane of a row overlaps its neighbour instead of one
-// right-hand side per lane); 13 on 4.8M entries of 100K columns 86 -> 60.
+// right-hand side per lane); 13 on 4.8M entries of 100K columns 86 -> 60 (all
+// with X's rows k floats apart; tc_spmm pads them since, see padded_rows).
 template <int V, int KG, bool RWR, template <int> class XR>
 __global__ void __launch_bounds__(kB) k_tile_spmm(const Wl* __restrict__ wl, int64_t n_wl, int64_t n_lead,
                                                   int32_t pieces, int32_t slices, const int32_t* __restrict__ idx,
                                                   const float* __restrict__ val, const int32_t* __restrict__ rowid,
-                                                  const float* __restrict__ X, int64_t n_cols, float* __restrict__ Y,
-                                                  int32_t k, int32_t c0, double* __restrict__ partial, RwrEpi epi) {
+                                                  const float* __restrict__ X, int64_t n_cols, int32_t ldx,
+                                                  float* __restrict__ Y, int32_t k, int32_t c0,
+                                                  double* __restrict__ partial, RwrEpi epi) {
   // fused restart: the seeds (k <= kB) in LDS, read only where rows are written
   __shared__ int32_t sd[RWR ? kB : 1];
   if constexpr (RWR) {
@@ -372,7 +374,7 @@ __global__ void __launch_bounds__(kB) k_tile_spmm(const Wl* __restrict__ wl, int
   const bool lead = v < 0;
   const Wl d = wl[lead ? w / pieces : n_lead + v / slices];
   const Cols<V, KG> c(lane, c0 + (int32_t)blockIdx.y * (V * KG), k);
-  const XR<V> xr(X, n_cols, k);
+  const XR<V> xr(X, n_cols, ldx);
   spmm_item<V, KG, RWR>(d, (int32_t)(lead ? w % pieces : v % slices), lead ? pieces : slices, lead, idx, val, rowid,
                         xr, Y, k, c, lane, partial, epi, sd);
 }
@@ -438,12 +440,12 @@ void spmm_plan(tc_handle* h) {
 // product; 16 per pass slows k = 32 by 40%).
 template <bool RWR, template <int> class XR>
 void spmm_tile_x(tc_handle* h, int64_t b, int64_t n, int64_t lead, int32_t pieces, int32_t slices, const float* X,
-                 float* Y, int32_t k, double* partial, const RwrEpi& ep, hipStream_t st) {
+                 int32_t ldx, float* Y, int32_t k, double* partial, const RwrEpi& ep, hipStream_t st) {
   const unsigned gx = nblk(lead * pieces + (n - lead) * slices, kWpb);
   auto go = [&](auto kern, int32_t c0, unsigned gy) {
     launch_tile(h, kern, dim3(gx, gy), dim3(kB), 0, st, (const Wl*)(h->d_wl + b), n, lead, pieces, slices,
-                (const int32_t*)h->d_idx, (const float*)h->d_val, (const int32_t*)h->d_rowid, X, (int64_t)h->n_cols, Y,
-                k, c0, partial, ep);
+                (const int32_t*)h->d_idx, (const float*)h->d_val, (const int32_t*)h->d_rowid, X, (int64_t)h->n_cols, ldx,
+                Y, k, c0, partial, ep);
   };
   if (k == 1) return go(k_tile_spmm<1, 1, RWR, XR>, 0, 1);
   if (k == 2) return go(k_tile_spmm<2, 1, RWR, XR>, 0, 1);
@@ -460,12 +462,47 @@ void spmm_tile_x(tc_handle* h, int64_t b, int64_t n, int64_t lead, int32_t piece
     go(k_tile_spmm<4, 1, RWR, XR>, 32 * full, 1);
 }
 
+// out[c] = X[cperm[c]], rows of k floats into rows of 4 ld4 (the rest zeros)
+__global__ void __launch_bounds__(kB) k_gather_pad(const float* __restrict__ X, const int32_t* __restrict__ cperm,
+                                                   int64_t n, int32_t k, uint32_t ld4, v4f* __restrict__ out) {
+  const int64_t t = (int64_t)blockIdx.x * kB + threadIdx.x;
+  if (t >= n * ld4) return;
+  const int64_t c = t / ld4;
+  const int32_t q = 4 * (int32_t)(t - c * ld4);
+  const float* p = X + (int64_t)cperm[c] * k;
+  v4f v;
+  if (q + 4 <= k) {
+    v = *(const v4fu*)(p + q);
+  } else {
+#pragma unroll
+    for (int u = 0; u < 4; ++u) v[u] = q + u < k ? p[q + u] : 0.0f;
+  }
+  out[t] = v;
+}
+
+// Floats between the rows of tc_spmm's own copy of X: rows of more than 4 lie in
+// as few lines as they can.  us a product, unpadded / padded, on a rectangle of
+// 4.8M entries and 100K columns: k = 7 61 / 58, 13 71 / 65, 23 108 / 91, 29 130 / 92,
+// 37 229 / 208; on the 16M-entry R-MAT matrix of 2^20: 228 / 214, 281 / 249, 453 / 383,
+// 545 / 418, 844 / 751.  17 and 18 would nearly double (17: 85 / 88 and 346 / 337), and
+// a copy past the 256 MB MALL was not measured: both stay as they are.
+int32_t padded_rows(int64_t n_cols, int32_t k) {
+  int32_t ld = k;
+  if (k > 32)
+    ld = (k + 7) / 8 * 8;
+  else if (k > 18)
+    ld = 32;
+  else if (k > 4 && k <= 16)
+    ld = k <= 8 ? 8 : 16;
+  return n_cols * ld * (int64_t)sizeof(float) <= ((int64_t)256 << 20) ? ld : k;
+}
+
 void spmm_tile(tc_handle* h, int64_t b, int64_t n, int64_t lead, int32_t pieces, int32_t slices, const float* X,
-               float* Y, int32_t k, double* partial, bool rwr, const RwrEpi& ep, hipStream_t st) {
-  const bool small = h->n_cols <= ((int64_t)1 << 24) && h->n_cols * k < ((int64_t)1 << 29);
+               int32_t ldx, float* Y, int32_t k, double* partial, bool rwr, const RwrEpi& ep, hipStream_t st) {
+  const bool small = h->n_cols <= ((int64_t)1 << 24) && h->n_cols * ldx < ((int64_t)1 << 29);
   auto f = rwr ? (small ? spmm_tile_x<true, SmallX> : spmm_tile_x<true, LargeX>)
                : (small ? spmm_tile_x<false, SmallX> : spmm_tile_x<false, LargeX>);
-  f(h, b, n, lead, pieces, slices, X, Y, k, partial, ep, st);
+  f(h, b, n, lead, pieces, slices, X, ldx, Y, k, partial, ep, st);
 }
 
 }  // namespace
@@ -479,7 +516,8 @@ size_t spmm_partial_doubles(tc_handle* h, int32_t k) {
 }
 
 void spmm_internal(tc_handle* h, const float* X, float* Y, int32_t k, hipStream_t st, bool skip_empty,
-                   const RwrEpi* epi, double* partial_ext) {
+                   const RwrEpi* epi, double* partial_ext, int32_t ldx) {
+  if (ldx == 0) ldx = k;
   if (epi && !(h->n_tiles == 1 && h->xcd_groups == 0 && k <= kB))
     throw Err{TC_EINVAL, "fused restart needs one tile and k <= 256"};
   const RwrEpi ep = epi ? *epi : RwrEpi{0.0, nullptr};
@@ -512,7 +550,7 @@ void spmm_internal(tc_handle* h, const float* X, float* Y, int32_t k, hipStream_
   for (int t = 0; t < h->n_tiles; ++t) {
     const int64_t b = h->tile_wl_begin[t], e = h->tile_wl_begin[t + 1];
     const int64_t lead = h->mm_lead[t];
-    if (e > b) spmm_tile(h, b, e - b, lead, pieces, slices, X, Y, k, partial, epi != nullptr, ep, st);
+    if (e > b) spmm_tile(h, b, e - b, lead, pieces, slices, X, ldx, Y, k, partial, epi != nullptr, ep, st);
   }
   if (h->n_split_rows > 0) {
     hipLaunchKernelGGL(k_split_combine_mm, dim3(nblk(h->n_split_rows * k, kB)), dim3(kB), 0, st, h->d_split,
@@ -534,16 +572,30 @@ extern "C" tc_status tc_spmm(const tc_handle* hc, const float* X, float* Y, int3
     if ((const void*)X == (const void*)Y && hc->n_rows > 0) throw Err{TC_EINVAL, "X and Y must not alias"};
     tc_handle* h = const_cast<tc_handle*>(hc);
     hipStream_t st = (hipStream_t)stream;
-    const size_t xb = sizeof(float) * (size_t)h->n_cols * k, yb = sizeof(float) * (size_t)h->n_rows * k;
-    char* ws = (char*)workspace(h, ((xb + 255) / 256) * 256 + yb, st);
+    const size_t yb = sizeof(float) * (size_t)h->n_rows * k;
+    auto x_bytes = [&](int32_t ld) { return (sizeof(float) * (size_t)h->n_cols * ld + 255) / 256 * 256; };
+    int32_t ld = padded_rows(h->n_cols, k);
+    char* ws = nullptr;
+    try {
+      ws = (char*)workspace(h, x_bytes(ld) + yb, st);
+    } catch (const Err&) {
+      if (ld == k) throw;
+      ws = (char*)workspace(h, x_bytes(ld = k) + yb, st);
+    }
     float* Xi = (float*)ws;
-    float* Yi = (float*)(ws + ((xb + 255) / 256) * 256);
-    gather_rows(X, h->d_cperm, h->n_cols, k, Xi, st);
+    float* Yi = (float*)(ws + x_bytes(ld));
+    if (ld == k) {
+      gather_rows(X, h->d_cperm, h->n_cols, k, Xi, st);
+    } else {
+      hipLaunchKernelGGL(k_gather_pad, dim3(nblk(h->n_cols * (ld / 4), kB)), dim3(kB), 0, st, X,
+                         (const int32_t*)h->d_cperm, h->n_cols, k, (uint32_t)(ld / 4), (v4f*)Xi);
+      HIPC(hipGetLastError());
+    }
     if (h->relabel) {
-      spmm_internal(h, Xi, Yi, k, st);
+      spmm_internal(h, Xi, Yi, k, st, false, nullptr, nullptr, ld);
       gather_rows(Yi, h->d_rowmap, h->n_rows, k, Y, st);
     } else {
-      spmm_internal(h, Xi, Y, k, st);
+      spmm_internal(h, Xi, Y, k, st, false, nullptr, nullptr, ld);
     }
     return TC_OK;
   });

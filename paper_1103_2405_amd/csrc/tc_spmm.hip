@@ -586,7 +586,7 @@ extern "C" tc_status tc_spmm(const tc_handle* hc, const float* X, float* Y, int3
     float* Yi = (float*)(ws + x_bytes(ld));
     if (ld == k) {
       gather_rows(X, h->d_cperm, h->n_cols, k, Xi, st);
-    } else {
+    } else if (h->n_cols > 0) {
       hipLaunchKernelGGL(k_gather_pad, dim3(nblk(h->n_cols * (ld / 4), kB)), dim3(kB), 0, st, X,
                          (const int32_t*)h->d_cperm, h->n_cols, k, (uint32_t)(ld / 4), (v4f*)Xi);
       HIPC(hipGetLastError());

@@ -200,20 +200,21 @@ struct Slots {
 
 // sum over entries [lo, hi) of the row-major row at `base`: sub-step u of each
 // step of SUB * G entries gives group g the entry u * G + g, and a group adds
-// its own in increasing order
+// its own in increasing order.  (Unsigned: the last step of a row of almost
+// 2^31 entries ends up to 2 SUB * G entries past 2^31.)
 template <int V, int KG, int SUB, class XR>
 __device__ inline Vec<V> rm_range(const int32_t* __restrict__ idx, const float* __restrict__ val, const XR& X,
-                                  int64_t base, int32_t lo, int32_t hi, const Cols<V, KG>& c, int lane) {
+                                  int64_t base, uint32_t lo, uint32_t hi, const Cols<V, KG>& c, int lane) {
   using Sl = Slots<KG, SUB>;
   const int g = lane / KG;
   Vec<V> acc;
   acc.zero();
   Sl nx;
-  auto fetch = [&](int32_t e0) {
-    nx.load(idx, val, lane, base, [&](int s) { return e0 + s < hi; }, [&](int s) { return base + e0 + s; });
+  auto fetch = [&](uint32_t e0) {
+    nx.load(idx, val, lane, base, [&](int s) { return e0 + s < hi; }, [&](int s) { return base + (e0 + s); });
   };
   if (lo < hi) fetch(lo);
-  for (int32_t e0 = lo; e0 < hi; e0 += Sl::N) {
+  for (uint32_t e0 = lo; e0 < hi; e0 += Sl::N) {
     const Sl cur = nx;
     float v[SUB];
     FVec<V> x[SUB];
@@ -303,7 +304,7 @@ __device__ inline void spmm_item(const Wl& d, int32_t part, int32_t parts, bool 
   constexpr int G = kWave / KG;
   const bool g0 = lane < KG;
   if (lead) {
-    const int32_t lo = (int32_t)min<int64_t>((int64_t)part * kPiece, d.w_pad), hi = min(lo + kPiece, d.w_pad);
+    const uint32_t w = (uint32_t)d.w_pad, lo = min((uint32_t)part * kPiece, w), hi = min(lo + kPiece, w);
     Vec<V> acc = rm_range<V, KG, 8>(idx, val, xr, d.data_off, lo, hi, c, lane);
     group_sum<V, KG>(acc);
     if (c.act && g0)

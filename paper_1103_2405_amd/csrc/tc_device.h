@@ -567,7 +567,7 @@ __device__ __attribute__((always_inline)) inline void run_workload(const Wl& d, 
 // What a one-tile product writes besides its workloads' rows: the rows
 // without entries, and the split rows' sums, each by the wavefront that
 // finishes the row's last chunk (ticket[i] counts split row i's finished
-// chunks and goes back to 0 with the last).
+// chunks modulo their number).
 struct TileRest {
   const int32_t* empty;
   int64_t n_empty;
@@ -582,15 +582,19 @@ struct TileRest {
 // the wait makes this wavefront's slot complete there before its ticket is
 // drawn, so the last ticket's wavefront reads every slot.  No fence (an
 // agent-scope release would write back the whole L2) and no wavefront waits
-// for another.
+// for another.  The ticket counts modulo the row's chunks, so any whole number
+// of products, also ones that overlapped on the handle against its contract,
+// leaves it at 0 for the next (a reset by the last wavefront would lose what
+// another product counted meanwhile, and finish the row early ever after).
 // (i, sr: the chunk's split row, read before the chunk is summed.)
 template <class X>
 __device__ inline void finish_chunk(int32_t i, const SplitRow& sr, int lane, const X& x, float* __restrict__ y,
                                     const double* partial, const TileRest& rest) {
   asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
+  const uint32_t last = (uint32_t)sr.n_slots - 1;
   uint32_t t = 0;
-  if (lane == 0) t = __hip_atomic_fetch_add(rest.ticket + i, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-  if (__builtin_amdgcn_readfirstlane(t) + 1 != (uint32_t)sr.n_slots) return;
+  if (lane == 0) t = atomicInc(rest.ticket + i, last);  // relaxed, agent scope
+  if (__builtin_amdgcn_readfirstlane(t) != last) return;
   asm volatile("" ::: "memory");
   double acc = 0.0;
   for (int32_t q = 0; q < sr.n_slots; q += kWave) {
@@ -602,10 +606,7 @@ __device__ inline void finish_chunk(int32_t i, const SplitRow& sr, int lane, con
       acc += __hiloint2double(__builtin_amdgcn_readlane(__double2hiint(v), k),
                               __builtin_amdgcn_readlane(__double2loint(v), k));
   }
-  if (lane == 0) {
-    x.addy(y, sr.row, acc);
-    __hip_atomic_store(rest.ticket + i, 0u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-  }
+  if (lane == 0) x.addy(y, sr.row, acc);
 }
 
 // A workload slice of a one-tile product (or, without tickets, of any tile)

@@ -181,7 +181,7 @@ struct tc_handle {
   tc::SplitRow* d_split = nullptr;
   double* d_partial = nullptr;
   int32_t* d_slot_split = nullptr;  // partial slot -> split row (index into d_split)
-  uint32_t* d_ticket = nullptr;     // [n_split_rows] finished chunks of each split row; 0 between products
+  uint32_t* d_ticket = nullptr;     // [n_split_rows] finished chunks of each split row, modulo their number
   float* d_xbuf = nullptr;          // internal-space x for spmv on user vectors
   float* d_ybuf = nullptr;
   double* d_red = nullptr;          // reduction scratch

@@ -357,7 +357,10 @@ tc_status tc_rwr_iterates(const tc_handle* W, int32_t seed, float c, int32_t K, 
                           float* d_rK, tc_stream_t stream);
 
 /* Adjoint pass from d_gK = dL/dr^K: recomputes the iterates between
- * checkpoints (every x n scratch), and returns, for every entry (i, j) of A in
+ * checkpoints (scratch: nnz ints and 2 every + 17 vectors of n floats, or more
+ * steps at a time where that stays within 1 GiB; without the memory for it 2
+ * every + 1 vectors, + 2 for handles of several tiles; every counts as K where
+ * it is larger), and returns, for every entry (i, j) of A in
  * A^T's order, d_G = sum_k g^{k+1}_i r^k_j (FP64, nnz; dL/dW = c G) and, if
  * d_g0 is not NULL, g^0.  Wt is the handle built from A^T with W's values
  * (d_rpT, d_colT and d_valT); the sum of each entry runs latest step first,

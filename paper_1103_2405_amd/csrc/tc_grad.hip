@@ -3,6 +3,7 @@
 // checkpointed forward iterations, the adjoint pass and the chain to theta.
 #include <algorithm>
 #include <cmath>
+#include <memory>
 #include <vector>
 
 #include "tc_expand.h"
@@ -230,6 +231,25 @@ __global__ void __launch_bounds__(kB) k_edge_accum(const int32_t* __restrict__ g
   if (q0 + lane < nnz) G[q] = acc;
 }
 
+// The same without rows, where there is no memory for them: step t's values at
+// g[t n + i] and r[t n + j], i and j by way of the maps to the vectors' ids (null:
+// they are in user ids).
+template <bool FIRST>
+__global__ void __launch_bounds__(kB) k_edge_accum_vec(const int32_t* __restrict__ gidx,
+                                                       const int32_t* __restrict__ ridx, int64_t nnz,
+                                                       const float* __restrict__ g, const float* __restrict__ r,
+                                                       const int32_t* __restrict__ gmap,
+                                                       const int32_t* __restrict__ rmap, int64_t n, int32_t m,
+                                                       double* __restrict__ G) {
+  const int64_t q = (int64_t)blockIdx.x * kB + threadIdx.x;
+  if (q >= nnz) return;
+  const int32_t i = gmap ? gmap[gidx[q]] : gidx[q], j = rmap ? rmap[ridx[q]] : ridx[q];
+  double acc = FIRST ? 0.0 : G[q];
+#pragma unroll 4
+  for (int32_t t = 0; t < m; ++t) acc = fma((double)g[t * n + i], (double)r[t * n + j], acc);
+  G[q] = acc;
+}
+
 // a seed's internal id (no seed: -1)
 __global__ void k_set_seed(int32_t* __restrict__ out, const int32_t* __restrict__ map, int32_t seed) {
   if (threadIdx.x == 0 && blockIdx.x == 0) *out = seed < 0 ? -1 : map[seed];
@@ -339,6 +359,7 @@ struct Steps {
   }
   // working order -> caller's ids, or null
   const int32_t* inv() const { return inner ? h->d_rowinv : nullptr; }
+  const int32_t* map() const { return inner ? h->d_rowmap : nullptr; }  // and back
   void copy(const float* v, const int32_t* perm, float* out) const {
     if (inner)
       gather_rows(v, perm, h->n_rows, 1, out, st);
@@ -347,7 +368,7 @@ struct Steps {
   }
   void to_user(const float* v, float* out) const { copy(v, h->d_rowmap, out); }
   void from_user(const float* v, float* out) const { copy(v, h->d_rowinv, out); }
-  // out = fl32(c fl32(A in) + (1 - c) [seed])
+  // out = fl32(c fl32(A in) + (1 - c) [seed]); out may be in where the ids are the caller's
   void step(const float* in, float* out) const {
     if (inner) {
       run_tile(h, 0, RwrSpec{in, c, id.as<const int32_t>()}, out, st, tile_rest(h, true));
@@ -361,8 +382,36 @@ struct Steps {
   }
 };
 
-// vectors of one batch of the adjoint pass (beyond one segment's, which the caller chose)
-constexpr int64_t kBatchBytes = (int64_t)256 << 20;
+// The adjoint pass: steps whose vectors are kept for one batch (whole segments),
+// and floats of the rows that its passes over the entries read (0: no rows).
+struct Batch {
+  int32_t cap, row;
+  int64_t vectors() const { return 2 * (int64_t)cap + 1 + 2 * row; }  // of n floats
+};
+
+// Scratch beyond what the caller's interval asks for: more than one segment, or
+// rows of 32, only where all of it stays within this.
+constexpr int64_t kBatchBytes = (int64_t)1 << 30;
+
+// Rows of 32 (one line of 128 bytes) where they fit the bytes above, or what four
+// vectors a step of a segment take; else rows of 8: at most 2 every + 17 vectors.
+Batch plan_batch(int64_t n, int32_t K, int32_t seglen) {
+  const int64_t room = std::max<int64_t>(kBatchBytes / (4 * std::max<int64_t>(n, 1)), 4 * (int64_t)seglen + 2);
+  for (const int32_t row : {32, 8}) {
+    const int64_t most = (room - 1 - 2 * row) / 2;
+    if (most < seglen) continue;
+    const int32_t cap = std::max<int32_t>(seglen, (int32_t)std::min<int64_t>(std::min(std::max(K, 1), 32), most));
+    return Batch{cap, cap <= 8 ? 8 : row};
+  }
+  return Batch{seglen, 8};
+}
+
+struct BatchBufs {
+  PoolBuf seg, gseg, rowr, rowg;
+  BatchBufs(const Batch& b, int64_t n, bool rows, hipStream_t st)
+      : seg(sizeof(float) * n * b.cap, st), gseg(sizeof(float) * n * (b.cap + 1), st),
+        rowr(rows ? sizeof(float) * n * b.row : 1, st), rowg(rows ? sizeof(float) * n * b.row : 1, st) {}
+};
 
 int32_t n_checkpoints(int32_t K, int32_t every) { return K <= 0 ? 0 : (K + every - 1) / every; }
 }  // namespace
@@ -425,17 +474,17 @@ extern "C" tc_status tc_rwr_iterates(const tc_handle* hc, int32_t seed, float c,
     hipStream_t st = (hipStream_t)stream;
     const int64_t n = h->n_rows;
     const Steps W(h, c, seed, st);
-    PoolBuf r0(sizeof(float) * n, st), r1(sizeof(float) * n, st);
-    float *cur = r0.as<float>(), *nxt = r1.as<float>();
+    // in internal ids the handle's two vectors in turn, else in place
+    float *cur = W.inner ? h->d_xbuf : d_rK, *nxt = W.inner ? h->d_ybuf : d_rK;
     hipLaunchKernelGGL(k_onehot, dim3(nblk(n, kB)), dim3(kB), 0, st, d_rK, n, seed);
     HIPC(hipGetLastError());
-    if (K > 0) W.from_user(d_rK, cur);
+    if (W.inner && K > 0) W.from_user(d_rK, cur);
     for (int32_t k = 0; k < K; ++k) {
       if (k % every == 0) W.to_user(cur, d_ckpt + (int64_t)(k / every) * n);
       W.step(cur, nxt);
       std::swap(cur, nxt);
     }
-    if (K > 0) W.to_user(cur, d_rK);
+    if (W.inner && K > 0) W.to_user(cur, d_rK);
     return TC_OK;
   });
 }
@@ -458,39 +507,50 @@ extern "C" tc_status tc_rwr_adjoint(const tc_handle* hc, const tc_handle* htc, c
     tc_handle* ht = const_cast<tc_handle*>(htc);
     hipStream_t st = (hipStream_t)stream;
     const Steps W(h, c, seed, st), Wt(ht, c, -1, st);
-    // Steps per pass over the entries: whole segments while they fit a row of 32
-    // and the vectors stay within kBatchBytes; a longer segment goes through
-    // in batches of its own.  The sums run latest step first in any case.
     const int32_t seglen = std::min(every, std::max(K, 1));
-    const int64_t fit = kBatchBytes / (8 * std::max<int64_t>(n, 1));
-    const int32_t cap = (int32_t)std::max<int64_t>(seglen, std::min<int64_t>(std::max(K, 1), std::min<int64_t>(32, fit)));
-    const int32_t row = cap <= 8 ? 8 : 32;
-    const size_t vec = sizeof(float) * (size_t)n, rowb = nnz > 0 ? vec * row : 1;
-    PoolBuf seg(vec * cap, st), gseg(vec * (cap + 1), st), rowr(rowb, st), rowg(rowb, st),
-        rows(sizeof(int32_t) * (size_t)std::max<int64_t>(nnz, 1), st);
+    PoolBuf rows(sizeof(int32_t) * (size_t)std::max<int64_t>(nnz, 1), st);
+    Batch batch = plan_batch(n, K, seglen);
+    std::unique_ptr<BatchBufs> bufs;
+    try {
+      bufs = std::make_unique<BatchBufs>(batch, n, nnz > 0, st);
+    } catch (const Err& e) {  // what one segment cannot do without
+      if (e.st != TC_ENOMEM) throw;
+      batch = Batch{seglen, 0};
+      bufs = std::make_unique<BatchBufs>(batch, n, nnz > 0, st);
+    }
+    const int32_t cap = batch.cap, row = batch.row;
     if (nnz > 0) {
       rows_of(d_rpT, n, nnz, rows.as<int32_t>(), st);
       HIPC(hipGetLastError());
     }
     // steps in S and GS, latest first; GS's next slot holds the current g
-    float *S = seg.as<float>(), *GS = gseg.as<float>();
+    float *S = bufs->seg.as<float>(), *GS = bufs->gseg.as<float>();
+    float *rowr = bufs->rowr.as<float>(), *rowg = bufs->rowg.as<float>();
     Wt.from_user(d_gK, GS);
     int32_t have = 0;
     bool first = true;
     auto flush = [&]() {
+      if (row == 0 && have > 0 && nnz > 0) {
+        hipLaunchKernelGGL(first ? k_edge_accum_vec<true> : k_edge_accum_vec<false>, dim3(nblk(nnz, kB)), dim3(kB), 0,
+                           st, d_colT, rows.as<const int32_t>(), nnz, (const float*)GS, (const float*)S, Wt.map(),
+                           W.map(), n, have, d_G);
+        HIPC(hipGetLastError());
+        first = false;
+        return;
+      }
       for (int32_t b = 0; b < have && nnz > 0; b += row) {
         const int32_t m = std::min(row, have - b);
         auto put = row == 8 ? k_step_rows<8> : k_step_rows<32>;
         hipLaunchKernelGGL(put, dim3(nblk(n, kB)), dim3(kB), 0, st, (const float*)(GS + (int64_t)b * n), m, n,
-                           Wt.inv(), rowg.as<float>());
+                           Wt.inv(), rowg);
         HIPC(hipGetLastError());
         hipLaunchKernelGGL(put, dim3(nblk(n, kB)), dim3(kB), 0, st, (const float*)(S + (int64_t)b * n), m, n, W.inv(),
-                           rowr.as<float>());
+                           rowr);
         HIPC(hipGetLastError());
         auto sum = row == 8 ? (first ? k_edge_accum<8, true> : k_edge_accum<8, false>)
                             : (first ? k_edge_accum<32, true> : k_edge_accum<32, false>);
         hipLaunchKernelGGL(sum, dim3(nblk(nnz, kB)), dim3(kB), 0, st, d_colT, rows.as<const int32_t>(), nnz,
-                           rowg.as<const float>(), rowr.as<const float>(), m, d_G);
+                           (const float*)rowg, (const float*)rowr, m, d_G);
         HIPC(hipGetLastError());
         first = false;
       }
@@ -499,7 +559,7 @@ extern "C" tc_status tc_rwr_adjoint(const tc_handle* hc, const tc_handle* htc, c
       const int32_t k0 = q * every, m = std::min(K, k0 + every) - k0;
       if (have + m > cap) {
         flush();
-        HIPC(hipMemcpyAsync(GS, GS + (int64_t)have * n, vec, hipMemcpyDeviceToDevice, st));
+        HIPC(hipMemcpyAsync(GS, GS + (int64_t)have * n, sizeof(float) * n, hipMemcpyDeviceToDevice, st));
         have = 0;
       }
       // r^k at slot have + (k0 + m - 1 - k), recomputed from the checkpoint, which

@@ -114,8 +114,10 @@ typedef struct {
                                  40960 columns) with at least 8 entries per float staged has its
                                  x segment staged in LDS by a persistent kernel, so its gathers
                                  are LDS reads, and any other tile of at least 3M entries has
-                                 its first (hottest) 40896 columns staged; 1: every tile that
-                                 fits is staged, the first columns of every other; -1: every
+                                 its first (hottest) 40896 columns staged where those hold at
+                                 least half as many entries as the tile has columns and no
+                                 unsplit row a 2048th of the tile; 1: also every tile that
+                                 fits is staged (its first 40896 columns); -1: every
                                  tile gathers x through the caches */
   int32_t panels;             /* row panels (MI355X reading of Section 3.2's row partition, applied
                                  to the workgroups of one GPU): 0 (default) = none; P > 0 = P

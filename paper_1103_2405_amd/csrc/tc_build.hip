@@ -486,6 +486,26 @@ __global__ void k_first_zero(const int32_t* __restrict__ a, int64_t n, int64_t* 
   if (lane == 0) *out = lo;
 }
 
+// sum of a[0, n), n > 0, by one block: eight loads in flight a thread
+__global__ void __launch_bounds__(1024) k_sum_i32(const int32_t* __restrict__ a, int64_t n, int64_t* __restrict__ out) {
+  __shared__ int64_t ws[1024 / kWave];
+  int64_t v = 0;
+  for (int64_t i0 = threadIdx.x; i0 < n; i0 += 8 * 1024) {
+    int32_t t[8];
+#pragma unroll
+    for (int u = 0; u < 8; ++u) t[u] = a[i0 + u * 1024 < n ? i0 + u * 1024 : 0];
+#pragma unroll
+    for (int u = 0; u < 8; ++u) v += i0 + u * 1024 < n ? t[u] : 0;
+  }
+  v = wave_incl_scan(v);
+  if (lane_id() == kWave - 1) ws[threadIdx.x / kWave] = v;
+  __syncthreads();
+  if (threadIdx.x == 0) {
+    for (int w = 1; w < 1024 / kWave; ++w) ws[0] += ws[w];
+    *out = ws[0];
+  }
+}
+
 __global__ void k_desc_keys(const int32_t* __restrict__ len, int64_t n, int32_t maxv, uint32_t* __restrict__ keys,
                             int32_t* __restrict__ vals) {
   int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
@@ -1953,6 +1973,21 @@ void build(const tc_csr* A, const tc_build_opts* o, hipStream_t st, tc_handle* h
   for (int t = 0; t < ntiles; ++t) h->tile_nnz[t] = tstart[t + 1] - tstart[t];
   h->tile_split.assign(ntiles, 0);
   for (int t = 0; t < ntiles; ++t) h->tile_split[t] = tile_split_len(h->split_len, h->tile_nnz[t], h->max_act_warp, h->S);
+  // Entries in the columns that the staged tile kernel would hold, where its rule
+  // asks; they are the tile's longest, so they hold at least their even share,
+  // and where that answers it (half the tile's width) nothing is counted.
+  std::vector<int64_t> hot_at(ntiles, -1);
+  h->tile_hot_nnz.assign(ntiles, 0);
+  for (int t = 0; t < ntiles && h->n_panels == 0; ++t) {
+    if (h->tile_nnz[t] < kHotMinNnz || h->lds_tiles == 0 || h->hot_room() <= 0) continue;
+    const int64_t width = h->tile_col_end[t] - h->tile_col_begin[t], room = std::min(h->hot_room(), width);
+    h->tile_hot_nnz[t] = (int64_t)((double)h->tile_nnz[t] * (double)room / (double)width);
+    if (2 * h->tile_hot_nnz[t] >= width) continue;
+    hot_at[t] = sc.take();
+    hipLaunchKernelGGL(k_sum_i32, dim3(1), dim3(1024), 0, st, (const int32_t*)(clen_sorted + h->tile_col_begin[t]),
+                       room, sc.dev(hot_at[t]));
+    HIPX(hipGetLastError());
+  }
   int64_t* d_split_t = tmp.get<int64_t>(std::max(ntiles, 1));
   if (ntiles > 0)
     HIPX(hipMemcpyAsync(d_split_t, h->tile_split.data(), sizeof(int64_t) * ntiles, hipMemcpyHostToDevice, st));
@@ -2171,6 +2206,14 @@ void build(const tc_csr* A, const tc_build_opts* o, hipStream_t st, tc_handle* h
   if (nruns > 0)
     for (int t = 0; t < ntiles; ++t)
       truns[t] = RunSpan{run_list->p + tile_run[t], (size_t)(tile_run[t + 1] - tile_run[t])};
+  h->tile_hot_nnz.resize(ntiles, 0);
+  h->tile_long.assign(ntiles, 0);
+  for (int t = 0; t < ntiles; ++t) {
+    // (read after the segments' waits; row panels: more tiles than column tiles, none counted)
+    if (t < (int)hot_at.size() && hot_at[t] >= 0) h->tile_hot_nnz[t] = sc[hot_at[t]];
+    const int64_t len = truns[t].empty() ? 0 : truns[t][0].len;
+    h->tile_long[t] = h->tile_split[t] > 0 ? std::min(len, h->tile_split[t]) : len;
+  }
   clk.mark("a6 runs");
   if (o->wl_policy == 1 && o->n_wl_per_tile < ntiles)
     throw Fail{TC_EINVAL, "wl_per_tile has fewer entries than tiles built"};
@@ -2581,7 +2624,7 @@ extern "C" tc_status tc_build_tiled(const tc_csr* A, const tc_build_opts* opts, 
   h->xcd_groups = o->xcd_groups;
   h->kernel = o->kernel;
   h->slices = o->slices;
-  h->lds_tiles = o->lds_stage + 1;  // 0 never, 1 automatic, 2 every tile that fits
+  h->lds_tiles = o->lds_stage + 1;  // 0 never, 1 automatic, 2 also every tile that fits
   h->n_panels = o->panels;
   h->panel_rows = o->panels != 0 ? o->panel_rows : 0;
   h->panel_waves = o->panels != 0 ? (o->panel_waves > 0 ? o->panel_waves : 16) : 0;

@@ -17,6 +17,10 @@ constexpr int kWave = 64;
 // Most floats of x a tile stages in LDS (160 KB, the LDS of one gfx950 CU).
 constexpr int64_t kLdsMaxFloats = 40960;
 
+// Least entries of a tile whose hottest columns are staged without being asked
+// for (the rule is with the kernel, in tc_tile.h).
+constexpr int64_t kHotMinNnz = (int64_t)3 << 20;
+
 // Row ids stored in `rowid` carry bit 30 when an earlier tile already wrote
 // that row of y (the tile adds); without it the tile is the row's first
 // writer and stores.  Rows are therefore limited to 2^30.
@@ -195,8 +199,11 @@ struct tc_handle {
   int64_t* d_tile_wl_begin = nullptr;  // device copy of tile_wl_begin
   int64_t n_zero0 = 0;
   int n_cu = 256;                   // compute units of the device
-  int32_t lds_tiles = 1;            // LDS staging of narrow tiles: 0 never, 1 automatic, 2 whenever it fits
+  int32_t lds_tiles = 1;            // LDS staging of a tile's x: 0 never, 1 automatic, 2 also whenever it fits
   int64_t lds_floats = 0;           // floats of x one workgroup can stage (device limit)
+  int64_t hot_room() const { return lds_floats - 64; }  // ... beside the staged kernel's item counter
+  std::vector<int64_t> tile_hot_nnz;   // entries in the tile's first hot_room() columns, or fewer (0: not counted)
+  std::vector<int64_t> tile_long;      // most entries of a tile's row, or chunk, that one wavefront sums
   int64_t lds_cu_bytes = 0;         // LDS bytes per compute unit
   int64_t l2_bytes = 0;             // L2 bytes of one XCD (the L2 a workgroup's gathers see)
   // row panels: tile g = panel g / n_col_tiles, column tile g % n_col_tiles

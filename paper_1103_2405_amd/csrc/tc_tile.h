@@ -149,24 +149,35 @@ __global__ void __launch_bounds__(kHotB) k_tile_hot(const Wl* __restrict__ wl, u
   }
 }
 
-// Columns of tile t that k_tile_hot stages, or 0 for k_tile.  From 3M entries
-// on the staging (up to 160 KB into every compute unit, 3.4 us) and the fewer
-// wavefronts pay: measured k_tile / k_tile_hot over R-MAT, Chung-Lu and
-// uniform matrices of 2^12-2^20 columns, 0.71-1.02 up to 2.1M entries,
-// 1.01-1.24 on power-law and 0.96-0.98 on uniform ones at 3-4.2M, 0.99-1.67
-// from 6M on; a tile that is staged whole also with 8 entries per float staged
-// in every compute unit.  The build option lds_stage = 1 stages every tile, -1
-// none.  x must fit the buffer load's 32-bit offsets.
-constexpr int64_t kHotMinNnz = (int64_t)3 << 20;
+// Columns of tile t that k_tile_hot stages, or 0 for k_tile.  Measured k_tile /
+// k_tile_hot, R-MAT (r), Chung-Lu (c), uniform (u) and mildly skewed columns
+// (share of the entries in the 40896 columns: r .99-.56, c .90-.50, u .57-.02):
+//  - Below 3M entries the staging (up to 160 KB into every compute unit, 3.4 us)
+//    does not pay: 0.68-1.15 at 1-2M; 1.00-1.54 at 3.1-9M on r and c, u below.
+//  - What LDS serves has to make up for gathers of the other columns by half as
+//    many wavefronts, and the more floats x has, the farther away they are.  With
+//    at least half as many entries in the staged columns as the tile has columns
+//    0.98-1.67, most of it 1.05 and more; with fewer 0.87-0.99 (u, 2^22 columns,
+//    4-16M entries: 0.90-0.92; 2.3M columns, 4-16M: 0.92-0.97; 2^20, 4M: 0.97)
+//    and 1.02-1.04 at most (u, 1.6M columns, 16M entries).
+//  - A row that one wavefront sums alone takes 7.5 ns an entry here and 4.2 in
+//    k_tile: past a 2048th of the entries (the automatic split length is an
+//    8192th) it lasts as long as the whole pass, and unsplit hubs set the time
+//    (c 2^20, 14.7M entries, split_len 0: 533 us with k_tile, 966 here).
+//  - A tile that fits is staged whole also with 8 entries per float staged in
+//    every compute unit.
+// The build option lds_stage = 1 stages every tile that fits, and the others by
+// the same rule; -1 none.  x must fit the buffer load's 32-bit offsets.
 constexpr int64_t kHotMinReuse = 8;
+constexpr int64_t kHotRowShare = 2048;
 inline int64_t hot_width(const tc_handle* h, int t, int64_t items) {
   if (!h->lds_tiles || h->n_cols >= kBufMaxFloats || items >= ((int64_t)1 << 31)) return 0;
-  const int64_t room = h->lds_floats - 64;  // and the counter
-  const int64_t width = h->tile_col_end[t] - h->tile_col_begin[t];
-  if (h->lds_tiles == 1 && h->tile_nnz[t] < kHotMinNnz &&
-      !(width <= room && h->tile_nnz[t] >= kHotMinReuse * width * h->n_cu))
-    return 0;
-  return std::max<int64_t>(0, std::min(room, width));
+  const int64_t width = h->tile_col_end[t] - h->tile_col_begin[t], nnz = h->tile_nnz[t];
+  const bool fits = width <= h->lds_floats;
+  const int64_t stage = std::max<int64_t>(0, std::min(h->hot_room(), width));
+  if (fits && (h->lds_tiles == 2 || nnz >= kHotMinReuse * width * h->n_cu)) return stage;
+  if (nnz < kHotMinNnz || kHotRowShare * h->tile_long[t] > nnz || 2 * h->tile_hot_nnz[t] < width) return 0;
+  return stage;
 }
 
 // The rest of a one-tile product of the composite kernel (empty: its rows

@@ -200,21 +200,23 @@ struct Slots {
 
 // sum over entries [lo, hi) of the row-major row at `base`: sub-step u of each
 // step of SUB * G entries gives group g the entry u * G + g, and a group adds
-// its own in increasing order.  (Unsigned: the last step of a row of almost
-// 2^31 entries ends up to 2 SUB * G entries past 2^31.)
+// its own in increasing order.  (Counted by what is left: the entry after the
+// last step of a row of almost 2^31 entries has no 32-bit number.)
 template <int V, int KG, int SUB, class XR>
 __device__ inline Vec<V> rm_range(const int32_t* __restrict__ idx, const float* __restrict__ val, const XR& X,
-                                  int64_t base, uint32_t lo, uint32_t hi, const Cols<V, KG>& c, int lane) {
+                                  int64_t base, int32_t lo, int32_t hi, const Cols<V, KG>& c, int lane) {
   using Sl = Slots<KG, SUB>;
   const int g = lane / KG;
   Vec<V> acc;
   acc.zero();
   Sl nx;
-  auto fetch = [&](uint32_t e0) {
-    nx.load(idx, val, lane, base, [&](int s) { return e0 + s < hi; }, [&](int s) { return base + (e0 + s); });
+  int64_t at = base + lo;
+  int32_t left = hi - lo;
+  auto fetch = [&](int64_t e, int32_t n) {
+    nx.load(idx, val, lane, base, [&](int s) { return s < n; }, [&](int s) { return e + s; });
   };
-  if (lo < hi) fetch(lo);
-  for (uint32_t e0 = lo; e0 < hi; e0 += Sl::N) {
+  if (left > 0) fetch(at, left);
+  for (; left > 0; left -= Sl::N, at += Sl::N) {
     const Sl cur = nx;
     float v[SUB];
     FVec<V> x[SUB];
@@ -224,7 +226,8 @@ __device__ inline Vec<V> rm_range(const int32_t* __restrict__ idx, const float* 
       cur.get(u, g, v[u], i);
       x[u] = X(i, c.col, c.act && v[u] != 0.0f);
     }
-    fetch(e0 + Sl::N);  // past the end: the row's first entry, not used
+    fetch(at + Sl::N, left - Sl::N);  // past the end: the row's first entry, not used
+    __builtin_amdgcn_sched_barrier(0);  // every load is out before the first sum waits
 #pragma unroll
     for (int u = 0; u < SUB; ++u) fma_vec<V>(acc, v[u], x[u]);
   }
@@ -234,7 +237,7 @@ __device__ inline Vec<V> rm_range(const int32_t* __restrict__ idx, const float* 
 // Column-major rectangle, rows sl * U * G, + slices * U * G, ...: a step covers
 // U rows and C columns per group (U C gathers in flight); each row is summed by
 // its group's lanes in column order.
-template <int V, int KG, int U, int C, bool RWR, class XR>
+template <int V, int KG, int U, int C, bool FENCE, bool RWR, class XR>
 __device__ inline void cm_range(const Wl& d, int32_t sl, int32_t slices, const int32_t* __restrict__ idx,
                                 const float* __restrict__ val, const int32_t* __restrict__ rowid, const XR& X,
                                 float* __restrict__ Y, int32_t k, const Cols<V, KG>& c, int lane, const RwrEpi& epi,
@@ -277,6 +280,7 @@ __device__ inline void cm_range(const Wl& d, int32_t sl, int32_t slices, const i
       x[q] = X(i, c.col, c.act && v[q] != 0.0f);
     }
     fetch(rn, cn);  // past the rectangle: its first entry, not used
+    if constexpr (FENCE) __builtin_amdgcn_sched_barrier(0);
 #pragma unroll
     for (int q = 0; q < U * C; ++q) fma_vec<V>(acc[q % U], v[q], x[q]);
     if (last) {
@@ -291,21 +295,63 @@ __device__ inline void cm_range(const Wl& d, int32_t sl, int32_t slices, const i
   }
 }
 
+// Entries in flight per group of KG lanes: R of a row-major row or chunk; U x C
+// (rows x columns) of a column-major rectangle of one column (U1 x 1), of two or
+// three, of more.  Registers set the wavefronts: the deep form takes 104-173 VGPRs
+// (2 to 4 wavefronts per SIMD), the others 57-78 (6 to 8).  More wavefronts win where
+// X's part of a pass lies near (uniform 2^16 rows and columns, 1M entries, k = 4:
+// 71 -> 42 us, 32: 61 -> 46, 100: 239 -> 150), more in flight where it does not
+// (R-MAT 2^20, k = 32: 339 deep, 356 not) and where one wavefront has to sum a
+// long row (Chung-Lu 2^20 without split rows, five steps at k = 16: 2,180 / 2,890).
+// One lane a row (k = 1, 2, 4) has 64 entries in flight a wavefront to begin with.
+template <int V, int KG, bool DEEP>
+struct Flight {  // deep; KG of 4 and 8
+  static constexpr int R = DEEP ? 8 : 4, U1 = DEEP ? 8 : 4;
+  static constexpr int U2 = DEEP ? 4 : 2, C2 = 2, U4 = 2, C4 = DEEP ? 4 : 2;
+  static constexpr bool kFence = false;
+};
+template <>
+struct Flight<4, 2, false> {  // k = 5-8; the fence: 42 against 46 us on the uniform matrix, k = 8
+  static constexpr int R = 4, U1 = 4, U2 = 2, C2 = 2, U4 = 1, C4 = 4;
+  static constexpr bool kFence = true;
+};
+template <>
+struct Flight<2, 2, false> {  // k = 3
+  static constexpr int R = 4, U1 = 2, U2 = 2, C2 = 1, U4 = 2, C4 = 1;
+  static constexpr bool kFence = false;
+};
+template <>
+struct Flight<4, 1, false> {  // k = 4
+  static constexpr int R = 2, U1 = 1, U2 = 1, C2 = 1, U4 = 1, C4 = 1;
+  static constexpr bool kFence = false;
+};
+template <>
+struct Flight<2, 1, false> {  // k = 2
+  static constexpr int R = 4, U1 = 1, U2 = 1, C2 = 1, U4 = 1, C4 = 1;
+  static constexpr bool kFence = false;
+};
+template <>
+struct Flight<1, 1, false> {  // k = 1
+  static constexpr int R = 4, U1 = 2, U2 = 1, C2 = 2, U4 = 1, C4 = 2;
+  static constexpr bool kFence = false;
+};
+
 // One wavefront's part of a workload: piece `part` of a leading chunk workload
 // (a split row's pieces: kPiece entries each, sums to slot chunk slot * parts +
 // part of `partial`), or row slice `part` of `parts` of any other workload.  (A
 // chunk among the others is done whole, as one piece.)
 constexpr int kPiece = 512;
-template <int V, int KG, bool RWR, class XR>
+template <int V, int KG, bool DEEP, bool RWR, class XR>
 __device__ inline void spmm_item(const Wl& d, int32_t part, int32_t parts, bool lead, const int32_t* __restrict__ idx,
                                  const float* __restrict__ val, const int32_t* __restrict__ rowid, const XR& xr,
                                  float* __restrict__ Y, int32_t k, const Cols<V, KG>& c, int lane,
                                  double* __restrict__ partial, const RwrEpi& epi, const int32_t* sd) {
   constexpr int G = kWave / KG;
+  using F = Flight<V, KG, DEEP>;
   const bool g0 = lane < KG;
   if (lead) {
-    const uint32_t w = (uint32_t)d.w_pad, lo = min((uint32_t)part * kPiece, w), hi = min(lo + kPiece, w);
-    Vec<V> acc = rm_range<V, KG, 8>(idx, val, xr, d.data_off, lo, hi, c, lane);
+    const int32_t lo = (int32_t)min<int64_t>((int64_t)part * kPiece, d.w_pad), hi = lo + min(kPiece, d.w_pad - lo);
+    Vec<V> acc = rm_range<V, KG, F::R>(idx, val, xr, d.data_off, lo, hi, c, lane);
     group_sum<V, KG>(acc);
     if (c.act && g0)
 #pragma unroll
@@ -316,17 +362,17 @@ __device__ inline void spmm_item(const Wl& d, int32_t part, int32_t parts, bool 
   const int layout = d.info & 3;
   if (layout == kCM) {
     if (d.w_pad == 1)
-      cm_range<V, KG, 8, 1, RWR>(d, part, parts, idx, val, rowid, xr, Y, k, c, lane, epi, sd);
+      cm_range<V, KG, F::U1, 1, F::kFence, RWR>(d, part, parts, idx, val, rowid, xr, Y, k, c, lane, epi, sd);
     else if (d.w_pad <= 3)
-      cm_range<V, KG, 4, 2, RWR>(d, part, parts, idx, val, rowid, xr, Y, k, c, lane, epi, sd);
+      cm_range<V, KG, F::U2, F::C2, F::kFence, RWR>(d, part, parts, idx, val, rowid, xr, Y, k, c, lane, epi, sd);
     else
-      cm_range<V, KG, 2, 4, RWR>(d, part, parts, idx, val, rowid, xr, Y, k, c, lane, epi, sd);
+      cm_range<V, KG, F::U4, F::C4, F::kFence, RWR>(d, part, parts, idx, val, rowid, xr, Y, k, c, lane, epi, sd);
     return;
   }
   for (int32_t r = part; r < d.n_rows; r += parts) {
     const int64_t base = d.data_off + (int64_t)r * d.w_pad;
     const int32_t rid = layout == kChunk ? 0 : ld_nt(rowid + d.rowid_off + r);
-    Vec<V> acc = d.w_pad > 2 * G ? rm_range<V, KG, 8>(idx, val, xr, base, 0, d.w_pad, c, lane)
+    Vec<V> acc = d.w_pad > 2 * G ? rm_range<V, KG, F::R>(idx, val, xr, base, 0, d.w_pad, c, lane)
                                  : rm_range<V, KG, 2>(idx, val, xr, base, 0, d.w_pad, c, lane);
     group_sum<V, KG>(acc);
     if (!(c.act && g0)) continue;
@@ -340,27 +386,26 @@ __device__ inline void spmm_item(const Wl& d, int32_t part, int32_t parts, bool 
   }
 }
 
-// One pass over a tile for the right-hand sides [c0 + V KG blockIdx.y, ...):
+// The passes over a tile, pass p = blockIdx.y for the right-hand sides V KG p, ...:
 // wavefronts for the pieces of the tile's leading chunk workloads, then for
 // the row slices of the others.
 //
 // Bound at k = 32 on a 31.4M-entry power-law matrix of 1M rows (304 us of the
 // kernel, 346 a product; 336 and 378 with two launches, four rows or eight
 // entries in flight without the next step's entries, and a branch per entry):
-// 2.0 GB of L2 misses, 6.5 TB/s, the card's streaming-read rate.  126 VGPRs,
+// 2.0 GB of L2 misses, 6.5 TB/s, the card's streaming-read rate.  124 VGPRs,
 // four wavefronts per SIMD: capping them for 5 or 6 measured 358 and 404 us (the
-// kernel spills), 4 entries in flight 394, 16 367, 8 row slices 455 (wavefronts
+// kernel spills), 16 entries in flight 367, 8 row slices 455 (wavefronts
 // without a row to sum), 2 362; a persistent grid with an LDS item counter 351.
-// By k, us a product before and now: 3 357 -> 224, 4 279 -> 227, 8 290 -> 249,
-// 37 1825 -> 931 (the last lane of a row overlaps its neighbour instead of one
-// right-hand side per lane); 13 on 4.8M entries of 100K columns 86 -> 60 (all
-// with X's rows k floats apart; tc_spmm pads them since, see padded_rows).
-template <int V, int KG, bool RWR, template <int> class XR>
+// By k, us a product of the R-MAT matrix of 2^20 (16M entries) with one right-hand
+// side per lane for k no multiple of 4, and now: 3 228 -> 174, 4 199 -> 165, 8 224 ->
+// 190, 37 1,295 -> 719; 13 on 4.8M entries of 100K columns 99 -> 62.
+template <int V, int KG, bool DEEP, bool RWR, template <int> class XR>
 __global__ void __launch_bounds__(kB) k_tile_spmm(const Wl* __restrict__ wl, int64_t n_wl, int64_t n_lead,
                                                   int32_t pieces, int32_t slices, const int32_t* __restrict__ idx,
                                                   const float* __restrict__ val, const int32_t* __restrict__ rowid,
                                                   const float* __restrict__ X, int64_t n_cols, int32_t ldx,
-                                                  float* __restrict__ Y, int32_t k, int32_t c0,
+                                                  float* __restrict__ Y, int32_t k,
                                                   double* __restrict__ partial, RwrEpi epi) {
   // fused restart: the seeds (k <= kB) in LDS, read only where rows are written
   __shared__ int32_t sd[RWR ? kB : 1];
@@ -374,9 +419,9 @@ __global__ void __launch_bounds__(kB) k_tile_spmm(const Wl* __restrict__ wl, int
   if (v >= (n_wl - n_lead) * slices) return;
   const bool lead = v < 0;
   const Wl d = wl[lead ? w / pieces : n_lead + v / slices];
-  const Cols<V, KG> c(lane, c0 + (int32_t)blockIdx.y * (V * KG), k);
+  const Cols<V, KG> c(lane, (int32_t)blockIdx.y * (V * KG), k);
   const XR<V> xr(X, n_cols, ldx);
-  spmm_item<V, KG, RWR>(d, (int32_t)(lead ? w % pieces : v % slices), lead ? pieces : slices, lead, idx, val, rowid,
+  spmm_item<V, KG, DEEP, RWR>(d, (int32_t)(lead ? w % pieces : v % slices), lead ? pieces : slices, lead, idx, val, rowid,
                         xr, Y, k, c, lane, partial, epi, sd);
 }
 
@@ -433,34 +478,40 @@ void spmm_plan(tc_handle* h) {
   h->mm_planned = true;
 }
 
-// The passes of one tile over the k right-hand sides: 32 at a time (128 bytes
-// of each X row, one cache line per gather), then the rest by as many lanes as
-// it needs.  Wider passes spread the gathers over n * 4k bytes, past the 256
-// MB MALL at a million rows and k = 64 (measured on a 31M-entry power-law
-// matrix, 1M rows: k = 64 1262 -> 1152 us, k = 128 2718 -> 2244 us per
-// product; 16 per pass slows k = 32 by 40%).
+// The passes of one tile over the k right-hand sides, 32 at a time (128 bytes
+// of each X row, one cache line per gather), in one launch.  Wider passes spread
+// the gathers over n * 4k bytes, past the 256 MB MALL at a million rows and k =
+// 64 (measured on a 31M-entry power-law matrix, 1M rows: k = 64 1262 -> 1152 us,
+// k = 128 2718 -> 2244 us per product; 16 per pass slows k = 32 by 40%).  The
+// last pass has the lanes of a whole one: fewer lanes in a launch of their own
+// measured 667 / 631 us at k = 36 on the R-MAT matrix of 2^20, 200 / 192 on a
+// rectangle of 4.8M entries, 25.3 / 22.1 on one of 2^12 rows (whole / fewer).
+//
+// The form of the kernel (see Flight): deep for a tile with a row, or chunk, of
+// at least a 2048th of its entries, and for more than 16 right-hand sides where a
+// pass reads more than 2^18 rows of X (32 MB, what the eight L2s hold): deep / not,
+// us at k = 32 and 64, uniform and R-MAT matrices of 2^17 columns 75 / 60, 142 /
+// 112, 57 / 54, 96 / 89; of 2^18 107 / 107, 206 / 208, 91 / 89, 166 / 163; of 2^20
+// 377 / 387, 744 / 761, 336 / 355, 613 / 642.
+constexpr int64_t kNearCols = (int64_t)1 << 18;
+constexpr int64_t kLongRow = 2048;
 template <bool RWR, template <int> class XR>
-void spmm_tile_x(tc_handle* h, int64_t b, int64_t n, int64_t lead, int32_t pieces, int32_t slices, const float* X,
-                 int32_t ldx, float* Y, int32_t k, double* partial, const RwrEpi& ep, hipStream_t st) {
+void spmm_tile_x(tc_handle* h, int t, int64_t b, int64_t n, int64_t lead, int32_t pieces, int32_t slices,
+                 const float* X, int32_t ldx, float* Y, int32_t k, double* partial, const RwrEpi& ep, hipStream_t st) {
+  const bool long_row = h->tile_long[t] >= kLongRow && kLongRow * h->tile_long[t] > h->tile_nnz[t];
   const unsigned gx = nblk(lead * pieces + (n - lead) * slices, kWpb);
-  auto go = [&](auto kern, int32_t c0, unsigned gy) {
-    launch_tile(h, kern, dim3(gx, gy), dim3(kB), 0, st, (const Wl*)(h->d_wl + b), n, lead, pieces, slices,
-                (const int32_t*)h->d_idx, (const float*)h->d_val, (const int32_t*)h->d_rowid, X, (int64_t)h->n_cols, ldx,
-                Y, k, c0, partial, ep);
+  auto go = [&](auto near, auto deep, bool d) {
+    launch_tile(h, d ? deep : near, dim3(gx, (unsigned)((k + 31) / 32)), dim3(kB), 0, st, (const Wl*)(h->d_wl + b), n,
+                lead, pieces, slices, (const int32_t*)h->d_idx, (const float*)h->d_val, (const int32_t*)h->d_rowid, X,
+                (int64_t)h->n_cols, ldx, Y, k, partial, ep);
   };
-  if (k == 1) return go(k_tile_spmm<1, 1, RWR, XR>, 0, 1);
-  if (k == 2) return go(k_tile_spmm<2, 1, RWR, XR>, 0, 1);
-  if (k == 3) return go(k_tile_spmm<2, 2, RWR, XR>, 0, 1);
-  const int32_t full = k / 32, rest = k - 32 * full;
-  if (full > 0) go(k_tile_spmm<4, 8, RWR, XR>, 0, (unsigned)full);
-  if (rest > 16)
-    go(k_tile_spmm<4, 8, RWR, XR>, 32 * full, 1);
-  else if (rest > 8)
-    go(k_tile_spmm<4, 4, RWR, XR>, 32 * full, 1);
-  else if (rest > 4)
-    go(k_tile_spmm<4, 2, RWR, XR>, 32 * full, 1);
-  else if (rest > 0)
-    go(k_tile_spmm<4, 1, RWR, XR>, 32 * full, 1);
+  if (k == 1) return go(k_tile_spmm<1, 1, false, RWR, XR>, k_tile_spmm<1, 1, true, RWR, XR>, long_row);
+  if (k == 2) return go(k_tile_spmm<2, 1, false, RWR, XR>, k_tile_spmm<2, 1, true, RWR, XR>, long_row);
+  if (k == 3) return go(k_tile_spmm<2, 2, false, RWR, XR>, k_tile_spmm<2, 2, true, RWR, XR>, long_row);
+  if (k == 4) return go(k_tile_spmm<4, 1, false, RWR, XR>, k_tile_spmm<4, 1, true, RWR, XR>, long_row);
+  if (k <= 8) return go(k_tile_spmm<4, 2, false, RWR, XR>, k_tile_spmm<4, 2, true, RWR, XR>, long_row);
+  if (k <= 16) return go(k_tile_spmm<4, 4, false, RWR, XR>, k_tile_spmm<4, 4, true, RWR, XR>, long_row);
+  go(k_tile_spmm<4, 8, false, RWR, XR>, k_tile_spmm<4, 8, true, RWR, XR>, long_row || h->n_cols > kNearCols);
 }
 
 // out[c] = X[cperm[c]], rows of k floats into rows of 4 ld4 (the rest zeros)
@@ -498,12 +549,12 @@ int32_t padded_rows(int64_t n_cols, int32_t k) {
   return n_cols * ld * (int64_t)sizeof(float) <= ((int64_t)256 << 20) ? ld : k;
 }
 
-void spmm_tile(tc_handle* h, int64_t b, int64_t n, int64_t lead, int32_t pieces, int32_t slices, const float* X,
+void spmm_tile(tc_handle* h, int t, int64_t b, int64_t n, int64_t lead, int32_t pieces, int32_t slices, const float* X,
                int32_t ldx, float* Y, int32_t k, double* partial, bool rwr, const RwrEpi& ep, hipStream_t st) {
   const bool small = h->n_cols <= ((int64_t)1 << 24) && h->n_cols * ldx < ((int64_t)1 << 29);
   auto f = rwr ? (small ? spmm_tile_x<true, SmallX> : spmm_tile_x<true, LargeX>)
                : (small ? spmm_tile_x<false, SmallX> : spmm_tile_x<false, LargeX>);
-  f(h, b, n, lead, pieces, slices, X, ldx, Y, k, partial, ep, st);
+  f(h, t, b, n, lead, pieces, slices, X, ldx, Y, k, partial, ep, st);
 }
 
 }  // namespace
@@ -551,7 +602,7 @@ void spmm_internal(tc_handle* h, const float* X, float* Y, int32_t k, hipStream_
   for (int t = 0; t < h->n_tiles; ++t) {
     const int64_t b = h->tile_wl_begin[t], e = h->tile_wl_begin[t + 1];
     const int64_t lead = h->mm_lead[t];
-    if (e > b) spmm_tile(h, b, e - b, lead, pieces, slices, X, ldx, Y, k, partial, epi != nullptr, ep, st);
+    if (e > b) spmm_tile(h, t, b, e - b, lead, pieces, slices, X, ldx, Y, k, partial, epi != nullptr, ep, st);
   }
   if (h->n_split_rows > 0) {
     hipLaunchKernelGGL(k_split_combine_mm, dim3(nblk(h->n_split_rows * k, kB)), dim3(kB), 0, st, h->d_split,

@@ -569,11 +569,17 @@ __device__ __attribute__((always_inline)) inline void run_workload(const Wl& d, 
 // finishes the row's last chunk (ticket[i] counts split row i's finished
 // chunks modulo their number).
 struct TileRest {
+  static constexpr bool kWhole = true;
   const int32_t* empty;
   int64_t n_empty;
   const SplitRow* split;
   const int32_t* slot_split;  // partial slot -> split row
-  uint32_t* ticket;           // null: the caller sums the partial slots
+  uint32_t* ticket;
+};
+// ... or nothing: one tile of several, whose chunk sums another launch adds
+struct NoRest {
+  static constexpr bool kWhole = false;
+  static constexpr int64_t n_empty = 0;
 };
 
 // After a chunk's sum is in its slot: the wavefront of the row's last chunk
@@ -609,20 +615,24 @@ __device__ inline void finish_chunk(int32_t i, const SplitRow& sr, int lane, con
   if (lane == 0) x.addy(y, sr.row, acc);
 }
 
-// A workload slice of a one-tile product (or, without tickets, of any tile)
-template <int S, bool VEC, class X>
+// A workload slice; the chunks of a one-tile product draw their tickets
+template <int S, bool VEC, class X, class Rest>
 __device__ inline void tile_item(const Wl& d, int lane, const int32_t* __restrict__ idx, const float* __restrict__ val,
                                  const int32_t* __restrict__ rowid, const X& x, float* __restrict__ y,
-                                 double* __restrict__ partial, int32_t sl, const TileRest& rest) {
-  const bool chunk = (d.info & 3) == kChunk && rest.ticket && sl == 0;
-  int32_t i = 0;
-  SplitRow sr{0, 0, 0, 0};
-  if (chunk) {
-    i = rest.slot_split[d.info >> 2];
-    sr = rest.split[i];
+                                 double* __restrict__ partial, int32_t sl, const Rest& rest) {
+  if constexpr (Rest::kWhole) {
+    const bool chunk = (d.info & 3) == kChunk && sl == 0;
+    int32_t i = 0;
+    SplitRow sr{0, 0, 0, 0};
+    if (chunk) {
+      i = rest.slot_split[d.info >> 2];
+      sr = rest.split[i];
+    }
+    run_workload<S, VEC, true>(d, lane, idx, val, rowid, x, y, partial, sl);
+    if (chunk) finish_chunk(i, sr, lane, x, y, partial, rest);
+  } else {
+    run_workload<S, VEC, false>(d, lane, idx, val, rowid, x, y, partial, sl);
   }
-  run_workload<S, VEC, true>(d, lane, idx, val, rowid, x, y, partial, sl);
-  if (chunk) finish_chunk(i, sr, lane, x, y, partial, rest);
 }
 
 template <class X>

@@ -609,7 +609,7 @@ void spmv_internal(tc_handle* h, const float* x, float* y, hipStream_t st, bool 
   for (int t = 0; t < (xcd ? 1 : h->n_tiles); ++t) {
     const int64_t b = h->tile_wl_begin[t], e = h->tile_wl_begin[t + 1];
     if (e == b) continue;
-    run_tile(h, t, PlainSpec{x}, y, st, tile_rest(h, false));
+    run_tile(h, t, TileSpec{x}, y, st, NoRest{});
   }
   if (xcd) {
     const int32_t G = h->n_tiles - 1;

@@ -1410,10 +1410,9 @@ void transpose(const tc_csr* A, int64_t* rpT, int32_t* colT, float* valT, int32_
   int32_t* clen = tmp.get<int32_t>(n_cols);
   const int cbits = bits_for((uint64_t)(n_cols > 1 ? n_cols - 1 : 0));
   const Checked checked = check_and_count(A, clen, sc, tmp, st);
-  const int64_t total = n_cols > 0 ? excl_scan<int32_t, int64_t>(clen, n_cols, rpT, sc, tmp, st) : 0;
-  if (n_cols == 0) sc.wait();
-  checked.need(sc);
-  HIPX(hipMemcpyAsync(rpT + n_cols, &total, sizeof(int64_t), hipMemcpyHostToDevice, st));
+  sc.wait();
+  checked.need(sc);  // nothing is written for a matrix that is refused
+  excl_scan_async<int32_t, int64_t>(clen, n_cols, rpT, rpT + n_cols, tmp, st);
   if (nnz > 0) {
     int32_t* row_of = tmp.get<int32_t>(nnz);
     rows_of(A->row_ptr, n_rows, nnz, row_of, st);

@@ -574,7 +574,7 @@ struct TileRest {
   int64_t n_empty;
   const SplitRow* split;
   const int32_t* slot_split;  // partial slot -> split row
-  uint32_t* ticket;
+  uint32_t* ticket;           // null: another launch adds the chunk sums
 };
 // ... or nothing: one tile of several, whose chunk sums another launch adds
 struct NoRest {
@@ -621,7 +621,7 @@ __device__ inline void tile_item(const Wl& d, int lane, const int32_t* __restric
                                  const int32_t* __restrict__ rowid, const X& x, float* __restrict__ y,
                                  double* __restrict__ partial, int32_t sl, const Rest& rest) {
   if constexpr (Rest::kWhole) {
-    const bool chunk = (d.info & 3) == kChunk && sl == 0;
+    const bool chunk = (d.info & 3) == kChunk && rest.ticket && sl == 0;
     int32_t i = 0;
     SplitRow sr{0, 0, 0, 0};
     if (chunk) {

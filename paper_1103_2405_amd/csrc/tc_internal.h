@@ -186,6 +186,7 @@ struct tc_handle {
   double* d_partial = nullptr;
   int32_t* d_slot_split = nullptr;  // partial slot -> split row (index into d_split)
   uint32_t* d_ticket = nullptr;     // [n_split_rows] finished chunks of each split row, modulo their number
+  bool tickets = false;             // one-tile products finish their split rows in the tile's launch
   float* d_xbuf = nullptr;          // internal-space x for spmv on user vectors
   float* d_ybuf = nullptr;
   double* d_red = nullptr;          // reduction scratch

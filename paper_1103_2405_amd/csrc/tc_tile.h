@@ -161,6 +161,22 @@ __global__ void __launch_bounds__(kHotB) k_tile_hot(const Wl* __restrict__ wl, u
   }
 }
 
+// The split rows of a one-tile product whose tile launch draws no tickets, one
+// wavefront a row: the chunk sums added left to right (the bits of the tickets').
+template <class Spec>
+__global__ void __launch_bounds__(kB) k_tile_splits(const SplitRow* __restrict__ split, int64_t n,
+                                                    const double* __restrict__ partial, Spec spec,
+                                                    float* __restrict__ y) {
+  const int lane = lane_id();
+  const int64_t i = (int64_t)blockIdx.x * kWpb + __builtin_amdgcn_readfirstlane(threadIdx.x / kWave);
+  if (i >= n) return;
+  __shared__ double buf[kWpb][4 * kWave];
+  const SplitRow s = split[i];
+  const auto x = spec.make();
+  const double acc = sum_slots_wave(partial + s.slot_begin, s.n_slots, lane, buf[threadIdx.x / kWave]);
+  if (lane == 0) x.addy(y, s.row, acc);
+}
+
 // Columns of tile t that k_tile_hot stages, or 0 for k_tile.  Measured k_tile /
 // k_tile_hot, R-MAT (r), Chung-Lu (c), uniform (u) and mildly skewed columns
 // (share of the entries in the 40896 columns: r .99-.56, c .90-.50, u .57-.02):
@@ -195,15 +211,13 @@ inline int64_t hot_width(const tc_handle* h, int t, int64_t items) {
 inline bool one_tile(const tc_handle* h) { return h->n_tiles == 1 && h->n_panels == 0 && h->kernel == 0; }
 // The rest of a one-tile product (empty: its rows without entries too).
 inline TileRest tile_rest(const tc_handle* h, bool empty) {
-  return TileRest{h->d_empty, empty ? h->n_empty : 0, h->d_split, h->d_slot_split, h->d_ticket};
+  return TileRest{h->d_empty, empty ? h->n_empty : 0, h->d_split, h->d_slot_split, h->tickets ? h->d_ticket : nullptr};
 }
 
-// y's rows of tile t, and the rest, through the writer of `sp`.
+// The launch of tile t's kernel.
 template <class Spec>
-void run_tile(tc_handle* h, int t, const Spec& sp, float* y, hipStream_t st,
-              const typename Spec::Rest& rest) {
-  const int64_t b = h->tile_wl_begin[t], n = h->tile_wl_begin[t + 1] - b;
-  if (n == 0 && rest.n_empty == 0) return;
+void launch_rows(tc_handle* h, int t, int64_t b, int64_t n, const Spec& sp, float* y, hipStream_t st,
+                 const typename Spec::Rest& rest) {
   const int32_t S = tile_slices(h, t, n);
   if constexpr (!Spec::kMapped) {  // staging takes x in internal ids
     const int64_t hot = n > 0 ? hot_width(h, t, n * S) : 0;
@@ -226,6 +240,20 @@ void run_tile(tc_handle* h, int t, const Spec& sp, float* y, hipStream_t st,
   launch_tile(h, pick_slices(S, k_tile<1, Spec>, k_tile<2, Spec>, k_tile<4, Spec>, k_tile<8, Spec>), dim3(wb + eb),
               dim3(kB), 0, st, (const Wl*)(h->d_wl + b), n, wb, (const int32_t*)h->d_idx, (const float*)h->d_val,
               (const int32_t*)h->d_rowid, sp, y, h->d_partial, rest);
+}
+
+// y's rows of tile t, and the rest, through the writer of `sp`.
+template <class Spec>
+void run_tile(tc_handle* h, int t, const Spec& sp, float* y, hipStream_t st, const typename Spec::Rest& rest) {
+  const int64_t b = h->tile_wl_begin[t], n = h->tile_wl_begin[t + 1] - b;
+  if (n == 0 && rest.n_empty == 0) return;
+  launch_rows(h, t, b, n, sp, y, st, rest);
+  if constexpr (Spec::Rest::kWhole)
+    if (!rest.ticket && h->n_split_rows > 0) {
+      hipLaunchKernelGGL(k_tile_splits<Spec>, dim3(nblk(h->n_split_rows, kWpb)), dim3(kB), 0, st,
+                         (const SplitRow*)h->d_split, h->n_split_rows, (const double*)h->d_partial, sp, y);
+      HIPC(hipGetLastError());
+    }
 }
 
 }  // namespace

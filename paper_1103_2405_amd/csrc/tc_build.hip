@@ -1579,11 +1579,13 @@ void parallel_for(int64_t n, int64_t min_par, F&& f) {
 
 // Most chunks of a one-tile format whose products finish its split rows in the
 // tile's own launch (a ticket a chunk); with more of them a launch after it does.
-// Measured tickets / launch, us a product: 2,023 chunks 96.6 / 98.5, 2,306 18.4 /
-// 19.8, 2,653 15.4 / 15.3, 3,492 13.6 / 13.8, 5,046 11.2 / 10.4, 5,684 22.7 / 22.2,
-// 9,710 19.5 / 15.2, 17,037 35.1 / 18.6, 100,171 171 / 70, 428,848 939 / 528 (short
-// chunks: a ticket each costs 1.5-2 ns, and a hub's draw them at one address).
-constexpr int64_t kTicketChunks = 4096;
+// Measured tickets / launch, us a product: 2,306 chunks 18.4 / 19.8, 3,492 13.6 /
+// 14.1, 4,487 9.8 / 12.2, 5,434 12.0 / 12.5, 5,516 11.0 / 12.0, 5,821 12.3 / 12.2,
+// 6,005 15.6 / 14.6, 9,710 19.5 / 15.2, 17,037 35 / 19, 100,171 171 / 70, 428,848
+// 939 / 528 (a ticket costs 1.5-2 ns, and a hub's chunks draw them at one address).
+// In a walk's iterations the launch is hidden from about 2,000 on and wins there
+// by up to a sixth (5,434: 295 / 244 us for 20), which is not used.
+constexpr int64_t kTicketChunks = 5632;
 
 // what a build needs to know of a device
 struct DeviceLimits {

@@ -1,5 +1,5 @@
 """One-tile formats with as many chunks as their products finish in the tile's own
-launch (4,096) and with more, which a launch after it finishes: the product in
+launch (5,632) and with more, which a launch after it finishes: the product in
 internal and in the caller's ids and the fused updates against the oracle, the
 same bits call after call and under both tile kernels."""
 import numpy as np
@@ -27,8 +27,8 @@ def matrix(n, lens):
     return n, n, rp, c[order].astype(np.int32), gg.uniform_f32(r.size, 4) / np.float32(64)
 
 
-@pytest.mark.parametrize("lens,chunks", [([128] * 2048, 4096), ([128] * 2047 + [129], 4097), ([65] * 5000, 10000),
-                                         ([20000, 9000] + [70] * 2000, 4454)])
+@pytest.mark.parametrize("lens,chunks", [([128] * 2816, 5632), ([128] * 2815 + [129], 5633), ([65] * 5000, 10000),
+                                         ([20000, 9000] + [70] * 2600, 5654)])
 @pytest.mark.parametrize("n,opts", [(30000, {}), (300000, {}), (30000, dict(lds_stage=1)), (30000, dict(slices=4, wl=512))])
 def test_products_and_updates(n, opts, lens, chunks):
     from paper_1103_2405_amd import TiledMatrix

@@ -38,6 +38,12 @@ void launch_tile(tc_handle* h, void (*kern)(KArgs...), dim3 grid, dim3 block, ui
   HIPC(hipGetLastError());
 }
 
+// A row, or chunk, that one wavefront sums alone sets the time of tile t's launch.
+constexpr int64_t kRowShare = 2048;
+inline bool long_row(const tc_handle* h, int t) {
+  return h->tile_long[t] >= kRowShare && kRowShare * h->tile_long[t] > h->tile_nnz[t];
+}
+
 // Row slices of tile t's workloads (the build option, or the measured rule).
 int32_t tile_slices(const tc_handle* h, int t, int64_t n_wl);
 template <class K>

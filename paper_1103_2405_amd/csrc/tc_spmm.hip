@@ -487,31 +487,29 @@ void spmm_plan(tc_handle* h) {
 // measured 667 / 631 us at k = 36 on the R-MAT matrix of 2^20, 200 / 192 on a
 // rectangle of 4.8M entries, 25.3 / 22.1 on one of 2^12 rows (whole / fewer).
 //
-// The form of the kernel (see Flight): deep for a tile with a row, or chunk, of
-// at least a 2048th of its entries, and for more than 16 right-hand sides where a
+// The form of the kernel (see Flight): deep for a tile with a long row, and for more than 16 right-hand sides where a
 // pass reads more than 2^18 rows of X (32 MB, what the eight L2s hold): deep / not,
 // us at k = 32 and 64, uniform and R-MAT matrices of 2^17 columns 75 / 60, 142 /
 // 112, 57 / 54, 96 / 89; of 2^18 107 / 107, 206 / 208, 91 / 89, 166 / 163; of 2^20
 // 377 / 387, 744 / 761, 336 / 355, 613 / 642.
 constexpr int64_t kNearCols = (int64_t)1 << 18;
-constexpr int64_t kLongRow = 2048;
 template <bool RWR, template <int> class XR>
 void spmm_tile_x(tc_handle* h, int t, int64_t b, int64_t n, int64_t lead, int32_t pieces, int32_t slices,
                  const float* X, int32_t ldx, float* Y, int32_t k, double* partial, const RwrEpi& ep, hipStream_t st) {
-  const bool long_row = h->tile_long[t] >= kLongRow && kLongRow * h->tile_long[t] > h->tile_nnz[t];
+  const bool lone = long_row(h, t);
   const unsigned gx = nblk(lead * pieces + (n - lead) * slices, kWpb);
   auto go = [&](auto near, auto deep, bool d) {
     launch_tile(h, d ? deep : near, dim3(gx, (unsigned)((k + 31) / 32)), dim3(kB), 0, st, (const Wl*)(h->d_wl + b), n,
                 lead, pieces, slices, (const int32_t*)h->d_idx, (const float*)h->d_val, (const int32_t*)h->d_rowid, X,
                 (int64_t)h->n_cols, ldx, Y, k, partial, ep);
   };
-  if (k == 1) return go(k_tile_spmm<1, 1, false, RWR, XR>, k_tile_spmm<1, 1, true, RWR, XR>, long_row);
-  if (k == 2) return go(k_tile_spmm<2, 1, false, RWR, XR>, k_tile_spmm<2, 1, true, RWR, XR>, long_row);
-  if (k == 3) return go(k_tile_spmm<2, 2, false, RWR, XR>, k_tile_spmm<2, 2, true, RWR, XR>, long_row);
-  if (k == 4) return go(k_tile_spmm<4, 1, false, RWR, XR>, k_tile_spmm<4, 1, true, RWR, XR>, long_row);
-  if (k <= 8) return go(k_tile_spmm<4, 2, false, RWR, XR>, k_tile_spmm<4, 2, true, RWR, XR>, long_row);
-  if (k <= 16) return go(k_tile_spmm<4, 4, false, RWR, XR>, k_tile_spmm<4, 4, true, RWR, XR>, long_row);
-  go(k_tile_spmm<4, 8, false, RWR, XR>, k_tile_spmm<4, 8, true, RWR, XR>, long_row || h->n_cols > kNearCols);
+  if (k == 1) return go(k_tile_spmm<1, 1, false, RWR, XR>, k_tile_spmm<1, 1, true, RWR, XR>, lone);
+  if (k == 2) return go(k_tile_spmm<2, 1, false, RWR, XR>, k_tile_spmm<2, 1, true, RWR, XR>, lone);
+  if (k == 3) return go(k_tile_spmm<2, 2, false, RWR, XR>, k_tile_spmm<2, 2, true, RWR, XR>, lone);
+  if (k == 4) return go(k_tile_spmm<4, 1, false, RWR, XR>, k_tile_spmm<4, 1, true, RWR, XR>, lone);
+  if (k <= 8) return go(k_tile_spmm<4, 2, false, RWR, XR>, k_tile_spmm<4, 2, true, RWR, XR>, lone);
+  if (k <= 16) return go(k_tile_spmm<4, 4, false, RWR, XR>, k_tile_spmm<4, 4, true, RWR, XR>, lone);
+  go(k_tile_spmm<4, 8, false, RWR, XR>, k_tile_spmm<4, 8, true, RWR, XR>, lone || h->n_cols > kNearCols);
 }
 
 // out[c] = X[cperm[c]], rows of k floats into rows of 4 ld4 (the rest zeros)

@@ -657,7 +657,8 @@ void gather_rows(const float* in, const int32_t* perm, int64_t n, int32_t w, flo
 // kUserRows rows the tile then writes y through rowinv, above them y is
 // gathered afterwards: rows through rowinv / y gathered 14.7 / 16.7 at 2^16
 // rows, 20.6 / 21.5 at 2^18, 18.5 / 18.7 at 2^19, 78.5 / 74.0 at 2^20 (the
-// dependent load at every row's end), 465 / 411 at 2^22.
+// dependent load at every row's end), 465 / 411 at 2^22; with an unsplit long row
+// y is gathered too (R-MAT 2^18, split_len 0: 119 / 108).
 constexpr int64_t kMapNnz = (int64_t)1 << 19;
 constexpr int64_t kUserRows = (int64_t)1 << 18;
 
@@ -671,7 +672,7 @@ void spmv_user(tc_handle* h, const float* x, float* y, hipStream_t st) {
   gather_rows(x, h->d_cperm, h->n_cols, 1, h->d_xbuf, st);
   if (!h->relabel) {
     spmv_internal(h, h->d_xbuf, y, st);
-  } else if (one_tile(h) && h->n_rows <= kUserRows) {
+  } else if (one_tile(h) && h->n_rows <= kUserRows && !long_row(h, 0)) {
     run_tile(h, 0, UserSpec<false>{h->d_xbuf, nullptr, h->d_rowinv}, y, st, tile_rest(h, true));
     h->spmv_calls++;
   } else {

@@ -197,14 +197,13 @@ __global__ void __launch_bounds__(kB) k_tile_splits(const SplitRow* __restrict__
 // The build option lds_stage = 1 stages every tile that fits, and the others by
 // the same rule; -1 none.  x must fit the buffer load's 32-bit offsets.
 constexpr int64_t kHotMinReuse = 8;
-constexpr int64_t kHotRowShare = 2048;
 inline int64_t hot_width(const tc_handle* h, int t, int64_t items) {
   if (!h->lds_tiles || h->n_cols >= kBufMaxFloats || items >= ((int64_t)1 << 31)) return 0;
   const int64_t width = h->tile_col_end[t] - h->tile_col_begin[t], nnz = h->tile_nnz[t];
   const bool fits = width <= h->lds_floats;
   const int64_t stage = std::max<int64_t>(0, std::min(h->hot_room(), width));
   if (fits && (h->lds_tiles == 2 || nnz >= kHotMinReuse * width * h->n_cu)) return stage;
-  if (nnz < kHotMinNnz || kHotRowShare * h->tile_long[t] > nnz || 2 * h->tile_hot_nnz[t] < width) return 0;
+  if (nnz < kHotMinNnz || kRowShare * h->tile_long[t] > nnz || 2 * h->tile_hot_nnz[t] < width) return 0;
   return stage;
 }
 

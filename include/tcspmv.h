@@ -110,15 +110,16 @@ typedef struct {
                                  Tiles of different widths (Solution 1 with one width per cache
                                  level); tile_width and n_tiles are then not used.  NULL = none */
   int32_t n_tile_bounds;      /* length of tile_bounds (0 = none) */
-  int32_t lds_stage;          /* 0 (default): a tile no wider than one workgroup's LDS (160 KB,
-                                 40960 columns) with at least 8 entries per float staged has its
-                                 x segment staged in LDS by a persistent kernel, so its gathers
-                                 are LDS reads, and any other tile of at least 3M entries has
-                                 its first (hottest) 40896 columns staged where those hold at
-                                 least half as many entries as the tile has columns and no
-                                 unsplit row a 2048th of the tile; 1: also every tile that
-                                 fits is staged (its first 40896 columns); -1: every
-                                 tile gathers x through the caches */
+  int32_t lds_stage;          /* x of a tile in LDS, by a persistent kernel (its gathers of the
+                                 columns held there are LDS reads), up to the tile's first
+                                 (hottest) 40896 columns.  0 (default): a tile no wider than
+                                 one workgroup's LDS (160 KB, 40960 columns) with at least 8
+                                 entries per float held in every compute unit, and any tile of
+                                 at least 3M entries whose held columns have at least half as
+                                 many of them as the tile has columns and whose longest row (a
+                                 split row: its chunks) is at most a 2048th of them; 1: also
+                                 every tile of at most 40960 columns; -1: every tile gathers x
+                                 through the caches */
   int32_t panels;             /* row panels (MI355X reading of Section 3.2's row partition, applied
                                  to the workgroups of one GPU): 0 (default) = none; P > 0 = P
                                  panels; -1 = automatic: min(compute units, ceil(n_rows / 2048))

@@ -1,7 +1,7 @@
 // The power iterations on a built handle (Appendix F): PageRank (Eq. 6), HITS
-// (Eq. 7-8) and RWR (Eq. 9), with their vector updates, reductions in FP64
-// and, on iterations whose convergence measure is not read, the update fused
-// into the product.
+// (Eq. 7-8) and RWR (Eq. 9), with their vector updates and reductions in FP64;
+// one-tile formats and row panels write PageRank's update, and one-tile formats
+// RWR's restart, from the product itself.
 #include <algorithm>
 #include <cmath>
 #include <vector>

@@ -571,7 +571,7 @@ void spmv_internal(tc_handle* h, const float* x, float* y, hipStream_t st, bool 
     h->spmv_calls++;
     return;
   }
-  if (one_tile(h)) {  // the product, its zero rows and its split rows in one launch
+  if (one_tile(h)) {  // the product, its zero rows and (of few chunks) its split rows in one launch
     run_tile(h, 0, PlainSpec{x}, y, st, tile_rest(h, !skip_zero));
     h->spmv_calls++;
     return;
@@ -658,13 +658,21 @@ void gather_rows(const float* in, const int32_t* perm, int64_t n, int32_t w, flo
 // gathered afterwards: rows through rowinv / y gathered 14.7 / 16.7 at 2^16
 // rows, 20.6 / 21.5 at 2^18, 18.5 / 18.7 at 2^19, 78.5 / 74.0 at 2^20 (the
 // dependent load at every row's end), 465 / 411 at 2^22; with an unsplit long row
-// y is gathered too (R-MAT 2^18, split_len 0: 119 / 108).
+// y is gathered too (R-MAT 2^18, split_len 0: 119 / 108).  With workloads of more
+// than kMapWl entries nothing is read or written through a map: their wavefronts
+// are few, and each pays the dependent loads one after another.  Through the
+// maps / with x gathered at workloads of 512, 1024, 2048 and 8192 entries: a
+// uniform matrix of 430K entries 8.5 / 10.9, 10.9 / 12.2, 16.4 / 16.2, 64 / 50;
+// Chung-Lu 442K 12.5 / 12.1, 15.6 / 14.6, 21.6 / 19.2, 64 / 54; y through rowinv /
+// gathered at 8192: 72 / 56 (R-MAT 2^18, 8M entries), 76 / 63 (uniform 2^16, 8M),
+// 39.8 / 40.1 at 1,418 and 60.9 / 59.7 at 1,852 (16M entries).
 constexpr int64_t kMapNnz = (int64_t)1 << 19;
+constexpr int32_t kMapWl = 1024;
 constexpr int64_t kUserRows = (int64_t)1 << 18;
 
 // y := A x in the caller's ids
 void spmv_user(tc_handle* h, const float* x, float* y, hipStream_t st) {
-  if (one_tile(h) && h->nnz <= kMapNnz && hot_width(h, 0, h->n_wl) == 0) {
+  if (one_tile(h) && h->nnz <= kMapNnz && h->tile_wl[0] <= kMapWl && hot_width(h, 0, h->n_wl) == 0) {
     run_tile(h, 0, UserSpec<true>{x, h->d_cperm, h->d_rowinv}, y, st, tile_rest(h, true));
     h->spmv_calls++;
     return;
@@ -672,7 +680,7 @@ void spmv_user(tc_handle* h, const float* x, float* y, hipStream_t st) {
   gather_rows(x, h->d_cperm, h->n_cols, 1, h->d_xbuf, st);
   if (!h->relabel) {
     spmv_internal(h, h->d_xbuf, y, st);
-  } else if (one_tile(h) && h->n_rows <= kUserRows && !long_row(h, 0)) {
+  } else if (one_tile(h) && h->n_rows <= kUserRows && h->tile_wl[0] <= kMapWl && !long_row(h, 0)) {
     run_tile(h, 0, UserSpec<false>{h->d_xbuf, nullptr, h->d_rowinv}, y, st, tile_rest(h, true));
     h->spmv_calls++;
   } else {

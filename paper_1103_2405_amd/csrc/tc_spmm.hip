@@ -154,13 +154,40 @@ __device__ inline void write_row(float* __restrict__ Y, int32_t rid, int32_t k, 
 }
 
 // Cross-group sum of a row-major row: the groups took interleaved entries,
-// and an xor tree over the group bits of the lane id adds their sums.
+// and an xor tree over the group bits of the lane id adds their sums.  At the
+// first log2 V levels each lane passes on one half of its columns and adds up the
+// other; the last steps hand every lane all V sums (the additions of the whole
+// tree; 10 shuffles rather than 20 for V = 4 and 32 groups: 56.3 -> 48.5 us at k = 5 of
+// a uniform matrix of 2^17 rows and 2.1M entries, 56.4 -> 42.7 at k = 4).
 template <int V, int KG>
-__device__ inline void group_sum(Vec<V>& s) {
+__device__ inline void group_sum(Vec<V>& s, int lane) {
+  static_assert(V * KG <= kWave, "a level per halving");
+  // the half of (a, b) that this lane keeps, with the partner's
+  auto halve = [&](double a, double b, int o) {
+    const bool up = lane & o;
+    return (up ? b : a) + __shfl_xor(up ? a : b, o, kWave);
+  };
+  double t;
+  if constexpr (V == 4)
+    t = halve(halve(s.a[0], s.a[2], KG), halve(s.a[1], s.a[3], KG), 2 * KG);
+  else if constexpr (V == 2)
+    t = halve(s.a[0], s.a[1], KG);
+  else
+    t = s.a[0];
 #pragma unroll
-  for (int o = KG; o < kWave; o <<= 1)
-#pragma unroll
-    for (int i = 0; i < V; ++i) s.a[i] += __shfl_xor(s.a[i], o, kWave);
+  for (int o = V * KG; o < kWave; o <<= 1) t += __shfl_xor(t, o, kWave);
+  const int c = lane & (KG - 1);
+  if constexpr (V == 4) {
+    s.a[0] = __shfl(t, c, kWave);
+    s.a[1] = __shfl(t, c + 2 * KG, kWave);
+    s.a[2] = __shfl(t, c + KG, kWave);
+    s.a[3] = __shfl(t, c + 3 * KG, kWave);
+  } else if constexpr (V == 2) {
+    s.a[0] = __shfl(t, c, kWave);
+    s.a[1] = __shfl(t, c + KG, kWave);
+  } else {
+    s.a[0] = t;
+  }
 }
 
 // The slots of one step: SUB * G of them (G = 64 / KG groups), L per lane;
@@ -352,7 +379,7 @@ __device__ inline void spmm_item(const Wl& d, int32_t part, int32_t parts, bool 
   if (lead) {
     const int32_t lo = (int32_t)min<int64_t>((int64_t)part * kPiece, d.w_pad), hi = lo + min(kPiece, d.w_pad - lo);
     Vec<V> acc = rm_range<V, KG, F::R>(idx, val, xr, d.data_off, lo, hi, c, lane);
-    group_sum<V, KG>(acc);
+    group_sum<V, KG>(acc, lane);
     if (c.act && g0)
 #pragma unroll
       for (int i = 0; i < V; ++i)
@@ -373,8 +400,9 @@ __device__ inline void spmm_item(const Wl& d, int32_t part, int32_t parts, bool 
     const int64_t base = d.data_off + (int64_t)r * d.w_pad;
     const int32_t rid = layout == kChunk ? 0 : ld_nt(rowid + d.rowid_off + r);
     Vec<V> acc = d.w_pad > 2 * G ? rm_range<V, KG, F::R>(idx, val, xr, base, 0, d.w_pad, c, lane)
-                                 : rm_range<V, KG, 2>(idx, val, xr, base, 0, d.w_pad, c, lane);
-    group_sum<V, KG>(acc);
+                 : d.w_pad > G   ? rm_range<V, KG, 2>(idx, val, xr, base, 0, d.w_pad, c, lane)
+                                 : rm_range<V, KG, 1>(idx, val, xr, base, 0, d.w_pad, c, lane);
+    group_sum<V, KG>(acc, lane);
     if (!(c.act && g0)) continue;
     if (layout == kChunk) {
 #pragma unroll
@@ -565,6 +593,13 @@ size_t spmm_partial_doubles(tc_handle* h, int32_t k) {
   return (size_t)h->n_slots * h->mm_pieces * k;
 }
 
+// Row slices of a workload: 4 (the kernel has the figures), 2 where the workloads
+// are so small that wavefronts without a row to sum are most of the launch.
+// Four / two, us at k = 5 by workload size: 22.1 / 17.8 at 54 (19,810 rows of 28
+// entries), 28.3 / 25.6 at 108 (40,000 of 28), 27.1 / 27.6 at 128 (R-MAT 2^16),
+// 16.1 / 17.2, 24.6 / 26.5 and 26.4 / 29.3 at 256.
+constexpr int64_t kFewSlicesWl = 128;
+
 void spmm_internal(tc_handle* h, const float* X, float* Y, int32_t k, hipStream_t st, bool skip_empty,
                    const RwrEpi* epi, double* partial_ext, int32_t ldx) {
   if (ldx == 0) ldx = k;
@@ -573,7 +608,6 @@ void spmm_internal(tc_handle* h, const float* X, float* Y, int32_t k, hipStream_
   const RwrEpi ep = epi ? *epi : RwrEpi{0.0, nullptr};
   spmm_plan(h);
   const int32_t pieces = h->mm_pieces;
-  const int32_t slices = 4;  // row slices of a workload (the kernel has the figures)
   double* partial = nullptr;
   if (partial_ext) {
     partial = partial_ext;
@@ -600,6 +634,7 @@ void spmm_internal(tc_handle* h, const float* X, float* Y, int32_t k, hipStream_
   for (int t = 0; t < h->n_tiles; ++t) {
     const int64_t b = h->tile_wl_begin[t], e = h->tile_wl_begin[t + 1];
     const int64_t lead = h->mm_lead[t];
+    const int32_t slices = h->tile_wl[t] <= kFewSlicesWl ? 2 : 4;
     if (e > b) spmm_tile(h, t, b, e - b, lead, pieces, slices, X, ldx, Y, k, partial, epi != nullptr, ep, st);
   }
   if (h->n_split_rows > 0) {

@@ -324,10 +324,11 @@ __device__ inline void cm_range(const Wl& d, int32_t sl, int32_t slices, const i
 
 // Entries in flight per group of KG lanes: R of a row-major row or chunk; U x C
 // (rows x columns) of a column-major rectangle of one column (U1 x 1), of two or
-// three, of more.  Registers set the wavefronts: the deep form takes 104-173 VGPRs
-// (2 to 4 wavefronts per SIMD), the others 57-78 (6 to 8).  More wavefronts win where
-// X's part of a pass lies near (uniform 2^16 rows and columns, 1M entries, k = 4:
-// 71 -> 42 us, 32: 61 -> 46, 100: 239 -> 150), more in flight where it does not
+// three, of more.  Registers set the wavefronts: the deep form takes 93-181 VGPRs
+// (2 to 5 wavefronts per SIMD), the others 53-80 (6 to 8).  More wavefronts win where
+// X's part of a pass lies near (uniform 2^16 rows and columns, 1M entries, with the
+// row sums of every column shuffled whole, k = 4: 71 -> 42 us, 32: 61 -> 46, 100: 239 ->
+// 150; group_sum makes the 42 33), more in flight where it does not
 // (R-MAT 2^20, k = 32: 339 deep, 356 not) and where one wavefront has to sum a
 // long row (Chung-Lu 2^20 without split rows, five steps at k = 16: 2,180 / 2,890).
 // One lane a row (k = 1, 2, 4) has 64 entries in flight a wavefront to begin with.
